@@ -282,9 +282,10 @@ wq_status_t wq_conv_forward_debug_slab(const wq_plan_t *plan, void *stream, cons
  *                 [taps][Cout_pad/16][Cin/kstep][4][16][kstep/4]  at blob_Wq_off
  *                 sW fp32 [taps][groups][Cout_pad]                 at blob_sW_off
  *                 bias fp32 [Cout_pad]                             at blob_bias_off
- *   workspace   : xq int8 [N*H*W][Cin] (NHWC)                      at ws_xq_off
- *                 sx fp32 [N*H*W][groups]                          at ws_sx_off
- *                 partial sums fp32 [splits][N*H*W][Cout]          at ws_part_off (scratch, splits > 1)
+ *   workspace   : xq int8 [Cin/kstep][4][N*H*W][kstep/4]           at ws_xq_off
+ *                   (planes of one K-quarter of one MFMA K-step, pixels in order inside a plane)
+ *                 sx fp32 [groups][N*H*W]                          at ws_sx_off
+ *                   (a 3x3 plan keeps W+1 zero scales right before it)
  * Conventions as above: caller-owned device memory, calls enqueue on `stream`
  * and never synchronise, every argument is checked on the host.  Errors:
  * non-positive sizes, NULL pointers, Cin not a multiple of group_size ->
@@ -295,13 +296,13 @@ typedef struct wq_direct_plan wq_direct_plan_t;
 
 typedef struct {
     int32_t N, H, W, Cin, Cout, group_size, groups, P, Cout_pad, kstep;
-    int32_t splits, taps; /* splits: workgroups sharing the reduction of an output tile: the 9 taps
-                             (1, 3 or 9) or, for a linear layer, its groups (a power of two up to 16);
+    int32_t splits, taps; /* splits: 1 = the plan's own choice of how many waves share the reduction of
+                             an output tile, else the number wq_direct_plan_tune asked for;
                              taps: 9 for the 3x3 convolution, 1 for a linear layer */
     int32_t weight_bits;  /* 8, or 4 (W4A8) */
     int32_t reserved;     /* 0 */
     uint64_t blob_bytes, blob_Wq_off, blob_sW_off, blob_bias_off;
-    uint64_t ws_bytes, ws_xq_off, ws_sx_off, ws_part_off;
+    uint64_t ws_bytes, ws_xq_off, ws_sx_off, ws_part_off;   /* ws_part_off: the end of sx (nothing lies behind it) */
 } wq_direct_layout_t;
 
 wq_status_t wq_direct_plan_create(wq_direct_plan_t **out, int N, int H, int W, int Cin, int Cout,
@@ -326,10 +327,10 @@ wq_status_t wq_direct_plan_create_bits(wq_direct_plan_t **out, int N, int H, int
                                        int group_size, int weight_bits);
 wq_status_t wq_linear_plan_create_bits(wq_direct_plan_t **out, int R, int Cin, int Cout, int group_size,
                                        int weight_bits);
-/* Tuning override for tests and sweeps: the number of workgroups that share the reduction of
- * an output tile (wq_direct_layout_t::splits).  0 keeps the plan's own choice; a 3x3 plan takes
- * 1, 3 or 9, a linear plan a power of two up to 16 that divides its group count; anything else
- * -> UNSUPPORTED.  Changes ws_bytes: call it before sizing the workspace. */
+/* Tuning override for tests and sweeps: the number of waves that share the reduction of an output
+ * tile (wq_direct_layout_t::splits).  0 keeps the plan as it is, 1 is the plan's own choice; a 3x3
+ * plan takes 1, 3 or 9, a linear plan a power of two up to 16 that divides its group count; anything
+ * else -> UNSUPPORTED. */
 wq_status_t wq_direct_plan_tune(wq_direct_plan_t *plan, int splits);
 wq_status_t wq_direct_plan_destroy(wq_direct_plan_t *plan);
 wq_status_t wq_direct_plan_layout(const wq_direct_plan_t *plan, wq_direct_layout_t *out);
@@ -343,8 +344,7 @@ wq_status_t wq_direct_weight_prepare(wq_direct_plan_t *plan, void *stream, const
 wq_status_t wq_direct_quantize(const wq_direct_plan_t *plan, void *stream, const float *x_dev,
                                void *workspace_dev, size_t workspace_bytes);
 
-/* The convolution proper on the quantized operands; writes y_dev [N][H][W][Cout] fp32.
- * May use the partial-sum area of the workspace. */
+/* The convolution proper on the quantized operands; writes y_dev [N][H][W][Cout] fp32. */
 wq_status_t wq_direct_conv(const wq_direct_plan_t *plan, void *stream, void *workspace_dev,
                            size_t workspace_bytes, const void *weight_blob_dev, size_t blob_bytes,
                            float *y_dev);

@@ -7,13 +7,8 @@
 //   y[p][o] = bias[o] + sum over the 9 taps and the groups of
 //             float(int32 dot product) * sx[shifted pixel][group] * sw[tap][group][o]
 //                                                                 k_direct_conv
-// k_direct_conv is an implicit GEMM: a workgroup owns 64 consecutive output pixels x 64 output
-// channels; per K-step the 256 threads copy four 16-channel weight blocks (already in MFMA
-// operand order) and gather the 64 input pixels of the current tap - shifted by the tap's
-// offset, zero where the window leaves the image - into MFMA operand order in LDS, plus the
-// 64+64 scales of the group.  Two K-steps are in flight in a statically indexed register
-// ring; every wave computes a 2x2 arrangement of 16x16 int8 MFMA blocks into fresh int32
-// accumulators per group and folds them into fp32 with the two scales.
+// k_direct_conv is an implicit GEMM without LDS staging: both operands lie in memory in the order
+// the MFMA reads them, a wave loads them straight into its registers (see the kernel).
 #include <float.h>
 
 #include <cstdlib>
@@ -28,7 +23,10 @@ struct wq_direct_plan {
     int N, H, W, Cin, Cout, g, groups, P, Cout_pad, kstep;
     int taps;     // 9 = 3x3 convolution, 1 = linear layer (every row is its own "image")
     int wbits;    // width of the weight codes: 8, or 4 (W4A8: two codes per byte)
-    int splits;   // the 9 filter taps are shared out over this many workgroups per output tile (1, 3 or 9)
+    // the kernel instance and its launch shape (choose_tile): 16-row blocks per wave along channels and
+    // pixels, waves per workgroup that split a wave tile's reduction, wave tiles per workgroup
+    int no, nb, slices, wo, wt;
+    int splits;   // 1, or the number of slices wq_direct_plan_tune asked for
     wq_direct_layout_t lay;
     std::atomic<int> prepared;
 };
@@ -38,21 +36,30 @@ namespace {
 constexpr unsigned kInvalid = kPastEnd;
 
 // ------------------------------------------------------------ activations
-// 8 lanes per (pixel, group); a lane owns CPL = g/8 consecutive channels.
+// xq is stored as [Cin/kstep][4][P][kstep/4]: planes of one K-quarter of one MFMA K-step, pixels
+// in order inside a plane.  The wave that multiplies 16 consecutive pixels then reads four runs of
+// 16 pieces, and a filter tap shifts all of them by the same number of bytes.  (From a pixel-major
+// tensor the same load takes 64 cycles of the address unit instead of 16: neighbouring lanes hold
+// different pixels.)  Scales are [groups][P], so that neighbouring pixels' scales are neighbours too.
+// 8 lanes per (pixel, group); a lane owns CPL = g/8 consecutive channels.  A workgroup holds 16
+// pixels x 2 groups: its code stores fill whole 128-byte lines.
 template <int CPL>
 __global__ __launch_bounds__(256) void k_quantize_pixels(const float *__restrict__ x,
                                                          int8_t *__restrict__ xq,
-                                                         float *__restrict__ sx, int units,
-                                                         int Cin, int groups) {
-    const int tid = threadIdx.x, l8 = tid & 7;
-    const int unit = blockIdx.x * 32 + (tid >> 3);
-    if (unit >= units) return;   // the 8 lanes of a unit leave together
-    const int p = unit / groups, gi = unit - p * groups;
-    const size_t e0 = (size_t)p * Cin + (size_t)gi * (CPL * 8) + (size_t)l8 * CPL;
+                                                         float *__restrict__ sx, int P, int Cin,
+                                                         int groups, int gpairs, int guard) {
+    if (blockIdx.x == 0)   // the scales a window position before the first pixel would read
+        for (int e = threadIdx.x; e < guard; e += 256) sx[e - guard] = 0.0f;
+    const int tid = threadIdx.x, l8 = tid & 7, unit = tid >> 3;
+    const int pb = blockIdx.x / gpairs, gi = (blockIdx.x % gpairs) * 2 + (unit >> 4);
+    const int row = unit & 15, p = pb * 16 + row;
+    if (p >= P || gi >= groups) return;   // the 8 lanes of a unit leave together
+    const int c0 = gi * (CPL * 8) + l8 * CPL;
+    const float *src = x + (size_t)p * Cin + c0;
     float v[CPL];
 #pragma unroll
     for (int k = 0; k < CPL / 4; ++k) {
-        const float4 t = *reinterpret_cast<const float4 *>(x + e0 + 4 * k);
+        const float4 t = *reinterpret_cast<const float4 *>(src + 4 * k);
         v[4 * k] = t.x; v[4 * k + 1] = t.y; v[4 * k + 2] = t.z; v[4 * k + 3] = t.w;
     }
     uint32_t a = 0;
@@ -72,18 +79,18 @@ __global__ __launch_bounds__(256) void k_quantize_pixels(const float *__restrict
     for (int k = 0; k < CPL / 4; ++k)
         words[k] = quant_code(v[4 * k], r) | (quant_code(v[4 * k + 1], r) << 8) |
                    (quant_code(v[4 * k + 2], r) << 16) | (quant_code(v[4 * k + 3], r) << 24);
-    uint32_t *dst = reinterpret_cast<uint32_t *>(xq + e0);
-    if constexpr (CPL == 4) {
-        dst[0] = words[0];
-    } else if constexpr (CPL == 8) {
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(words[0], words[1]);
+    if constexpr (CPL == 4) {   // K-step 32: the lane's 4 codes are half of a K-quarter of 8
+        *reinterpret_cast<uint32_t *>(xq + ((size_t)(gi * 4 + (l8 >> 1)) * P + p) * 8 + (l8 & 1) * 4) = words[0];
+    } else if constexpr (CPL == 8) {   // K-step 64: half of a K-quarter of 16
+        *reinterpret_cast<uint2 *>(xq + ((size_t)(gi * 4 + (l8 >> 1)) * P + p) * 16 + (l8 & 1) * 8) =
+            make_uint2(words[0], words[1]);
     } else {
 #pragma unroll
         for (int k = 0; k < CPL / 16; ++k)
-            *reinterpret_cast<uint4 *>(dst + 4 * k) =
+            *reinterpret_cast<uint4 *>(xq + ((size_t)((c0 >> 4) + k) * P + p) * 16) =
                 make_uint4(words[4 * k], words[4 * k + 1], words[4 * k + 2], words[4 * k + 3]);
     }
-    if (l8 == 0) sx[unit] = s;
+    if (l8 == 0) sx[(size_t)gi * P + p] = s;
 }
 
 // ------------------------------------------------------------ convolution
@@ -94,268 +101,279 @@ struct DArgs {
     const float *sW;
     const float *bias;
     float *y;
-    float *part;   // splits > 1: partial sums [split][P][Cout], summed (+ bias) by k_direct_reduce
-    int N, H, W, Cin, Cout, Cout_pad, P, log2g, splits, taps;
+    int H, W, Cin, Cout, Cout_pad, P, log2g, taps;
+    // how a workgroup's waves share its work: `slices` waves split the reduction of one wave tile,
+    // wo x wt wave tiles lie side by side along channels x pixels (slices * wo * wt waves)
+    int slices, wo, wt;
+    int nOt, total, per_xcd;   // workgroup tiles along channels, workgroups, share of each XCD
 };
 
-// W4: the weight codes are 4 bits wide, two per byte (see the weight kernels for the packing of a
-// 16-byte piece into 8).  A weight loader fetches the 8 packed bytes of its 16-byte LDS piece and
-// unpacks them on the way into LDS as 16 * code (a nibble moved to the top of its byte), so the
-// MFMA loop is the 8-bit one; the factor 16 leaves with the weight scales, which are staged as
-// sw / 16 (exact), and 16 * |sum| stays below 2^24 for every group size.
-template <bool K64, bool CPG1, bool W4>
-__global__ __launch_bounds__(256, 2) void k_direct_conv(const DArgs a) {
-    constexpr int KSTEP = K64 ? 64 : 32, KB = KSTEP / 4;
-    constexpr int BLK = 16 * KSTEP;   // bytes of one K-step of a 16-row block
-    constexpr int LPT = K64 ? 2 : 1;  // 16-byte loads per thread per K-step
-    constexpr int PD = 2;             // K-steps in flight (deeper rings measured no faster)
-    __shared__ __attribute__((aligned(16))) char opnd[2][8 * BLK];   // blocks 0-3 weights, 4-7 pixels
-    __shared__ __attribute__((aligned(16))) float sc[2][128];        // 64 weight scales, 64 pixel scales
-
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
-    const int ob0 = blockIdx.x * 4, p0 = blockIdx.y * 64;
-    const int Cin = a.Cin, Cout_pad = a.Cout_pad, H = a.H, W = a.W, P = a.P;
-    const int groups = Cin >> a.log2g, cps = Cin / KSTEP;
-    const int cpg_mask = ((1 << a.log2g) / KSTEP) - 1;
-
-    const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int8_t *>(a.Wq), 0,
-        (int)(((unsigned)a.taps * (unsigned)Cout_pad * (unsigned)Cin) >> (W4 ? 1 : 0)), kBufFlags);
-    const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int8_t *>(a.xq), 0, (int)((unsigned)P * (unsigned)Cin), kBufFlags);
-    const __amdgpu_buffer_rsrc_t rSW = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(a.sW), 0, (int)((unsigned)a.taps * (unsigned)groups * (unsigned)Cout_pad * 4u), kBufFlags);
-    const __amdgpu_buffer_rsrc_t rSX = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(a.sx), 0, (int)((unsigned)P * (unsigned)groups * 4u), kBufFlags);
-
-    // What this thread copies per K-step.
-    //   weights (K64: load 0 of every thread; K32: threads 0..127): a linear 16-byte piece of the
-    //     four 16-channel blocks;
-    //   pixels  (K64: load 1 of every thread; K32: threads 128..255): 16 bytes of one of the 64
-    //     pixel rows; `nb` = which bits of the 3x3 neighbourhood of that pixel lie inside the image.
-    const bool w_loader = K64 || w < 2;
-    unsigned vW = kInvalid;
-    {
-        const int c = K64 ? tid : (tid & 127), blk = c / (BLK / 16), off = (c % (BLK / 16)) * 16;
-        if ((ob0 + blk) * 16 < Cout_pad) vW = (unsigned)((ob0 + blk) * 16 * Cin + off) >> (W4 ? 1 : 0);
-    }
-    // pixel row and 16-byte piece of the gather, and where the piece goes in MFMA operand order
-    const int xr = K64 ? (tid >> 2) : ((tid & 127) >> 1);   // row 0..63 inside the pixel tile
-    const int xpc = K64 ? (tid & 3) : (tid & 1);            // 16-byte piece inside the row's K-step
-    unsigned nb = 0;
-    int prow = p0 + xr;
-    {
-        const int pc = min(prow, P - 1);
-        const int ww = pc % W, hh = (pc / W) % H;
-        if (prow < P) {
-            if (a.taps == 1) nb = 1u;   // linear layer: the row itself
-            else
-#pragma unroll
-            for (int u = 0; u < 3; ++u)
-#pragma unroll
-                for (int v = 0; v < 3; ++v)
-                    if (hh + u - 1 >= 0 && hh + u - 1 < H && ww + v - 1 >= 0 && ww + v - 1 < W)
-                        nb |= 1u << (u * 3 + v);
-        }
-    }
-    // scales: wave 0 the 64 weight scales, wave 1 the 64 pixel scales (waves 2,3 repeat them
-    // so that every wave issues the same loads; only waves 0 and 1 store them)
-    const bool sc_w = (w & 1) == 0;
-    unsigned nb_s = 0;
-    int prow_s = p0 + lane;
-    {
-        const int pc = min(prow_s, P - 1);
-        const int ww = pc % W, hh = (pc / W) % H;
-        if (prow_s < P) {
-            if (a.taps == 1) nb_s = 1u;
-            else
-#pragma unroll
-            for (int u = 0; u < 3; ++u)
-#pragma unroll
-                for (int v = 0; v < 3; ++v)
-                    if (hh + u - 1 >= 0 && hh + u - 1 < H && ww + v - 1 >= 0 && ww + v - 1 < W)
-                        nb_s |= 1u << (u * 3 + v);
-        }
-    }
-    const unsigned vSW = (ob0 * 16 + lane) < Cout_pad ? (unsigned)(ob0 * 16 + lane) * 4u : kInvalid;
-
-    v4i pre[PD][LPT];
-    float psc[PD];
-    // the loader walks (tap t, K-step s) in order; its cursor is kept incrementally (uniform
-    // scalars) and stops at the last step, which the tail of the ring fetches again
-    // this workgroup's share of the reduction: taps [t_beg, t_end) (all 9, a row of the window, or
-    // a single tap) times K-steps [s_beg, s_end) (all of them; a linear layer with few rows splits
-    // its one tap along K instead, in whole groups)
-    const bool ksplit = a.taps == 1;
-    const int tps = ksplit ? 1 : a.taps / a.splits, t_beg = ksplit ? 0 : (int)blockIdx.z * tps, t_end = t_beg + tps;
-    const int sps = ksplit ? cps / a.splits : cps, s_beg = ksplit ? (int)blockIdx.z * sps : 0, s_end = s_beg + sps;
-    int t_f = t_beg, s_f = s_beg, dp_f = a.taps == 1 ? 0 : (t_beg / 3 - 1) * W + (t_beg % 3 - 1);
-    auto fetch = [&](v4i (&dst)[LPT], float &dsc) {
-        const int t = t_f, s = s_f, dp = dp_f;
-        const unsigned gam = (unsigned)(s * KSTEP) >> a.log2g;
-        // pixels: row (prow + dp), bytes s*KSTEP + piece*16 ..
-        const unsigned vX = ((nb >> t) & 1u)
-                                ? (unsigned)(prow + dp) * (unsigned)Cin + (unsigned)(s * KSTEP + xpc * 16)
-                                : kInvalid;
-        const unsigned soW = ((unsigned)t * Cout_pad * Cin + (unsigned)s * BLK) >> (W4 ? 1 : 0);
-        if constexpr (K64) {
-            if constexpr (W4) {
-                const v2i pk = __builtin_amdgcn_raw_buffer_load_b64(rW, vW, soW, 0);
-                dst[0] = v4i{pk.x, pk.y, 0, 0};
-            } else {
-                dst[0] = __builtin_amdgcn_raw_buffer_load_b128(rW, vW, soW, 0);
-            }
-            dst[1] = __builtin_amdgcn_raw_buffer_load_b128(rX, vX, 0, 0);
-        } else {
-            // (W4: a weight loader's 16 bytes are its 8 packed bytes and its neighbour's, which it
-            // ignores: one load instruction for both kinds of loader keeps the waves in step)
-            dst[0] = __builtin_amdgcn_raw_buffer_load_b128(w_loader ? rW : rX, w_loader ? vW : vX,
-                                                           w_loader ? soW : 0u, 0);
-        }
-        const unsigned vs = sc_w ? vSW
-                                 : (((nb_s >> t) & 1u) ? ((unsigned)(prow_s + dp) * (unsigned)groups + gam) * 4u
-                                                       : kInvalid);
-        const unsigned so = sc_w ? ((unsigned)t * groups + gam) * (unsigned)Cout_pad * 4u : 0u;
-        dsc = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sc_w ? rSW : rSX, vs, so, 0));
-        if (!(t_f == t_end - 1 && s_f == s_end - 1)) {   // advance unless this was the last step
-            if (++s_f == s_end) {
-                s_f = s_beg;
-                ++t_f;
-                dp_f = (t_f == 3 || t_f == 6) ? dp_f + W - 2 : dp_f + 1;   // next row of the window, or next column
-            }
-        }
-    };
-    // LDS position of a gathered pixel piece in MFMA operand order [block][q][row16][KB bytes]
-    const int xblk = 4 + (xr >> 4), xr16 = xr & 15;
-    auto unpack = [](const v4i &pk) {   // 8 packed bytes -> 16 bytes of 16 * code
-        if constexpr (!W4) return pk;
-        const unsigned p0 = (unsigned)pk.x, p1 = (unsigned)pk.y;
-        return v4i{(int)((p0 << 4) & 0xf0f0f0f0u), (int)(p0 & 0xf0f0f0f0u),
-                   (int)((p1 << 4) & 0xf0f0f0f0u), (int)(p1 & 0xf0f0f0f0u)};
-    };
-    auto commit = [&](int buf, const v4i (&src)[LPT], float ssc) {
-        if constexpr (K64) {
-            *reinterpret_cast<v4i *>(&opnd[buf][tid * 16]) = unpack(src[0]);
-            *reinterpret_cast<v4i *>(&opnd[buf][xblk * BLK + xpc * 256 + xr16 * 16]) = src[1];
-        } else {
-            if (w_loader) {
-                *reinterpret_cast<v4i *>(&opnd[buf][tid * 16]) = unpack(src[0]);
-            } else {   // 16 bytes = two K-quarters of 8 bytes
-                char *d = &opnd[buf][xblk * BLK + (2 * xpc) * 128 + xr16 * 8];
-                *reinterpret_cast<v2i *>(d) = v2i{src[0].x, src[0].y};
-                *reinterpret_cast<v2i *>(d + 128) = v2i{src[0].z, src[0].w};
-            }
-        }
-        if (w < 2) sc[buf][w * 64 + lane] = (W4 && w == 0) ? ssc * 0.0625f : ssc;
-    };
-
-    v4i acc[2][2];
-    float4 Mc[2][2];
-#pragma unroll
-    for (int no = 0; no < 2; ++no)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            acc[no][nt] = v4i{0, 0, 0, 0};
-            Mc[no][nt] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-
-    const int NI = tps * sps;
-#pragma unroll
-    for (int u = 0; u < PD; ++u) fetch(pre[u], psc[u]);
-    commit(0, pre[0], psc[0]);
-    __syncthreads();
-    for (int i0 = 0; i0 < NI; i0 += PD) {
-#pragma unroll
-      for (int u = 0; u < PD; ++u) {
-        const int it = i0 + u;
-        if (it >= NI) break;
-        const int buf = u & 1;   // PD is even, so it & 1 == u & 1
-        fetch(pre[u], psc[u]);   // step it + PD (or the last one again); slot u held step it, already in LDS
-        v4i av[2], bv[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const char *pa = &opnd[buf][(2 * wn + e) * BLK + lane * KB];
-            const char *pb = &opnd[buf][(4 + 2 * wm + e) * BLK + lane * KB];
-            if constexpr (K64) {
-                av[e] = *reinterpret_cast<const v4i *>(pa);
-                bv[e] = *reinterpret_cast<const v4i *>(pb);
-            } else {
-                const v2i ta = *reinterpret_cast<const v2i *>(pa), tb = *reinterpret_cast<const v2i *>(pb);
-                av[e] = v4i{ta.x, ta.y, 0, 0};
-                bv[e] = v4i{tb.x, tb.y, 0, 0};
-            }
-        }
-#pragma unroll
-        for (int no = 0; no < 2; ++no)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                const v4i c0 = CPG1 ? v4i{0, 0, 0, 0} : acc[no][nt];
-                if constexpr (K64) {
-                    acc[no][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[no], bv[nt], c0, 0, 0, 0);
-                } else {
-                    const long x = __builtin_bit_cast(long, v2i{av[no].x, av[no].y});
-                    const long y = __builtin_bit_cast(long, v2i{bv[nt].x, bv[nt].y});
-                    acc[no][nt] = __builtin_amdgcn_mfma_i32_16x16x32_i8(x, y, c0, 0, 0, 0);
-                }
-            }
-        if (CPG1 || ((it + 1) & cpg_mask) == 0) {   // last K-step of a group (a share is a whole number of groups)
-#pragma unroll
-            for (int no = 0; no < 2; ++no) {
-                const v4f sw = *reinterpret_cast<const v4f *>(&sc[buf][(2 * wn + no) * 16 + 4 * q]);
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
-                    const float sxv = sc[buf][64 + (2 * wm + nt) * 16 + l16];
-                    Mc[no][nt].x = __builtin_fmaf((float)acc[no][nt][0], sw.x * sxv, Mc[no][nt].x);
-                    Mc[no][nt].y = __builtin_fmaf((float)acc[no][nt][1], sw.y * sxv, Mc[no][nt].y);
-                    Mc[no][nt].z = __builtin_fmaf((float)acc[no][nt][2], sw.z * sxv, Mc[no][nt].z);
-                    Mc[no][nt].w = __builtin_fmaf((float)acc[no][nt][3], sw.w * sxv, Mc[no][nt].w);
-                    if constexpr (!CPG1) acc[no][nt] = v4i{0, 0, 0, 0};
-                }
-            }
-        }
-        if (it + 1 < NI) commit(buf ^ 1, pre[(u + 1) % PD], psc[(u + 1) % PD]);
-        __syncthreads();
-      }
-    }
-    // + bias, NHWC store: the lane holds channels 4q..4q+3 of pixel l16 in each block
-    const bool vec = (a.Cout & 3) == 0;   // rows of y are 16-byte aligned
-    const bool final_sum = a.splits == 1;
-    float *out = final_sum ? a.y : a.part + (size_t)blockIdx.z * P * a.Cout;
-#pragma unroll
-    for (int no = 0; no < 2; ++no) {
-        const int o = (ob0 + 2 * wn + no) * 16 + 4 * q;
-        float bv[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bv[r] = (final_sum && o + r < a.Cout) ? a.bias[o + r] : 0.f;
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int p = p0 + (2 * wm + nt) * 16 + l16;
-            if (p >= P || o >= a.Cout) continue;
-            const float mv[4] = {Mc[no][nt].x + bv[0], Mc[no][nt].y + bv[1], Mc[no][nt].z + bv[2],
-                                 Mc[no][nt].w + bv[3]};
-            float *dst = out + (size_t)p * a.Cout + o;
-            if (vec) {   // o is a multiple of 4, so o + 3 < Cout too
-                __builtin_nontemporal_store(v4f{mv[0], mv[1], mv[2], mv[3]}, reinterpret_cast<v4f *>(dst));
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (o + r < a.Cout) __builtin_nontemporal_store(mv[r], dst + r);
-            }
-        }
+// Broadcast of 16-lane rows: lane l of `v` holds the value of pixel l of the wave's 64 (16) pixels;
+// r[f] gets pixel 16 f + l % 16 in every lane.
+template <int NB>
+__device__ __forceinline__ void spread_rows(float v, float (&r)[NB]) {
+    static_assert(NB == 1 || NB == 4, "row blocks per wave");
+    if constexpr (NB == 1) {
+        r[0] = v;
+    } else {
+        const unsigned u = __float_as_uint(v);
+        const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // rows 0 0 2 2 | 1 1 3 3
+        const auto e = __builtin_amdgcn_permlane32_swap(s[0], s[0], false, false);
+        const auto o = __builtin_amdgcn_permlane32_swap(s[1], s[1], false, false);
+        r[0] = __uint_as_float(e[0]);
+        r[1] = __uint_as_float(o[0]);
+        r[2] = __uint_as_float(e[1]);
+        r[3] = __uint_as_float(o[1]);
     }
 }
 
-// y = bias + sum of the per-split partial sums (splits > 1)
-__global__ __launch_bounds__(256) void k_direct_reduce(const float *__restrict__ part,
-                                                       const float *__restrict__ bias,
-                                                       float *__restrict__ y, int total, int Cout,
-                                                       int splits) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= total) return;
-    float acc = bias[e % Cout];
-    for (int z = 0; z < splits; ++z) acc += part[(size_t)z * total + e];
-    __builtin_nontemporal_store(acc, &y[e]);
+template <int R>
+__device__ __forceinline__ float quad_bcast(float v) {   // lane 4k + R of every quad to its four lanes
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), R * 0x55, 0xf, 0xf, true));
+}
+
+// A wave owns a (16 NO channels) x (16 NB pixels) tile and one slice of its reduction (whole
+// groups of the flat sequence tap-major, then channels).  Operands go from memory straight into
+// the registers the MFMA reads (both tensors are in its operand order) and are requested D
+// K-steps ahead; there is no LDS and no barrier before the slices are added up at the end, so a
+// wave waits for nothing but its own loads.
+//   bound: 12 vector-ALU instructions and one MFMA per 16x16 block and group (46 cycles of a
+//   SIMD, the two do not overlap), against 64 bytes per cycle and CU into registers: with NO x NB
+//   = 2 x 4 blocks a block costs 768 bytes = 12 cycles of the CU's load path for 11.5 of its
+//   four SIMDs.
+//   scales: one word per lane and load (the 64 pixels' scales in one load, spread over the lanes by
+//   row swaps; the channel scales of a quarter by DPP quad broadcasts): 256 bytes per load where a
+//   16-byte load per lane would move 1 KiB for the same 16 values, on the busier of the two paths.
+//   With one K-step per group the MFMA starts from kMagic instead of 0, which makes its int32
+//   result the bit pattern of 1.5 * 2^23 + sum: a subtraction (2.4 cycles) then replaces the
+//   conversion (4.3).  Exact while |sum| < 2^22: 64 * 127 * 127 and, for 4-bit weights, 64 * 16 * 7 * 127.
+// W4: the weight codes are 4 bits wide, two per byte (see the weight kernels for the packing of a
+// 16-byte piece into 8).  A lane loads the packed half of its piece and unpacks it as 16 * code
+// (a nibble moved to the top of its byte), so the MFMA loop is the 8-bit one; the factor 16 leaves
+// with the sums (exact), and 16 * |sum| stays below 2^24 for every group size.
+template <bool K64, bool CPG1, bool W4, bool T9, int NO, int NB, int D, int NWMAX>
+__global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
+    constexpr int KSTEP = K64 ? 64 : 32, KB = KSTEP / 4, BLK = 16 * KSTEP;
+    constexpr int RS = 16 * NO + 4;                        // floats per pixel row of the LDS staging
+    extern __shared__ __attribute__((aligned(16))) float part_s[];   // [waves][16][RS]
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ks = w % a.slices, wtile = w / a.slices, wo = wtile % a.wo, wt = wtile / a.wo;
+    // workgroup ids go round-robin over the XCDs: each takes a contiguous share of the tile order
+    // (channel tiles fastest), whose pixels its L2 then holds
+    const int logical = (int)(blockIdx.x & 7u) * a.per_xcd + (int)(blockIdx.x >> 3);
+    if (logical >= a.total) return;   // the whole workgroup leaves, before any barrier
+    const int ob0 = ((logical % a.nOt) * a.wo + wo) * NO, p0 = ((logical / a.nOt) * a.wt + wt) * 16 * NB;
+    const int Cin = a.Cin, P = a.P, groups = Cin >> a.log2g, cps = Cin / KSTEP;
+    const int cpg = (1 << a.log2g) / KSTEP;
+    // the pixel buffer starts the largest backward shift of a filter tap (a row and a pixel) early, so
+    // that shifts are non-negative scalar offsets; lanes whose pixel leaves the image load nothing
+    const int back = T9 ? a.W + 1 : 0;
+
+    const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int8_t *>(a.Wq), 0,
+        (int)(((unsigned)a.taps * (unsigned)a.Cout_pad * (unsigned)Cin) >> (W4 ? 1 : 0)), kBufFlags);
+    const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int8_t *>(a.xq) - back * KB, 0, (int)((unsigned)P * (unsigned)Cin + (unsigned)(back * KB)), kBufFlags);
+    const __amdgpu_buffer_rsrc_t rSW = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(a.sW), 0, (int)((unsigned)a.taps * (unsigned)groups * (unsigned)a.Cout_pad * 4u), kBufFlags);
+    const __amdgpu_buffer_rsrc_t rSX = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(a.sx) - back, 0, (int)(((unsigned)P * (unsigned)groups + (unsigned)back) * 4u), kBufFlags);
+
+    // which of the 9 window positions of the lane's pixel of each row block lie OUTSIDE the image
+    // (columns past the last pixel compute on whatever is there and are not stored)
+    unsigned out[NB], vX[NB];
+#pragma unroll
+    for (int f = 0; f < NB; ++f) {
+        const int p = p0 + 16 * f + l16;
+        vX[f] = (unsigned)(q * P + p) * (unsigned)KB;
+        if constexpr (T9) {
+            const int ww = p % a.W, hh = (p / a.W) % a.H;
+            out[f] = (hh == 0 ? 0x007u : 0u) | (hh == a.H - 1 ? 0x1c0u : 0u) | (ww == 0 ? 0x049u : 0u) |
+                     (ww == a.W - 1 ? 0x124u : 0u);
+        }
+    }
+
+    // ---- the loader: its cursor walks (tap, K-step) of the wave's slice and stops at the end ----
+    const int taps = T9 ? 9 : 1, G = taps * groups;
+    const int g_beg = ks * G / a.slices, g_end = (ks + 1) * G / a.slices;
+    const int NI = (g_end - g_beg) * cpg;
+    int t_f = g_beg / groups, gam_f = g_beg - t_f * groups, k_f = 0, left_f = NI;
+    const unsigned vW = (unsigned)(lane * KB) >> (W4 ? 1 : 0), vSW = (unsigned)(4 * q + (lane & 3)) * 4u, vSX = (unsigned)(p0 + (lane & (16 * NB - 1))) * 4u;
+    const unsigned blkW = 16u * (unsigned)Cin, jumpW = (unsigned)a.Cout_pad * (unsigned)Cin - blkW;   // next tap's plane
+    const unsigned stepX = 4u * (unsigned)P * (unsigned)KB, stepSX = (unsigned)P * 4u, stepSW = (unsigned)a.Cout_pad * 4u;
+    unsigned oW = (unsigned)t_f * (unsigned)a.Cout_pad * (unsigned)Cin + (unsigned)ob0 * blkW + (unsigned)(gam_f * cpg) * BLK;
+    unsigned oSW = (unsigned)g_beg * stepSW + (unsigned)ob0 * 64u;
+    int col_f = T9 ? t_f % 3 : 0;                      // the tap's column in the window
+    unsigned shift = T9 ? (unsigned)((t_f / 3) * a.W + col_f) : 0u;   // pixels from the buffer's start, = back + dp
+    unsigned oX = (unsigned)(gam_f * cpg) * stepX + shift * (unsigned)KB, oSX = (unsigned)gam_f * stepSX + shift * 4u;
+    v4i av[D][NO], bv[D][NB];
+    float swv[D][NO], sxv[D];
+    auto fetch = [&](int slot) {   // (slot is a constant after unrolling)
+#pragma unroll
+        for (int e = 0; e < NO; ++e) {
+            const unsigned so = (oW + (unsigned)e * blkW) >> (W4 ? 1 : 0);
+            if constexpr (K64 && !W4) {
+                av[slot][e] = __builtin_amdgcn_raw_buffer_load_b128(rW, vW, so, 0);
+            } else if constexpr (K64 || !W4) {
+                const v2i t = __builtin_amdgcn_raw_buffer_load_b64(rW, vW, so, 0);
+                av[slot][e] = v4i{t.x, t.y, 0, 0};
+            } else {
+                av[slot][e] = v4i{(int)__builtin_amdgcn_raw_buffer_load_b32(rW, vW, so, 0), 0, 0, 0};
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < NB; ++f) {   // a pixel outside the image: bit 31 of the offset, past the end
+            const unsigned vo = T9 ? vX[f] | ((out[f] << (31 - t_f)) & 0x80000000u) : vX[f];
+            if constexpr (K64) {
+                bv[slot][f] = __builtin_amdgcn_raw_buffer_load_b128(rX, vo, oX, 0);
+            } else {
+                const v2i t = __builtin_amdgcn_raw_buffer_load_b64(rX, vo, oX, 0);
+                bv[slot][f] = v4i{t.x, t.y, 0, 0};
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < NO; ++e)
+            swv[slot][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSW, vSW, oSW + 64u * e, 0));
+        // (a pixel outside the image takes some other pixel's scale, or the zeros before the first: its codes are 0)
+        sxv[slot] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX, oSX, 0));
+        // branch-free scalar bookkeeping (a branch here would let the compiler sink the
+        // dequantization of all D steps to the end of the round, with their sums in registers)
+        const bool go = --left_f > 0;
+        k_f += go ? 1 : 0;
+        const bool ng = go && k_f == cpg;
+        k_f = ng ? 0 : k_f;
+        gam_f += ng ? 1 : 0;
+        const bool nt = T9 && gam_f == groups;
+        gam_f = nt ? 0 : gam_f;
+        oW += (go ? (unsigned)BLK : 0u) + (nt ? jumpW : 0u);
+        oSW += ng ? stepSW : 0u;
+        oX += go ? stepX : 0u;
+        oSX += ng ? stepSX : 0u;
+        if constexpr (T9) {
+            t_f += nt ? 1 : 0;
+            const unsigned d = col_f == 2 ? (unsigned)(a.W - 2) : 1u;
+            shift += nt ? d : 0u;
+            col_f = nt ? (col_f == 2 ? 0 : col_f + 1) : col_f;
+            oX = nt ? shift * (unsigned)KB : oX;
+            oSX = nt ? shift * 4u : oSX;
+        }
+    };
+    auto unpack = [](const v4i &pk) {
+        if constexpr (!W4) return pk;
+        const unsigned a0 = (unsigned)pk.x, a1 = (unsigned)pk.y;
+        if constexpr (K64)
+            return v4i{(int)((a0 << 4) & 0xf0f0f0f0u), (int)(a0 & 0xf0f0f0f0u), (int)((a1 << 4) & 0xf0f0f0f0u),
+                       (int)(a1 & 0xf0f0f0f0u)};
+        return v4i{(int)((a0 << 4) & 0xf0f0f0f0u), (int)(a0 & 0xf0f0f0f0u), 0, 0};
+    };
+
+    float4 Mc[NO][NB];
+    v4i acc[NO][NB];
+#pragma unroll
+    for (int e = 0; e < NO; ++e)
+#pragma unroll
+        for (int f = 0; f < NB; ++f) {
+            Mc[e][f] = make_float4(0.f, 0.f, 0.f, 0.f);
+            acc[e][f] = v4i{0, 0, 0, 0};
+        }
+#pragma unroll
+    for (int d = 0; d < D; ++d) {   // in the order the loop expects them back
+        fetch(d);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const v4i magic = {kMagic, kMagic, kMagic, kMagic};
+    int k_c = 0;
+    auto compute = [&](int u) {   // the K-step in slot u (a constant after unrolling)
+        const bool done = CPG1 || ++k_c == cpg;   // the step completes a group: dequantize
+        k_c = done ? 0 : k_c;
+        float sx[NB];
+        if (done) spread_rows<NB>(sxv[u], sx);
+#pragma unroll
+        for (int e = 0; e < NO; ++e) {
+            const v4i aw = unpack(av[u][e]);
+            v4i P4[NB];
+#pragma unroll
+            for (int f = 0; f < NB; ++f) {
+                const v4i c0 = CPG1 ? magic : acc[e][f];
+                if constexpr (K64) {
+                    P4[f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aw, bv[u][f], c0, 0, 0, 0);
+                } else {
+                    const long x = __builtin_bit_cast(long, v2i{aw.x, aw.y});
+                    const long y = __builtin_bit_cast(long, v2i{bv[u][f].x, bv[u][f].y});
+                    P4[f] = __builtin_amdgcn_mfma_i32_16x16x32_i8(x, y, c0, 0, 0, 0);
+                }
+            }
+            if (done) {
+                const float s0 = quad_bcast<0>(swv[u][e]), s1 = quad_bcast<1>(swv[u][e]),
+                            s2 = quad_bcast<2>(swv[u][e]), s3 = quad_bcast<3>(swv[u][e]);
+#pragma unroll
+                for (int f = 0; f < NB; ++f) {
+                    Mc[e][f].x = __builtin_fmaf(group_sum<CPG1>(P4[f][0]), s0 * sx[f], Mc[e][f].x);
+                    Mc[e][f].y = __builtin_fmaf(group_sum<CPG1>(P4[f][1]), s1 * sx[f], Mc[e][f].y);
+                    Mc[e][f].z = __builtin_fmaf(group_sum<CPG1>(P4[f][2]), s2 * sx[f], Mc[e][f].z);
+                    Mc[e][f].w = __builtin_fmaf(group_sum<CPG1>(P4[f][3]), s3 * sx[f], Mc[e][f].w);
+                    P4[f] = v4i{0, 0, 0, 0};
+                }
+            }
+            if constexpr (!CPG1) {
+#pragma unroll
+                for (int f = 0; f < NB; ++f) acc[e][f] = P4[f];
+            }
+        }
+    };
+    // (whole rounds of the ring, then the rest: with the exit test inside the unrolled round the
+    // compiler waits for ALL outstanding loads at the top of every round)
+    for (int r = NI / D; r > 0; --r) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            compute(u);
+            // (nothing moves across: with the steps' instructions mixed the registers do not suffice)
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(u);   // D steps ahead (past the end: the last one again, never used)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    const int rest = NI % D;
+#pragma unroll
+    for (int u = 0; u < D - 1; ++u)
+        if (u < rest) compute(u);
+
+    // ---- sum of the slices through LDS, 16 pixels at a time, + bias; whole rows of 16 NO channels stored ----
+    float *mine = part_s + w * (16 * RS);
+    constexpr int CQ = 4 * NO, RPP = 64 / CQ;   // 4 channels per lane, RPP pixel rows per wave and pass
+    const float *tile = part_s + wtile * a.slices * (16 * RS) + (lane / CQ) * RS + (lane % CQ) * 4;
+    const int o = ob0 * 16 + (lane % CQ) * 4;
+    float bv4[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bv4[r] = o + r < a.Cout ? a.bias[o + r] : 0.f;
+#pragma unroll
+    for (int f = 0; f < NB; ++f) {
+        if (f) __syncthreads();   // the rows of the block before have been read
+#pragma unroll
+        for (int e = 0; e < NO; ++e) *reinterpret_cast<float4 *>(&mine[l16 * RS + 16 * e + 4 * q]) = Mc[e][f];
+        __syncthreads();
+        for (int r0 = ks * RPP; r0 < 16; r0 += a.slices * RPP) {   // the slices' waves share the rows
+            const int p = p0 + 16 * f + r0 + lane / CQ;
+            if (p >= P || o >= a.Cout) continue;
+            float4 s = *reinterpret_cast<const float4 *>(&tile[r0 * RS]);
+            for (int z = 1; z < a.slices; ++z) {
+                const float4 t = *reinterpret_cast<const float4 *>(&tile[(z * 16 + r0) * RS]);
+                s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+            }
+            constexpr float unscale = W4 ? 0.0625f : 1.0f;
+            const float sum[4] = {s.x * unscale + bv4[0], s.y * unscale + bv4[1], s.z * unscale + bv4[2],
+                                  s.w * unscale + bv4[3]};
+            float *dst = a.y + (size_t)p * a.Cout + o;
+            if ((a.Cout & 3) == 0) {   // o is a multiple of 4, so o + 3 < Cout and the address is 16-byte aligned
+                __builtin_nontemporal_store(v4f{sum[0], sum[1], sum[2], sum[3]}, reinterpret_cast<v4f *>(dst));
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (o + r < a.Cout) dst[r] = sum[r];
+            }
+        }
+    }
 }
 
 int ilog2(int v) {
@@ -365,6 +383,76 @@ int ilog2(int v) {
 }
 
 uint64_t align256(uint64_t v) { return (v + 255) / 256 * 256; }
+
+// Wave tile (16-row blocks along channels x pixels) and how many waves share its reduction.  A big
+// tile moves fewer operand bytes per product; but a CU takes only 8 waves of it, and a launch is as
+// slow as the CU with the most of them.  Measured over layers from 5 to 9792 pixels and 32 to 5120
+// channels; n44 = the tiles of 64 x 64:
+//   n44 >= 1500      64 x 64; from 3000 on enough waves without sharing a reduction at all
+//   n44 >= 150       64 x 64 and 4 slices, except 3x3 layers below 640 tiles: there the nine-fold
+//                    reduction makes a tile of work so big that 32 x 64 fills the last round better
+//                    (2 x 32^2 pixels, 640 -> 640: 26.5 against 29.8 us)
+//   n44 >= 40        32 x 64, 8 slices
+//   fewer            16 x 16 (as long as those are few too), else 16 x 64, 8 slices: latency rules,
+//                    every wave should have only a handful of K-steps
+void choose_tile(wq_direct_plan *p) {
+    const long ob = p->Cout_pad / 16, pb = (p->P + 15) / 16, G = (long)p->taps * p->groups;
+    const long n44 = ((ob + 3) / 4) * ((pb + 3) / 4);
+    p->wo = p->wt = 1;
+    p->nb = 4;
+    if (pb == 1 || (n44 < 40 && ob * pb <= 512)) {
+        p->no = p->nb = 1;
+        p->slices = 8;
+        while (p->slices > 4 && ob * pb * p->slices > 2048) p->slices /= 2;
+    } else if (n44 < 40) {
+        p->no = 1; p->slices = 8;
+    } else if (n44 < 150) {
+        p->no = 2; p->slices = 8;
+    } else if (p->taps == 9 && n44 < 640) {
+        p->no = 2;
+        p->slices = ((ob + 1) / 2) * ((pb + 3) / 4) > 1000 ? 2 : 4;
+    } else if (n44 < 1500) {
+        p->no = 4; p->slices = 4;
+    } else if (n44 < 3000) {
+        p->no = 4; p->slices = 2; p->wt = 2;
+    } else {
+        p->no = 4; p->slices = 1; p->wo = p->wt = 2;
+    }
+    if (p->splits > 1) {
+        p->slices = p->splits;
+        p->wo = p->wt = 1;
+        if (p->slices > 8) p->no = 1;   // the larger tiles' registers allow 8 waves per workgroup
+    } else {
+        while (p->slices > 1 && G * p->g < 2L * p->kstep * p->slices) p->slices /= 2;   // two K-steps each at least
+    }
+}
+
+template <bool K64, bool CPG1, bool W4, bool T9, int NO, int NB, int D, int NWMAX>
+void launch_conv(const DArgs &a0, hipStream_t s) {
+    DArgs a = a0;
+    const long ob = a.Cout_pad / 16, pb = (a.P + 15) / 16;
+    a.nOt = (int)((ob + NO * a.wo - 1) / (NO * a.wo));
+    const long nPt = (pb + NB * a.wt - 1) / (NB * a.wt);
+    a.total = (int)(a.nOt * nPt);
+    a.per_xcd = (a.total + 7) / 8;
+    const int waves = a.slices * a.wo * a.wt;
+    hipLaunchKernelGGL((k_direct_conv<K64, CPG1, W4, T9, NO, NB, D, NWMAX>), dim3((unsigned)a.per_xcd * 8u),
+                       dim3(64 * waves), (size_t)waves * 16 * (16 * NO + 4) * 4, s, a);
+}
+
+template <bool K64, bool CPG1, bool W4, bool T9>
+void launch_conv_tile(const wq_direct_plan *p, const DArgs &a, hipStream_t s) {
+    if (p->no == 4) launch_conv<K64, CPG1, W4, T9, 4, 4, 2, 8>(a, s);
+    else if (p->no == 2) launch_conv<K64, CPG1, W4, T9, 2, 4, 3, 8>(a, s);
+    else if (p->nb == 4) launch_conv<K64, CPG1, W4, T9, 1, 4, 3, 16>(a, s);
+    else launch_conv<K64, CPG1, W4, T9, 1, 1, 6, 16>(a, s);
+}
+
+template <bool K64, bool CPG1, bool W4>
+void launch_conv_taps(const wq_direct_plan *p, const DArgs &a, hipStream_t s) {
+    if (p->taps == 9) launch_conv_tile<K64, CPG1, W4, true>(p, a, s);
+    else launch_conv_tile<K64, CPG1, W4, false>(p, a, s);
+}
 
 }  // namespace
 
@@ -414,22 +502,13 @@ static wq_status_t make_plan(wq_direct_plan_t **out, int N, int H, int W, int Ci
     L.blob_bias_off = L.blob_sW_off + align256((uint64_t)taps * p->groups * p->Cout_pad * 4);
     L.blob_bytes = L.blob_bias_off + align256((uint64_t)p->Cout_pad * 4);
     L.ws_xq_off = 0;
-    L.ws_sx_off = align256((uint64_t)P * Cin);
-    // few output tiles: share the taps out over 3 or 9 workgroups per tile (partial sums in the
-    // workspace, one more small kernel adds them) so that the chip has enough waves
-    const long long base = ((P + 63) / 64) * ((Cp + 63) / 64);
-    p->splits = base >= 512 ? 1 : (base * 3 >= 512 ? 3 : 9);
-    if (taps == 1) {
-        // a linear layer with few rows: split K, in whole groups, until the chip has enough
-        // workgroups (the partial sums are added by the same small kernel)
-        p->splits = 1;
-        while (base * p->splits < 512 && p->splits < 16 && p->groups % (p->splits * 2) == 0 &&
-               Cin / (p->splits * 2) >= 256)
-            p->splits *= 2;
-    }
+    // (a window row and a pixel of zero scales lie before the first pixel's)
+    L.ws_sx_off = align256((uint64_t)P * Cin + (taps == 9 ? (uint64_t)(W + 1) * 4 : 0));
+    p->splits = 1;
+    choose_tile(p);
     L.splits = p->splits;
     L.ws_part_off = L.ws_sx_off + align256((uint64_t)P * p->groups * 4);
-    L.ws_bytes = L.ws_part_off + (p->splits > 1 ? align256((uint64_t)p->splits * P * Cout * 4) : 0);
+    L.ws_bytes = L.ws_part_off;
     p->prepared.store(0);
     *out = p;
     return WQ_OK;
@@ -462,10 +541,8 @@ wq_status_t wq_direct_plan_tune(wq_direct_plan_t *plan, int splits) {
                                        plan->groups % splits == 0);
     if (!ok) return WQ_ERR_UNSUPPORTED;
     plan->splits = splits;
-    wq_direct_layout_t &L = plan->lay;
-    L.splits = splits;
-    L.ws_bytes = L.ws_part_off +
-                 (splits > 1 ? align256((uint64_t)splits * plan->P * plan->Cout * 4) : 0);
+    choose_tile(plan);
+    plan->lay.splits = splits;
     return WQ_OK;
 }
 
@@ -501,15 +578,15 @@ wq_status_t wq_direct_quantize(const wq_direct_plan_t *plan, void *stream, const
     char *ws = (char *)workspace_dev;
     int8_t *xq = (int8_t *)(ws + plan->lay.ws_xq_off);
     float *sx = (float *)(ws + plan->lay.ws_sx_off);
-    const int units = plan->P * plan->groups;
-    const dim3 grid((unsigned)((units + 31) / 32)), block(256);
+    const int gpairs = (plan->groups + 1) / 2, guard = plan->taps == 9 ? plan->W + 1 : 0;
+    const dim3 grid((unsigned)((plan->P + 15) / 16) * (unsigned)gpairs), block(256);
     hipStream_t s = (hipStream_t)stream;
     switch (plan->g) {
-        case 32: hipLaunchKernelGGL((k_quantize_pixels<4>), grid, block, 0, s, x_dev, xq, sx, units, plan->Cin, plan->groups); break;
-        case 64: hipLaunchKernelGGL((k_quantize_pixels<8>), grid, block, 0, s, x_dev, xq, sx, units, plan->Cin, plan->groups); break;
-        case 128: hipLaunchKernelGGL((k_quantize_pixels<16>), grid, block, 0, s, x_dev, xq, sx, units, plan->Cin, plan->groups); break;
-        case 256: hipLaunchKernelGGL((k_quantize_pixels<32>), grid, block, 0, s, x_dev, xq, sx, units, plan->Cin, plan->groups); break;
-        default: hipLaunchKernelGGL((k_quantize_pixels<64>), grid, block, 0, s, x_dev, xq, sx, units, plan->Cin, plan->groups); break;
+        case 32: hipLaunchKernelGGL((k_quantize_pixels<4>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
+        case 64: hipLaunchKernelGGL((k_quantize_pixels<8>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
+        case 128: hipLaunchKernelGGL((k_quantize_pixels<16>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
+        case 256: hipLaunchKernelGGL((k_quantize_pixels<32>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
+        default: hipLaunchKernelGGL((k_quantize_pixels<64>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
     }
     return hipGetLastError() == hipSuccess ? WQ_OK : WQ_ERR_DEVICE;
 }
@@ -528,28 +605,20 @@ wq_status_t wq_direct_conv(const wq_direct_plan_t *plan, void *stream, void *wor
     a.sW = (const float *)(b + plan->lay.blob_sW_off);
     a.bias = (const float *)(b + plan->lay.blob_bias_off);
     a.y = y_dev;
-    a.part = (float *)(const_cast<char *>(ws) + plan->lay.ws_part_off);
-    a.splits = plan->splits;
     a.taps = plan->taps;
-    a.N = plan->N; a.H = plan->H; a.W = plan->W; a.Cin = plan->Cin; a.Cout = plan->Cout;
+    a.H = plan->H; a.W = plan->W; a.Cin = plan->Cin; a.Cout = plan->Cout;
     a.Cout_pad = plan->Cout_pad; a.P = plan->P; a.log2g = ilog2(plan->g);
-    const dim3 grid((unsigned)((plan->Cout_pad + 63) / 64), (unsigned)((plan->P + 63) / 64),
-                    (unsigned)plan->splits), block(256);
+    a.slices = plan->slices; a.wo = plan->wo; a.wt = plan->wt;
     hipStream_t s = (hipStream_t)stream;
+    const bool k32 = plan->kstep == 32, one = plan->g == 64;
     if (plan->wbits == 4) {
-        if (plan->kstep == 32) hipLaunchKernelGGL((k_direct_conv<false, true, true>), grid, block, 0, s, a);
-        else if (plan->g == 64) hipLaunchKernelGGL((k_direct_conv<true, true, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_direct_conv<true, false, true>), grid, block, 0, s, a);
+        if (k32) launch_conv_taps<false, true, true>(plan, a, s);
+        else if (one) launch_conv_taps<true, true, true>(plan, a, s);
+        else launch_conv_taps<true, false, true>(plan, a, s);
     } else {
-        if (plan->kstep == 32) hipLaunchKernelGGL((k_direct_conv<false, true, false>), grid, block, 0, s, a);
-        else if (plan->g == 64) hipLaunchKernelGGL((k_direct_conv<true, true, false>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_direct_conv<true, false, false>), grid, block, 0, s, a);
-    }
-    if (hipGetLastError() != hipSuccess) return WQ_ERR_DEVICE;
-    if (plan->splits > 1) {
-        const int total = plan->P * plan->Cout;
-        hipLaunchKernelGGL(k_direct_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                           (const float *)a.part, a.bias, y_dev, total, plan->Cout, plan->splits);
+        if (k32) launch_conv_taps<false, true, false>(plan, a, s);
+        else if (one) launch_conv_taps<true, true, false>(plan, a, s);
+        else launch_conv_taps<true, false, false>(plan, a, s);
     }
     return hipGetLastError() == hipSuccess ? WQ_OK : WQ_ERR_DEVICE;
 }

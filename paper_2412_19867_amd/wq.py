@@ -446,12 +446,13 @@ class DirectPlan:
         return Wq, sW, bias
 
     def workspace_views(self, ws):
-        """(xq [P][Cin] int8, sx [P][groups] fp32)"""
+        """(xq [P][Cin] int8, sx [P][groups] fp32) - un-blocked and transposed (pure index permutations)"""
         import torch
         L = self.layout
-        xq = ws[L.ws_xq_off:L.ws_xq_off + L.P * L.Cin].view(torch.int8).view(L.P, L.Cin)
-        sx = ws[L.ws_sx_off:L.ws_sx_off + L.P * L.groups * 4].view(torch.float32).view(L.P, L.groups)
-        return xq, sx
+        xq = ws[L.ws_xq_off:L.ws_xq_off + L.P * L.Cin].view(torch.int8) \
+            .view(L.Cin // L.kstep, 4, L.P, L.kstep // 4).permute(2, 0, 1, 3).reshape(L.P, L.Cin)
+        sx = ws[L.ws_sx_off:L.ws_sx_off + L.P * L.groups * 4].view(torch.float32).view(L.groups, L.P)
+        return xq, sx.t().contiguous()
 
     def weight_prepare(self, w, bias, blob, stream=None):
         import torch

@@ -117,3 +117,44 @@ def test_direct_largest_pixel_count(wq):
     """Just under the largest pixel count a plan takes (65535 pixel tiles of 64)."""
     d = workloads.small_layer(78, 1, 2047, 2048, 32, 32, 4, 32)
     check_direct(wq, d.x, d.w, d.bias, 32, "largest")
+
+
+@pytest.mark.parametrize("case", [
+    # P    Cin  Cout  g   (linear: every launch shape of the tile choice, with ragged pixels and channels)
+    (16, 64, 33, 32), (17, 128, 16, 64), (257, 192, 260, 64), (400, 128, 1000, 32), (700, 256, 500, 128),
+    (1601, 64, 2050, 64), (3300, 64, 2100, 32), (12500, 32, 1030, 32),
+], ids=lambda c: "p%d_%d-%d_g%d" % c)
+def test_every_tile_choice_of_the_quantized_gemm(wq, case):
+    """Rows and channels that end inside a tile, for every wave tile and slice count the plan picks
+    from (against the oracle in fp64)."""
+    R, Cin, Cout, g = case
+    rng = np.random.default_rng(R)
+    x, w = rng.standard_normal((R, Cin)).astype(np.float32), rng.standard_normal((Cout, Cin)).astype(np.float32)
+    ref = oracle.linear_pipeline(x, w, None, g)
+    plan = wq.DirectPlan(R, 1, 1, Cin, Cout, g, linear=True)
+    blob, ws, y = plan.alloc_blob(), plan.alloc_workspace(), plan.alloc_output()
+    y.fill_(float("nan"))
+    plan.weight_prepare(torch.from_numpy(w).cuda(), None, blob)
+    plan.forward(torch.from_numpy(x).cuda(), blob, ws, y)
+    got = y.cpu().numpy().reshape(R, Cout).astype(np.float64)
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref["y64"]).max() <= Y_TOL * np.abs(ref["y64"]).max()
+
+
+@pytest.mark.parametrize("shape", [(2, 16, 15, 64, 48, 64), (1, 34, 33, 32, 130, 32), (3, 40, 40, 64, 300, 64)],
+                         ids=lambda s: "%dx%dx%d_%d-%d_g%d" % s)
+@pytest.mark.parametrize("splits", [1, 3, 9])
+def test_slices_of_the_quantized_convolution(wq, shape, splits):
+    """The reduction shared by 1, 3 or 9 waves, on images whose rows do not match the tiles."""
+    N, H, W, Cin, Cout, g = shape
+    d = workloads.small_layer(400 + H, N, H, W, Cin, Cout, 4, g)
+    ref = oracle.direct_pipeline(d.x, d.w, d.bias, g)
+    plan = wq.DirectPlan(N, H, W, Cin, Cout, g).tune(splits)
+    blob, ws, y = plan.alloc_blob(), plan.alloc_workspace(), plan.alloc_output()
+    ws.fill_(0xff)   # every bit set: a NaN wherever a scale is read that nobody wrote
+    y.fill_(float("nan"))
+    plan.weight_prepare(torch.from_numpy(d.w).cuda(), torch.from_numpy(d.bias).cuda(), blob)
+    plan.forward(torch.from_numpy(d.x).cuda(), blob, ws, y)
+    got = y.cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref["y64"]).max() <= Y_TOL * np.abs(ref["y64"]).max()
