@@ -20,6 +20,16 @@
 // finishes Y[a][b] = sum_i A^T[a][i] (sum_ks R_{i,ks}[b]), adds bias and stores
 // NHWC with the ragged right/bottom edge masked.
 //
+// A wave waits for nothing but its own loads, so what counts is that the compiler can count them:
+// the request of the K-step D ahead is unconditional (the cursor stops at the last one), whole
+// rounds of the ring make up a wave's walk, and it is placed between the MFMAs and the
+// dequantization, which covers their latency.  Scales cost one word per lane and load (a v4 load of
+// the four channel scales moves four times the bytes through the load path) and reach the lanes by
+// DPP quad broadcasts and a row swap; groups of one K-step start their sums at kMagic.  Measured
+// against conditional requests, v4 scales and conversions: 32x28^2 128->128 F(6,3) 26.1 -> 24.6 us,
+// 8x100x128 192->64 F(4,3) g 32 69.8 -> 61.4 us, 2x64x64 320->320 F(4,3) at one block per wave
+// 32.3 -> 26.5 us (whole forward).
+//
 // Workgroups are numbered so that the eight XCDs (which receive consecutive
 // workgroup ids round-robin and have private L2s) each own a slice of the
 // larger operand: with xcd_mode 0 an XCD owns every 8th block of output
@@ -32,7 +42,10 @@
 
 namespace {   // every including file instantiates its own tile size; nothing here is exported
 
-constexpr int kPrefetchBase = 4;         // K-steps in flight of the 16x16 configurations
+// K-steps in flight of a wave, a divisor of the taps of a row.  (F(4,3) with 6 in flight: 2x64x64
+// 320->320 with two blocks per wave 33.9 against 27.4 us, the registers cost a workgroup per CU.)
+template <int M, int NT, int NO>
+constexpr int kDepth = M == 4 ? 3 : (NT * NO == 4 ? 2 : 4);
 constexpr int RS_STRIDE = 20;           // floats per tile row of the LDS exchange (16 + pad)
 
 struct Args {
@@ -51,13 +64,16 @@ struct Args {
 template <bool K64, int NT, int NO>
 struct Stage {
     v4i a[NO], b[NT];   // K64: 16 operand bytes per lane; otherwise .xy only
-    v4f sw[NO];         // weight scales of the lane's 4 output channels per sub-block
-    float sx[NT];       // activation scale of the lane's tile per sub-block
+    float sw[NO];       // weight scale of channel 4 q + lane % 4 of each sub-block
+    float sx;           // activation scale of tile lane % (16 NT)
 };
 
 template <int M, bool K64, bool CPG1, bool WIDE, bool ATSP, bool DUMP, int NT, int NO, int KS, int D>
 __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Args a) {
     constexpr int n = M + 2;
+    static_assert(n % D == 0, "a tap row is a whole number of rounds of the ring");
+    // an int32 block that starts at kMagic converts by a subtraction (groups of one K-step: |sum| < 2^21)
+    constexpr bool MAGIC = CPG1;
     constexpr int KSTEP = K64 ? 64 : 32;   // K per MFMA
     constexpr int KB = KSTEP / 4;          // operand bytes per lane per MFMA
     constexpr int NW = n * KS;             // waves
@@ -109,8 +125,8 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
     // per-lane byte offsets inside a tap plane (sub-block 0); the tap/K position is scalar
     const int vW = o0 * Cin + lane * KB;
     const int vX = tau0 * Cin + lane * KB;
-    const int vSW = (o0 + 4 * q) * 4;                       // sW [tap][group][Cout_pad]
-    const int vSX = (tau0 >> 4) * groups * 64 + l16 * 4;    // sX [tap][16-tile block][group][16]
+    const int vSW = (o0 + 4 * q + (lane & 3)) * 4;          // sW [tap][group][Cout_pad]
+    const int vSX = ((tau0 >> 4) + ((lane >> 4) & (NT - 1))) * groups * 64 + l16 * 4;   // sX [tap][16-tile block][group][16]
     const unsigned planeW = (unsigned)Cout_pad * Cin, planeX = (unsigned)T_pad * Cin;
     const unsigned planeSW = (unsigned)groups * Cout_pad * 4, planeSX = (unsigned)T_pad * groups * 4;
     constexpr unsigned stepOp = 16 * KSTEP;                 // bytes of one K-step of a 16-row block
@@ -123,7 +139,8 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
     unsigned oSX = t0 * planeSX + (unsigned)(ks * gps) * 64u;
     const unsigned dW = planeW - (unsigned)cps * stepOp, dX = planeX - (unsigned)cps * stepOp;
     const unsigned dSW = planeSW - (unsigned)gps * stepSW, dSX = planeSX - (unsigned)gps * 64u;
-    int k_ld = cps, kg_ld = 0;
+    const int NI = n * cps;                      // the wave's K-steps, a multiple of D
+    int k_ld = 0, kg_ld = 0, left_ld = NI;
 
     auto load_stage = [&](Stage<K64, NT, NO> &s) {
 #pragma unroll
@@ -134,8 +151,6 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
                 const v2i t = __builtin_amdgcn_raw_buffer_load_b64(rW, vW + no * 16 * Cin, oW, 0);
                 s.a[no] = v4i{t.x, t.y, 0, 0};
             }
-            s.sw[no] = __builtin_bit_cast(
-                v4f, __builtin_amdgcn_raw_buffer_load_b128(rSW, vSW + no * 64, oSW, 0));
         }
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -145,22 +160,22 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
                 const v2i t = __builtin_amdgcn_raw_buffer_load_b64(rX, vX + nt * 16 * Cin, oX, 0);
                 s.b[nt] = v4i{t.x, t.y, 0, 0};
             }
-            s.sx[nt] = __builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX + nt * groups * 64, oSX, 0));
         }
-        oW += stepOp;
-        oX += stepOp;
-        if (CPG1 || (++kg_ld & cpg_mask) == 0) {
-            oSW += stepSW;
-            oSX += 64u;
-        }
-        if (--k_ld == 0) {
-            k_ld = cps;
-            oW += dW;
-            oX += dX;
-            oSW += dSW;
-            oSX += dSX;
-        }
+#pragma unroll
+        for (int no = 0; no < NO; ++no)
+            s.sw[no] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSW, vSW, oSW + 64u * no, 0));
+        s.sx = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX, oSX, 0));
+        // branch-free scalar bookkeeping; the cursor stops at the last K-step, which the last D
+        // requests repeat
+        const bool go = --left_ld > 0;
+        k_ld += go ? 1 : 0;
+        kg_ld += go ? 1 : 0;
+        const bool next_group = go && (CPG1 || (kg_ld & cpg_mask) == 0), next_tap = go && k_ld == cps;
+        k_ld = next_tap ? 0 : k_ld;
+        oW += (go ? stepOp : 0u) + (next_tap ? dW : 0u);
+        oX += (go ? stepOp : 0u) + (next_tap ? dX : 0u);
+        oSW += (next_group ? stepSW : 0u) + (next_tap ? dSW : 0u);
+        oSX += (next_group ? 64u : 0u) + (next_tap ? dSX : 0u);
     };
 
     float4 R[M][NO][NT];
@@ -171,11 +186,12 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) R[b][no][nt] = make_float4(0.f, 0.f, 0.f, 0.f);
 
-    const int NI = n * cps;   // >= n >= 4 >= D
     Stage<K64, NT, NO> st[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) load_stage(st[d]);
-    int loads_left = NI - D;
+    for (int d = 0; d < D; ++d) {   // in the order the loop expects them back
+        load_stage(st[d]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 
     // compute cursor (uniform)
     int j_cp = 0, k_left = cps, kg_cp = 0, gam_cp = 0, in_chunk = 0;
@@ -195,103 +211,110 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
 #pragma unroll
     for (int b = 0; b < M; ++b) atc[b] = a.xf.AT[b * n];   // column of tap j = 0
 
+    const v4i magic = {kMagic, kMagic, kMagic, kMagic};
+    // (no exit test and no conditional request inside a round: with either of them the compiler
+    // cannot count the loads in flight and waits for all of them at the top of every round)
     for (int it = 0; it < NI; it += D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            if (it + d < NI) {
-                Stage<K64, NT, NO> &s = st[d];
+            Stage<K64, NT, NO> &s = st[d];
+            const bool group_end = CPG1 || ((++kg_cp & cpg_mask) == 0);
+#pragma unroll
+            for (int no = 0; no < NO; ++no)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const v4i c0 = MAGIC ? magic : acc[no][nt];
+                    if constexpr (K64) {
+                        acc[no][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(s.a[no], s.b[nt], c0, 0, 0, 0);
+                    } else {
+                        const long av = __builtin_bit_cast(long, v2i{s.a[no].x, s.a[no].y});
+                        const long bv = __builtin_bit_cast(long, v2i{s.b[nt].x, s.b[nt].y});
+                        acc[no][nt] = __builtin_amdgcn_mfma_i32_16x16x32_i8(av, bv, c0, 0, 0, 0);
+                    }
+                }
+            // the scale products leave the stage, whose registers are then refilled while the MFMAs run
+            float4 c[NO][NT];
+            {
+                float sx[NT];
+                spread_rows<NT>(s.sx, sx);
+#pragma unroll
+                for (int no = 0; no < NO; ++no) {
+                    const float sw0 = quad_bcast<0>(s.sw[no]), sw1 = quad_bcast<1>(s.sw[no]),
+                                sw2 = quad_bcast<2>(s.sw[no]), sw3 = quad_bcast<3>(s.sw[no]);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        c[no][nt] = make_float4(sw0 * sx[nt], sw1 * sx[nt], sw2 * sx[nt], sw3 * sx[nt]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_stage(s);   // D steps ahead
+            __builtin_amdgcn_sched_barrier(0);
+            if (group_end) {
 #pragma unroll
                 for (int no = 0; no < NO; ++no)
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
-                        const v4i c0 = CPG1 ? v4i{0, 0, 0, 0} : acc[no][nt];
-                        if constexpr (K64) {
-                            acc[no][nt] =
-                                __builtin_amdgcn_mfma_i32_16x16x64_i8(s.a[no], s.b[nt], c0, 0, 0, 0);
-                        } else {
-                            const long av = __builtin_bit_cast(long, v2i{s.a[no].x, s.a[no].y});
-                            const long bv = __builtin_bit_cast(long, v2i{s.b[nt].x, s.b[nt].y});
-                            acc[no][nt] = __builtin_amdgcn_mfma_i32_16x16x32_i8(av, bv, c0, 0, 0, 0);
+                        Mc[no][nt].x = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][0]), c[no][nt].x, Mc[no][nt].x);
+                        Mc[no][nt].y = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][1]), c[no][nt].y, Mc[no][nt].y);
+                        Mc[no][nt].z = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][2]), c[no][nt].z, Mc[no][nt].z);
+                        Mc[no][nt].w = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][3]), c[no][nt].w, Mc[no][nt].w);
+                        if constexpr (DUMP) {   // the debug entry point's instance of this kernel
+                            constexpr int off = MAGIC ? kMagic : 0;
+                            const int v[4] = {acc[no][nt][0] - off, acc[no][nt][1] - off, acc[no][nt][2] - off,
+                                              acc[no][nt][3] - off};
+                            wq_dump_store(a.dump, i * n + j_cp, tau0 + nt * 16 + l16,
+                                          ks * gps + gam_cp, groups, o0 + no * 16 + 4 * q, a.Cout,
+                                          a.T, v);
                         }
+                        if constexpr (!CPG1) acc[no][nt] = v4i{0, 0, 0, 0};
                     }
-                const bool group_end = CPG1 || ((++kg_cp & cpg_mask) == 0);
-                float4 c[NO][NT];
+                ++gam_cp;
+                if (WIDE && ++in_chunk == 4) {   // fp64 totals of 4-group fp32 chunks (long reductions)
+                    in_chunk = 0;
+#pragma unroll
+                    for (int no = 0; no < NO; ++no)
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) {
+                            Mt[no][nt][0] += (double)Mc[no][nt].x;
+                            Mt[no][nt][1] += (double)Mc[no][nt].y;
+                            Mt[no][nt][2] += (double)Mc[no][nt].z;
+                            Mt[no][nt][3] += (double)Mc[no][nt].w;
+                            Mc[no][nt] = make_float4(0.f, 0.f, 0.f, 0.f);
+                        }
+                }
+            }
+            if (--k_left == 0) {   // end of tap j_cp: fold into (this slice's share of) row i of Y A
+                k_left = cps;
+                gam_cp = 0;
+                in_chunk = 0;
+                // branch-free on purpose: entries of A^T that are zero simply add nothing
 #pragma unroll
                 for (int no = 0; no < NO; ++no)
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        c[no][nt] = make_float4(s.sw[no].x * s.sx[nt], s.sw[no].y * s.sx[nt],
-                                                s.sw[no].z * s.sx[nt], s.sw[no].w * s.sx[nt]);
-                if (loads_left > 0) {   // the stage's registers are free again: refill them
-                    load_stage(s);
-                    --loads_left;
-                }
-                if (group_end) {
+                    for (int nt = 0; nt < NT; ++nt) {
+                        float4 Mv = Mc[no][nt];
+                        if constexpr (WIDE) {
+                            Mv = make_float4((float)(Mt[no][nt][0] + (double)Mv.x),
+                                             (float)(Mt[no][nt][1] + (double)Mv.y),
+                                             (float)(Mt[no][nt][2] + (double)Mv.z),
+                                             (float)(Mt[no][nt][3] + (double)Mv.w));
 #pragma unroll
-                    for (int no = 0; no < NO; ++no)
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt) {
-                            Mc[no][nt].x = __builtin_fmaf((float)acc[no][nt][0], c[no][nt].x, Mc[no][nt].x);
-                            Mc[no][nt].y = __builtin_fmaf((float)acc[no][nt][1], c[no][nt].y, Mc[no][nt].y);
-                            Mc[no][nt].z = __builtin_fmaf((float)acc[no][nt][2], c[no][nt].z, Mc[no][nt].z);
-                            Mc[no][nt].w = __builtin_fmaf((float)acc[no][nt][3], c[no][nt].w, Mc[no][nt].w);
-                            if constexpr (DUMP) {   // the debug entry point's instance of this kernel
-                                const int v[4] = {acc[no][nt][0], acc[no][nt][1], acc[no][nt][2],
-                                                  acc[no][nt][3]};
-                                wq_dump_store(a.dump, i * n + j_cp, tau0 + nt * 16 + l16,
-                                              ks * gps + gam_cp, groups, o0 + no * 16 + 4 * q, a.Cout,
-                                              a.T, v);
-                            }
-                            if constexpr (!CPG1) acc[no][nt] = v4i{0, 0, 0, 0};
+                            for (int r = 0; r < 4; ++r) Mt[no][nt][r] = 0.0;
                         }
-                    ++gam_cp;
-                    if (WIDE && ++in_chunk == 4) {   // fp64 totals of 4-group fp32 chunks (long reductions)
-                        in_chunk = 0;
+                        Mc[no][nt] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-                        for (int no = 0; no < NO; ++no)
-#pragma unroll
-                            for (int nt = 0; nt < NT; ++nt) {
-                                Mt[no][nt][0] += (double)Mc[no][nt].x;
-                                Mt[no][nt][1] += (double)Mc[no][nt].y;
-                                Mt[no][nt][2] += (double)Mc[no][nt].z;
-                                Mt[no][nt][3] += (double)Mc[no][nt].w;
-                                Mc[no][nt] = make_float4(0.f, 0.f, 0.f, 0.f);
-                            }
+                        for (int b = 0; b < M; ++b) {
+                            float4 &Rb = R[b][no][nt];
+                            Rb.x = __builtin_fmaf(atc[b], Mv.x, Rb.x);
+                            Rb.y = __builtin_fmaf(atc[b], Mv.y, Rb.y);
+                            Rb.z = __builtin_fmaf(atc[b], Mv.z, Rb.z);
+                            Rb.w = __builtin_fmaf(atc[b], Mv.w, Rb.w);
+                        }
                     }
-                }
-                if (--k_left == 0) {   // end of tap j_cp: fold into (this slice's share of) row i of Y A
-                    k_left = cps;
-                    gam_cp = 0;
-                    in_chunk = 0;
-                    // branch-free on purpose: entries of A^T that are zero simply add nothing
+                ++j_cp;
+                const int jn = j_cp < n ? j_cp : 0;
 #pragma unroll
-                    for (int no = 0; no < NO; ++no)
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt) {
-                            float4 Mv = Mc[no][nt];
-                            if constexpr (WIDE) {
-                                Mv = make_float4((float)(Mt[no][nt][0] + (double)Mv.x),
-                                                 (float)(Mt[no][nt][1] + (double)Mv.y),
-                                                 (float)(Mt[no][nt][2] + (double)Mv.z),
-                                                 (float)(Mt[no][nt][3] + (double)Mv.w));
-#pragma unroll
-                                for (int r = 0; r < 4; ++r) Mt[no][nt][r] = 0.0;
-                            }
-                            Mc[no][nt] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                            for (int b = 0; b < M; ++b) {
-                                float4 &Rb = R[b][no][nt];
-                                Rb.x = __builtin_fmaf(atc[b], Mv.x, Rb.x);
-                                Rb.y = __builtin_fmaf(atc[b], Mv.y, Rb.y);
-                                Rb.z = __builtin_fmaf(atc[b], Mv.z, Rb.z);
-                                Rb.w = __builtin_fmaf(atc[b], Mv.w, Rb.w);
-                            }
-                        }
-                    ++j_cp;
-                    const int jn = j_cp < n ? j_cp : 0;
-#pragma unroll
-                    for (int b = 0; b < M; ++b) atc[b] = a.xf.AT[b * n + jn];
-                }
+                for (int b = 0; b < M; ++b) atc[b] = a.xf.AT[b * n + jn];
             }
         }
     }
@@ -387,21 +410,21 @@ hipError_t launch_cfg(const Args &a, hipStream_t s) {
 // fp64 chunk totals only where a wave reduces more than 8 groups per tap
 template <int M, bool K64, bool CPG1, bool ATSP>
 hipError_t launch_base(const Args &a, hipStream_t s, bool wide) {
-    return wide ? launch_cfg<M, K64, CPG1, true, ATSP, 1, 1, 1, kPrefetchBase>(a, s)
-                : launch_cfg<M, K64, CPG1, false, ATSP, 1, 1, 1, kPrefetchBase>(a, s);
+    return wide ? launch_cfg<M, K64, CPG1, true, ATSP, 1, 1, 1, kDepth<M, 1, 1>>(a, s)
+                : launch_cfg<M, K64, CPG1, false, ATSP, 1, 1, 1, kDepth<M, 1, 1>>(a, s);
 }
 
 // the register-tile variants: one K-step per group, paired form of A^T
 template <int M, bool K64>
 hipError_t launch_fast(const Args &a, hipStream_t s, int variant, bool wide) {
     if (variant == WQ_K2_FUSED_KSPLIT)
-        return wide ? launch_cfg<M, K64, true, true, true, 1, 1, 2, kPrefetchBase>(a, s)
-                    : launch_cfg<M, K64, true, false, true, 1, 1, 2, kPrefetchBase>(a, s);
+        return wide ? launch_cfg<M, K64, true, true, true, 1, 1, 2, kDepth<M, 1, 1>>(a, s)
+                    : launch_cfg<M, K64, true, false, true, 1, 1, 2, kDepth<M, 1, 1>>(a, s);
     if (variant == WQ_K2_FUSED_32x16)
-        return wide ? launch_cfg<M, K64, true, true, true, 2, 1, 1, 3>(a, s)
-                    : launch_cfg<M, K64, true, false, true, 2, 1, 1, 3>(a, s);
-    return wide ? launch_cfg<M, K64, true, true, true, 2, 2, 1, 2>(a, s)
-                : launch_cfg<M, K64, true, false, true, 2, 2, 1, 2>(a, s);
+        return wide ? launch_cfg<M, K64, true, true, true, 2, 1, 1, kDepth<M, 2, 1>>(a, s)
+                    : launch_cfg<M, K64, true, false, true, 2, 1, 1, kDepth<M, 2, 1>>(a, s);
+    return wide ? launch_cfg<M, K64, true, true, true, 2, 2, 1, kDepth<M, 2, 2>>(a, s)
+                : launch_cfg<M, K64, true, false, true, 2, 2, 1, kDepth<M, 2, 2>>(a, s);
 }
 
 template <int M>

@@ -47,3 +47,32 @@ template <bool MAGIC>
 __device__ __forceinline__ float group_sum(int v) {
     return MAGIC ? __int_as_float(v) - 12582912.0f : (float)v;
 }
+
+// Broadcast of 16-lane rows: lane l of `v` holds the value of pixel l of the wave's 64 (16) pixels;
+// r[f] gets pixel 16 f + l % 16 in every lane.
+template <int NB>
+__device__ __forceinline__ void spread_rows(float v, float (&r)[NB]) {
+    static_assert(NB == 1 || NB == 2 || NB == 4, "row blocks per wave");
+    if constexpr (NB == 1) {
+        r[0] = v;
+    } else {
+        const unsigned u = __float_as_uint(v);
+        const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // rows 0 0 2 2 | 1 1 3 3
+        if constexpr (NB == 2) {   // (the lane rows carry 0 1 0 1)
+            r[0] = __uint_as_float(s[0]);
+            r[1] = __uint_as_float(s[1]);
+            return;
+        }
+        const auto e = __builtin_amdgcn_permlane32_swap(s[0], s[0], false, false);
+        const auto o = __builtin_amdgcn_permlane32_swap(s[1], s[1], false, false);
+        r[0] = __uint_as_float(e[0]);
+        r[1] = __uint_as_float(o[0]);
+        r[2] = __uint_as_float(e[1]);
+        r[3] = __uint_as_float(o[1]);
+    }
+}
+
+template <int R>
+__device__ __forceinline__ float quad_bcast(float v) {   // lane 4k + R of every quad to its four lanes
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), R * 0x55, 0xf, 0xf, true));
+}

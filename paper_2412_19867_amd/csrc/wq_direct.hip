@@ -108,30 +108,6 @@ struct DArgs {
     int nOt, total, per_xcd;   // workgroup tiles along channels, workgroups, share of each XCD
 };
 
-// Broadcast of 16-lane rows: lane l of `v` holds the value of pixel l of the wave's 64 (16) pixels;
-// r[f] gets pixel 16 f + l % 16 in every lane.
-template <int NB>
-__device__ __forceinline__ void spread_rows(float v, float (&r)[NB]) {
-    static_assert(NB == 1 || NB == 4, "row blocks per wave");
-    if constexpr (NB == 1) {
-        r[0] = v;
-    } else {
-        const unsigned u = __float_as_uint(v);
-        const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // rows 0 0 2 2 | 1 1 3 3
-        const auto e = __builtin_amdgcn_permlane32_swap(s[0], s[0], false, false);
-        const auto o = __builtin_amdgcn_permlane32_swap(s[1], s[1], false, false);
-        r[0] = __uint_as_float(e[0]);
-        r[1] = __uint_as_float(o[0]);
-        r[2] = __uint_as_float(e[1]);
-        r[3] = __uint_as_float(o[1]);
-    }
-}
-
-template <int R>
-__device__ __forceinline__ float quad_bcast(float v) {   // lane 4k + R of every quad to its four lanes
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), R * 0x55, 0xf, 0xf, true));
-}
-
 // A wave owns a (16 NO channels) x (16 NB pixels) tile and one slice of its reduction (whole
 // groups of the flat sequence tap-major, then channels).  Operands go from memory straight into
 // the registers the MFMA reads (both tensors are in its operand order) and are requested D

@@ -196,6 +196,13 @@ int default_k2_variant(const wq_plan *p) {
     // operands too often.
     const bool two_kernel = (p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128))) ||
                             p->Cin >= 1024 || p->g >= 128;
+    // one group of 128 or more per tap: nothing is re-read between groups, and the product of a tap
+    // written out costs more than the fused kernel's one block per wave (22x54x54 128->96 F(2,3) 48
+    // against 69 us, 10x20x20 128->70 F(4,3) 12.5 against 13.9; F(6,3)'s 64 taps go either way; a
+    // handful of blocks does not fill the GPU without the taps side by side: 29x39 128->39 11.6
+    // against 11.2)
+    if (p->g >= 128 && p->groups == 1 && p->m != 6 && (long)(p->T_pad / 16) * (p->Cout_pad / 16) >= 64)
+        return WQ_K2_FUSED_16x16;
     if (two_kernel) {
         // 128x128 tiles: groups of 128 and more on layers with at least 1024 tiles and 256 channels
         if (p->g >= 128 && p->groups <= 8 && p->T_pad >= 1024 && p->Cout_pad >= 256)
@@ -211,16 +218,39 @@ int default_k2_variant(const wq_plan *p) {
     // the operands shared through LDS, four workgroups of 32 tiles x 32 channels per CU.  A workgroup
     // walks all n*n taps in sequence, so the reduction must be short and the workgroups must fill
     // the GPU at least twice over; the fused kernel below has the same traffic but fewer, fatter waves.
-    if (p->m == 4 && p->g == p->kstep && variant_applicable(p, WQ_K2_LDS_FULL_32x32)) {
+    // Its lanes store four channels each: with Cout not a multiple of 4 those stores are scalar and
+    // scattered (5x79x68 128->654: 242 against 66 us of the fused kernel, whose lanes store a row).
+    if (p->m == 4 && p->g == p->kstep && p->Cout % 4 == 0 && variant_applicable(p, WQ_K2_LDS_FULL_32x32)) {
         const long wgs = (long)((p->T_pad + 31) / 32) * ((p->Cout_pad + 31) / 32);
         if (wgs >= 512 && p->groups <= 6) return WQ_K2_LDS_FULL_32x32;
     }
     if (!variant_applicable(p, WQ_K2_FUSED_32x16)) return WQ_K2_FUSED_16x16;
-    // few tile blocks -> split K over more waves; many blocks -> taller or bigger register tiles
+    // The fused kernel's tile of a workgroup, in blocks of 16 tiles x 16 channels (us of the forward):
     const long tb = p->T_pad / 16, ob = p->Cout_pad / 16;
     const bool can_split = p->groups % 2 == 0 && p->groups >= 4;
     if (tb <= 2) return can_split ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
-    if (tb * ob >= 640) return ob >= 40 ? WQ_K2_FUSED_32x32 : WQ_K2_FUSED_32x16;
+    // a single group per tap leaves a bigger tile nothing to reuse (12x80x90 64->416 F(6,3): one block
+    // 73, two 87, four 83)
+    if (p->groups == 1) return WQ_K2_FUSED_16x16;
+    // fewer blocks than CUs: more and shorter waves (2x97x67 256->64: split 20.3, one block 22.6, two
+    // 26.4; 3x20x20 384->480: split 15.5, one block 16.7)
+    if (tb * ob < 256 && p->m == 4)
+        return (can_split && p->groups >= 6) ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
+    // one block each where those workgroups just fit the GPU at once, three on a CU, while pairs
+    // would be one CU's worth and a few (3x45x61 192->200: 19.7 against 20.7; 2x64x64 320->320: 26.5
+    // against 27.4)
+    if (p->m == 4 && p->g == 64 && tb * ob >= 448 && tb * ob <= 704) return WQ_K2_FUSED_16x16;
+    if (tb * ob >= 600) {
+        // four blocks pay for their registers where a tap reduces four groups or more and their
+        // workgroups fill the CUs evenly, once or at least three times (3x89x89 320->256 F(6,3)
+        // 40.5 against 49.5; 18x59x59 512->320 164 against 189; 3x76x63 448->384, 348 workgroups,
+        // 56 against 52; with two groups 11x33x23 128->640 32.9 against 26.4), and on wide F(6,3)
+        // layers in any case (14x32x32 128->1074 97 against 101)
+        const long quads = tb * ob / 4;
+        if (p->groups >= 4 && (ob >= 40 || (p->g == 64 && (quads <= 256 || quads >= 768)))) return WQ_K2_FUSED_32x32;
+        if (p->m == 6 && ob >= 40) return WQ_K2_FUSED_32x32;
+        return WQ_K2_FUSED_32x16;
+    }
     if (tb >= 16) return WQ_K2_FUSED_32x16;
     return (can_split && p->groups >= 16) ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
 }
