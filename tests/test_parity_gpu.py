@@ -135,6 +135,21 @@ def test_small_layers(wq, case):
     check(wq, d)
 
 
+@pytest.mark.parametrize("with_bias", [True, False], ids=["bias", "none"])
+@pytest.mark.parametrize("Cin,Cout,m,g", [(32, 1, 4, 32), (64, 15, 2, 64), (512, 33, 6, 128), (512, 64, 4, 512)])
+def test_weight_stage_writes_the_padded_bias(wq, Cin, Cout, m, g, with_bias):
+    """The bias leaves in blocks of 16 channels: every one is written, padding and a missing bias as zero."""
+    plan = wq.Plan(1, 8, 8, Cin, Cout, m, g)
+    blob = torch.full_like(plan.alloc_blob(), 0x7f)
+    w = torch.randn(Cout, Cin, 3, 3, device="cuda")
+    b = torch.randn(Cout, device="cuda") if with_bias else None
+    plan.weight_prepare(w, b, blob)
+    want = torch.zeros(plan.layout.Cout_pad, device="cuda")
+    if with_bias:
+        want[:Cout] = b
+    assert torch.equal(plan.blob_views(blob)[2], want)
+
+
 def test_no_bias_and_repeatability(wq):
     d = workloads.small_layer(21, 2, 9, 7, 64, 32, 4, 32)
     d.bias = None
