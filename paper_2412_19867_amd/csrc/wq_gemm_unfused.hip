@@ -362,7 +362,7 @@ __global__ __launch_bounds__(256) void k_output_transform_int(const OIArgs a) {
     for (int i = 0; i < n; ++i)
 #pragma unroll
         for (int j = 0; j < n; ++j)
-            q[i][j] = (int)fmin(127.0, fmax(-127.0, rint((double)Yv[i * n + j] * r_y)));
+            q[i][j] = quant_code_f64((double)Yv[i * n + j] * r_y);
     int u[M][n];   // Q_A q
 #pragma unroll
     for (int aa = 0; aa < M; ++aa)
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void k_output_transform_int(const OIArgs a) {
         for (int j = 0; j < n; ++j) {
             int acc = 0;
 #pragma unroll
-            for (int i = 0; i < n; ++i) acc += a.xi.QA[aa * n + i] * q[i][j];
+            for (int i = 0; i < n; ++i) acc = mad24(a.xi.QA[aa * n + i], q[i][j], acc);
             u[aa][j] = acc;
         }
     const int tw = tau % a.TW, th = (tau / a.TW) % a.TH, bb = tau / (a.TW * a.TH);
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256) void k_output_transform_int(const OIArgs a) {
         for (int b = 0; b < M; ++b) {
             int acc = 0;
 #pragma unroll
-            for (int j = 0; j < n; ++j) acc += u[aa][j] * a.xi.QA[b * n + j];
+            for (int j = 0; j < n; ++j) acc = mad24(a.xi.QA[b * n + j], u[aa][j], acc);
             const double v = (a.xi.sAA[aa * M + b] * s_y) * (double)acc + bv;
             if (aa < hv && b < wv) store_y((float)v, base + ((size_t)aa * a.W + b) * a.Cout);
         }

@@ -376,7 +376,7 @@ __global__ __launch_bounds__(256) void k_input_transform_int(wq_xi xi, const flo
 #pragma unroll
             for (int j = 0; j < n; ++j) {
                 const double v = (double)(c ? d[kk][j].y : d[kk][j].x) * r_x;
-                q[kk][j] = (int)fmin(127.0, fmax(-127.0, rint(v)));
+                q[kk][j] = quant_code_f64(v);
             }
         int t1[n][n];   // Q_B q
 #pragma unroll
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(256) void k_input_transform_int(wq_xi xi, const flo
             for (int j = 0; j < n; ++j) {
                 int acc = 0;
 #pragma unroll
-                for (int kk = 0; kk < n; ++kk) acc += xi.QB[i * n + kk] * q[kk][j];
+                for (int kk = 0; kk < n; ++kk) acc = mad24(xi.QB[i * n + kk], q[kk][j], acc);
                 t1[i][j] = acc;
             }
 #pragma unroll
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void k_input_transform_int(wq_xi xi, const flo
             for (int j = 0; j < n; ++j) {
                 int acc = 0;
 #pragma unroll
-                for (int l = 0; l < n; ++l) acc += t1[i][l] * xi.QB[j * n + l];
+                for (int l = 0; l < n; ++l) acc = mad24(xi.QB[j * n + l], t1[i][l], acc);
                 const float v = (float)((xi.sBB[i * n + j] * s_x) * (double)acc);
                 if (c) X[i * n + j].y = v; else X[i * n + j].x = v;
             }

@@ -42,6 +42,16 @@ def test_integer_transforms_match_the_oracle(wq, case):
     check_integer(wq, d, mode, variant)
 
 
+@pytest.mark.parametrize("m", [2, 4, 6])
+def test_integer_transforms_at_codes_of_full_magnitude(wq, m):
+    """Every patch code is +-127 (one magnitude, signs that line up with a row of B^T or none): the
+    largest integer sums the transforms meet, and many values that lie exactly on a code."""
+    d = workloads.small_layer(320 + m, 1, 3 * m, 2 * m + 1, 64, 33, m, 32)
+    d.x = np.where(d.x < 0, np.float32(-3.0), np.float32(3.0))
+    d.x[:, : m + 1] = np.float32(3.0)
+    check_integer(wq, d, 1, None)
+
+
 @pytest.mark.parametrize("idx", [0, 1, 2])
 def test_integer_transforms_on_the_headline_layers_at_full_size(wq, idx):
     """The three layer shapes of the SDXL-scale stack, in the variant the plan picks."""
