@@ -16,6 +16,7 @@
 #include <new>
 
 #include "wq_device.h"
+#include "wq_direct_walk.h"
 #include "wq_internal.h"
 
 struct wq_direct_plan {
@@ -23,9 +24,7 @@ struct wq_direct_plan {
     int N, H, W, Cin, Cout, g, groups, P, Cout_pad, kstep;
     int taps;     // 9 = 3x3 convolution, 1 = linear layer (every row is its own "image")
     int wbits;    // width of the weight codes: 8, or 4 (W4A8: two codes per byte)
-    // the kernel instance and its launch shape (choose_tile): 16-row blocks per wave along channels and
-    // pixels, waves per workgroup that split a wave tile's reduction, wave tiles per workgroup
-    int no, nb, slices, wo, wt;
+    wq_direct_tile tile;   // the kernel instance and its launch shape
     int splits;   // 1, or the number of slices wq_direct_plan_tune asked for
     wq_direct_layout_t lay;
     std::atomic<int> prepared;
@@ -101,7 +100,7 @@ struct DArgs {
     const float *sW;
     const float *bias;
     float *y;
-    int H, W, Cin, Cout, Cout_pad, P, log2g, taps;
+    int H, W, Cin, Cout, Cout_pad, P, log2g;
     // how a workgroup's waves share its work: `slices` waves split the reduction of one wave tile,
     // wo x wt wave tiles lie side by side along channels x pixels (slices * wo * wt waves)
     int slices, wo, wt;
@@ -129,7 +128,8 @@ struct DArgs {
 // with the sums (exact), and 16 * |sum| stays below 2^24 for every group size.
 template <bool K64, bool CPG1, bool W4, bool T9, int NO, int NB, int D, int NWMAX>
 __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
-    constexpr int KSTEP = K64 ? 64 : 32, KB = KSTEP / 4, BLK = 16 * KSTEP;
+    constexpr int KSTEP = K64 ? 64 : 32, KB = KSTEP / 4;
+    using Walk = wq_direct_walk<KSTEP, W4, T9>;
     constexpr int RS = 16 * NO + 4;                        // floats per pixel row of the LDS staging
     extern __shared__ __attribute__((aligned(16))) float part_s[];   // [waves][16][RS]
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
@@ -140,19 +140,15 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     const int logical = (int)(blockIdx.x & 7u) * a.per_xcd + (int)(blockIdx.x >> 3);
     if (logical >= a.total) return;   // the whole workgroup leaves, before any barrier
     const int ob0 = ((logical % a.nOt) * a.wo + wo) * NO, p0 = ((logical / a.nOt) * a.wt + wt) * 16 * NB;
-    const int Cin = a.Cin, P = a.P, groups = Cin >> a.log2g, cps = Cin / KSTEP;
-    const int cpg = (1 << a.log2g) / KSTEP;
-    // the pixel buffer starts the largest backward shift of a filter tap (a row and a pixel) early, so
-    // that shifts are non-negative scalar offsets; lanes whose pixel leaves the image load nothing
-    const int back = T9 ? a.W + 1 : 0;
+    const int Cin = a.Cin, P = a.P, groups = Cin >> a.log2g, back = Walk::back(a.W);
+    // (lanes whose pixel leaves the image load nothing)
 
     const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int8_t *>(a.Wq), 0,
-        (int)(((unsigned)a.taps * (unsigned)a.Cout_pad * (unsigned)Cin) >> (W4 ? 1 : 0)), kBufFlags);
+        const_cast<int8_t *>(a.Wq), 0, (int)Walk::bytes_w(a.Cout_pad, Cin), kBufFlags);
     const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int8_t *>(a.xq) - back * KB, 0, (int)((unsigned)P * (unsigned)Cin + (unsigned)(back * KB)), kBufFlags);
     const __amdgpu_buffer_rsrc_t rSW = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(a.sW), 0, (int)((unsigned)a.taps * (unsigned)groups * (unsigned)a.Cout_pad * 4u), kBufFlags);
+        const_cast<float *>(a.sW), 0, (int)Walk::bytes_sw(a.Cout_pad, groups), kBufFlags);
     const __amdgpu_buffer_rsrc_t rSX = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(a.sx) - back, 0, (int)(((unsigned)P * (unsigned)groups + (unsigned)back) * 4u), kBufFlags);
 
@@ -171,24 +167,18 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     }
 
     // ---- the loader: its cursor walks (tap, K-step) of the wave's slice and stops at the end ----
-    const int taps = T9 ? 9 : 1, G = taps * groups;
-    const int g_beg = ks * G / a.slices, g_end = (ks + 1) * G / a.slices;
-    const int NI = (g_end - g_beg) * cpg;
-    int t_f = g_beg / groups, gam_f = g_beg - t_f * groups, k_f = 0, left_f = NI;
-    const unsigned vW = (unsigned)(lane * KB) >> (W4 ? 1 : 0), vSW = (unsigned)(4 * q + (lane & 3)) * 4u, vSX = (unsigned)(p0 + (lane & (16 * NB - 1))) * 4u;
-    const unsigned blkW = 16u * (unsigned)Cin, jumpW = (unsigned)a.Cout_pad * (unsigned)Cin - blkW;   // next tap's plane
-    const unsigned stepX = 4u * (unsigned)P * (unsigned)KB, stepSX = (unsigned)P * 4u, stepSW = (unsigned)a.Cout_pad * 4u;
-    unsigned oW = (unsigned)t_f * (unsigned)a.Cout_pad * (unsigned)Cin + (unsigned)ob0 * blkW + (unsigned)(gam_f * cpg) * BLK;
-    unsigned oSW = (unsigned)g_beg * stepSW + (unsigned)ob0 * 64u;
-    int col_f = T9 ? t_f % 3 : 0;                      // the tap's column in the window
-    unsigned shift = T9 ? (unsigned)((t_f / 3) * a.W + col_f) : 0u;   // pixels from the buffer's start, = back + dp
-    unsigned oX = (unsigned)(gam_f * cpg) * stepX + shift * (unsigned)KB, oSX = (unsigned)gam_f * stepSX + shift * 4u;
+    Walk at(P, a.W, Cin, a.Cout_pad, a.log2g, ks, a.slices);
+    const int NI = at.steps, cpg = at.cpg;
+    const unsigned vW = Walk::lane_w(lane), vSW = Walk::lane_sw(lane), vSX = (unsigned)(p0 + (lane & (16 * NB - 1))) * 4u;
+    unsigned oe[NO];
+#pragma unroll
+    for (int e = 0; e < NO; ++e) oe[e] = wq_direct_block(ob0, e, a.Cout_pad);
     v4i av[D][NO], bv[D][NB];
     float swv[D][NO], sxv[D];
     auto fetch = [&](int slot) {   // (slot is a constant after unrolling)
 #pragma unroll
         for (int e = 0; e < NO; ++e) {
-            const unsigned so = (oW + (unsigned)e * blkW) >> (W4 ? 1 : 0);
+            const unsigned so = at.weights(oe[e]);
             if constexpr (K64 && !W4) {
                 av[slot][e] = __builtin_amdgcn_raw_buffer_load_b128(rW, vW, so, 0);
             } else if constexpr (K64 || !W4) {
@@ -200,40 +190,20 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
         }
 #pragma unroll
         for (int f = 0; f < NB; ++f) {   // a pixel outside the image: bit 31 of the offset, past the end
-            const unsigned vo = T9 ? vX[f] | ((out[f] << (31 - t_f)) & 0x80000000u) : vX[f];
+            const unsigned vo = T9 ? vX[f] | ((out[f] << (31 - at.t)) & 0x80000000u) : vX[f];
             if constexpr (K64) {
-                bv[slot][f] = __builtin_amdgcn_raw_buffer_load_b128(rX, vo, oX, 0);
+                bv[slot][f] = __builtin_amdgcn_raw_buffer_load_b128(rX, vo, at.oX, 0);
             } else {
-                const v2i t = __builtin_amdgcn_raw_buffer_load_b64(rX, vo, oX, 0);
+                const v2i t = __builtin_amdgcn_raw_buffer_load_b64(rX, vo, at.oX, 0);
                 bv[slot][f] = v4i{t.x, t.y, 0, 0};
             }
         }
 #pragma unroll
         for (int e = 0; e < NO; ++e)
-            swv[slot][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSW, vSW, oSW + 64u * e, 0));
+            swv[slot][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSW, vSW, at.weight_scales(oe[e]), 0));
         // (a pixel outside the image takes some other pixel's scale, or the zeros before the first: its codes are 0)
-        sxv[slot] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX, oSX, 0));
-        // branch-free scalar bookkeeping (a branch here would let the compiler sink the
-        // dequantization of all D steps to the end of the round, with their sums in registers)
-        const bool go = --left_f > 0;
-        k_f += go ? 1 : 0;
-        const bool ng = go && k_f == cpg;
-        k_f = ng ? 0 : k_f;
-        gam_f += ng ? 1 : 0;
-        const bool nt = T9 && gam_f == groups;
-        gam_f = nt ? 0 : gam_f;
-        oW += (go ? (unsigned)BLK : 0u) + (nt ? jumpW : 0u);
-        oSW += ng ? stepSW : 0u;
-        oX += go ? stepX : 0u;
-        oSX += ng ? stepSX : 0u;
-        if constexpr (T9) {
-            t_f += nt ? 1 : 0;
-            const unsigned d = col_f == 2 ? (unsigned)(a.W - 2) : 1u;
-            shift += nt ? d : 0u;
-            col_f = nt ? (col_f == 2 ? 0 : col_f + 1) : col_f;
-            oX = nt ? shift * (unsigned)KB : oX;
-            oSX = nt ? shift * 4u : oSX;
-        }
+        sxv[slot] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX, at.oSX, 0));
+        at.advance();
     };
     auto unpack = [](const v4i &pk) {
         if constexpr (!W4) return pk;
@@ -360,47 +330,8 @@ int ilog2(int v) {
 
 uint64_t align256(uint64_t v) { return (v + 255) / 256 * 256; }
 
-// Wave tile (16-row blocks along channels x pixels) and how many waves share its reduction.  A big
-// tile moves fewer operand bytes per product; but a CU takes only 8 waves of it, and a launch is as
-// slow as the CU with the most of them.  Measured over layers from 5 to 9792 pixels and 32 to 5120
-// channels; n44 = the tiles of 64 x 64:
-//   n44 >= 1500      64 x 64; from 3000 on enough waves without sharing a reduction at all
-//   n44 >= 150       64 x 64 and 4 slices, except 3x3 layers below 640 tiles: there the nine-fold
-//                    reduction makes a tile of work so big that 32 x 64 fills the last round better
-//                    (2 x 32^2 pixels, 640 -> 640: 26.5 against 29.8 us)
-//   n44 >= 40        32 x 64, 8 slices
-//   fewer            16 x 16 (as long as those are few too), else 16 x 64, 8 slices: latency rules,
-//                    every wave should have only a handful of K-steps
 void choose_tile(wq_direct_plan *p) {
-    const long ob = p->Cout_pad / 16, pb = (p->P + 15) / 16, G = (long)p->taps * p->groups;
-    const long n44 = ((ob + 3) / 4) * ((pb + 3) / 4);
-    p->wo = p->wt = 1;
-    p->nb = 4;
-    if (pb == 1 || (n44 < 40 && ob * pb <= 512)) {
-        p->no = p->nb = 1;
-        p->slices = 8;
-        while (p->slices > 4 && ob * pb * p->slices > 2048) p->slices /= 2;
-    } else if (n44 < 40) {
-        p->no = 1; p->slices = 8;
-    } else if (n44 < 150) {
-        p->no = 2; p->slices = 8;
-    } else if (p->taps == 9 && n44 < 640) {
-        p->no = 2;
-        p->slices = ((ob + 1) / 2) * ((pb + 3) / 4) > 1000 ? 2 : 4;
-    } else if (n44 < 1500) {
-        p->no = 4; p->slices = 4;
-    } else if (n44 < 3000) {
-        p->no = 4; p->slices = 2; p->wt = 2;
-    } else {
-        p->no = 4; p->slices = 1; p->wo = p->wt = 2;
-    }
-    if (p->splits > 1) {
-        p->slices = p->splits;
-        p->wo = p->wt = 1;
-        if (p->slices > 8) p->no = 1;   // the larger tiles' registers allow 8 waves per workgroup
-    } else {
-        while (p->slices > 1 && G * p->g < 2L * p->kstep * p->slices) p->slices /= 2;   // two K-steps each at least
-    }
+    p->tile = wq_direct_choose_tile(p->P, p->Cout_pad, p->taps, p->groups, p->g, p->kstep, p->splits);
 }
 
 template <bool K64, bool CPG1, bool W4, bool T9, int NO, int NB, int D, int NWMAX>
@@ -418,9 +349,9 @@ void launch_conv(const DArgs &a0, hipStream_t s) {
 
 template <bool K64, bool CPG1, bool W4, bool T9>
 void launch_conv_tile(const wq_direct_plan *p, const DArgs &a, hipStream_t s) {
-    if (p->no == 4) launch_conv<K64, CPG1, W4, T9, 4, 4, 2, 8>(a, s);
-    else if (p->no == 2) launch_conv<K64, CPG1, W4, T9, 2, 4, 3, 8>(a, s);
-    else if (p->nb == 4) launch_conv<K64, CPG1, W4, T9, 1, 4, 3, 16>(a, s);
+    if (p->tile.no == 4) launch_conv<K64, CPG1, W4, T9, 4, 4, 2, 8>(a, s);
+    else if (p->tile.no == 2) launch_conv<K64, CPG1, W4, T9, 2, 4, 3, 8>(a, s);
+    else if (p->tile.nb == 4) launch_conv<K64, CPG1, W4, T9, 1, 4, 3, 16>(a, s);
     else launch_conv<K64, CPG1, W4, T9, 1, 1, 6, 16>(a, s);
 }
 
@@ -581,10 +512,9 @@ wq_status_t wq_direct_conv(const wq_direct_plan_t *plan, void *stream, void *wor
     a.sW = (const float *)(b + plan->lay.blob_sW_off);
     a.bias = (const float *)(b + plan->lay.blob_bias_off);
     a.y = y_dev;
-    a.taps = plan->taps;
     a.H = plan->H; a.W = plan->W; a.Cin = plan->Cin; a.Cout = plan->Cout;
     a.Cout_pad = plan->Cout_pad; a.P = plan->P; a.log2g = ilog2(plan->g);
-    a.slices = plan->slices; a.wo = plan->wo; a.wt = plan->wt;
+    a.slices = plan->tile.slices; a.wo = plan->tile.wo; a.wt = plan->tile.wt;
     hipStream_t s = (hipStream_t)stream;
     const bool k32 = plan->kstep == 32, one = plan->g == 64;
     if (plan->wbits == 4) {

@@ -1,0 +1,142 @@
+// How k_direct_conv (wq_direct.hip) cuts a layer into wave tiles, and the addresses a wave walks.
+// Plain integer arithmetic without device code, so that a CPU test can enumerate every access of a
+// launch against the buffers' sizes.
+#pragma once
+
+#ifdef __HIP__
+#define WQ_HD __host__ __device__ __forceinline__
+#else
+#define WQ_HD inline
+#endif
+
+// The kernel instance and its launch shape: 16-row blocks per wave along channels and pixels, waves per
+// workgroup that split a wave tile's reduction, wave tiles per workgroup along channels and pixels.
+struct wq_direct_tile {
+    int no, nb, slices, wo, wt;
+};
+
+// Wave tile (16-row blocks along channels x pixels) and how many waves share its reduction.  A big
+// tile moves fewer operand bytes per product; but a CU takes only 8 waves of it, and a launch is as
+// slow as the CU with the most of them.  Measured over layers from 5 to 9792 pixels and 32 to 5120
+// channels; n44 = the tiles of 64 x 64:
+//   n44 >= 1500      64 x 64; from 3000 on enough waves without sharing a reduction at all
+//   n44 >= 150       64 x 64 and 4 slices, except 3x3 layers below 640 tiles: there the nine-fold
+//                    reduction makes a tile of work so big that 32 x 64 fills the last round better
+//                    (2 x 32^2 pixels, 640 -> 640: 26.5 against 29.8 us)
+//   n44 >= 40        32 x 64, 8 slices
+//   fewer            16 x 16 (as long as those are few too), else 16 x 64, 8 slices: latency rules,
+//                    every wave should have only a handful of K-steps
+inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int groups, int g, int kstep, int splits) {
+    const long ob = Cout_pad / 16, pb = (P + 15) / 16, G = (long)taps * groups;
+    const long n44 = ((ob + 3) / 4) * ((pb + 3) / 4);
+    wq_direct_tile t = {1, 4, 1, 1, 1};
+    if (pb == 1 || (n44 < 40 && ob * pb <= 512)) {
+        t.nb = 1;
+        t.slices = 8;
+        while (t.slices > 4 && ob * pb * t.slices > 2048) t.slices /= 2;
+    } else if (n44 < 40) {
+        t.slices = 8;
+    } else if (n44 < 150) {
+        t.no = 2; t.slices = 8;
+    } else if (taps == 9 && n44 < 640) {
+        t.no = 2;
+        t.slices = ((ob + 1) / 2) * ((pb + 3) / 4) > 1000 ? 2 : 4;
+    } else if (n44 < 1500) {
+        t.no = 4; t.slices = 4;
+    } else if (n44 < 3000) {
+        t.no = 4; t.slices = 2; t.wt = 2;
+    } else {
+        t.no = 4; t.wo = t.wt = 2;
+    }
+    if (splits > 1) {
+        t.slices = splits;
+        t.wo = t.wt = 1;
+        if (t.slices > 8) t.no = 1;   // the larger tiles' registers allow 8 waves per workgroup
+    } else {
+        while (t.slices > 1 && G * g < 2L * kstep * t.slices) t.slices /= 2;   // two K-steps each at least
+    }
+    return t;
+}
+
+// The loader's cursor over one slice of a wave tile's reduction: whole groups of the flat sequence
+// tap-major, then channels.  Scalar byte offsets into the four buffers; the per-lane parts are below.
+template <int KSTEP, bool W4, bool T9>
+struct wq_direct_walk {
+    static constexpr unsigned KB = KSTEP / 4, BLK = 16 * KSTEP;
+    int W, groups, cpg, steps;   // steps: K-steps of the slice
+    int t, gam, k, left, col;    // filter tap, group, K-step in the group, K-steps not yet requested, tap's window column
+    unsigned blkW, jumpW, stepX, stepSX, stepSW;
+    unsigned oW, oSW, shift, oX, oSX;   // shift: pixels from the pixel buffer's start, = back + the tap's shift
+
+    // the pixel buffers start the largest backward shift of a filter tap (a row and a pixel) early, so
+    // that shifts are non-negative scalar offsets
+    static WQ_HD int back(int W) { return T9 ? W + 1 : 0; }
+    // lane parts
+    static WQ_HD unsigned lane_w(int lane) { return ((unsigned)lane * KB) >> (W4 ? 1 : 0); }
+    static WQ_HD unsigned lane_sw(int lane) { return (unsigned)(4 * (lane >> 4) + (lane & 3)) * 4u; }
+    // buffer sizes
+    static WQ_HD unsigned bytes_w(int Cout_pad, int Cin) {
+        return ((T9 ? 9u : 1u) * (unsigned)Cout_pad * (unsigned)Cin) >> (W4 ? 1 : 0);
+    }
+    static WQ_HD unsigned bytes_sw(int Cout_pad, int groups) {
+        return (T9 ? 9u : 1u) * (unsigned)groups * (unsigned)Cout_pad * 4u;
+    }
+
+    WQ_HD wq_direct_walk(int P, int W_, int Cin, int Cout_pad, int log2g, int ks, int slices) {
+        W = W_;
+        groups = Cin >> log2g;
+        cpg = (1 << log2g) / KSTEP;
+        const int G = (T9 ? 9 : 1) * groups, g_beg = ks * G / slices, g_end = (ks + 1) * G / slices;
+        steps = left = (g_end - g_beg) * cpg;
+        t = g_beg / groups;
+        gam = g_beg - t * groups;
+        k = 0;
+        blkW = 16u * (unsigned)Cin;
+        jumpW = (unsigned)Cout_pad * (unsigned)Cin - blkW;   // next tap's plane
+        stepX = 4u * (unsigned)P * KB;
+        stepSX = (unsigned)P * 4u;
+        stepSW = (unsigned)Cout_pad * 4u;
+        oW = (unsigned)t * (unsigned)Cout_pad * (unsigned)Cin + (unsigned)(gam * cpg) * BLK;
+        oSW = (unsigned)g_beg * stepSW;
+        col = T9 ? t % 3 : 0;
+        shift = T9 ? (unsigned)((t / 3) * W + col) : 0u;
+        oX = (unsigned)(gam * cpg) * stepX + shift * KB;
+        oSX = (unsigned)gam * stepSX + shift * 4u;
+    }
+
+    // offsets of the 16-channel block `ob`
+    WQ_HD unsigned weights(unsigned ob) const { return (oW + ob * blkW) >> (W4 ? 1 : 0); }
+    WQ_HD unsigned weight_scales(unsigned ob) const { return oSW + ob * 64u; }
+
+    // branch-free scalar bookkeeping (a branch here would let the compiler sink the dequantization of
+    // all steps in flight to the end of the round, with their sums in registers); stops at the last K-step
+    WQ_HD void advance() {
+        const bool go = --left > 0;
+        k += go ? 1 : 0;
+        const bool ng = go && k == cpg;
+        k = ng ? 0 : k;
+        gam += ng ? 1 : 0;
+        const bool nt = T9 && gam == groups;
+        gam = nt ? 0 : gam;
+        oW += (go ? BLK : 0u) + (nt ? jumpW : 0u);
+        oSW += ng ? stepSW : 0u;
+        oX += go ? stepX : 0u;
+        oSX += ng ? stepSX : 0u;
+        if constexpr (T9) {
+            t += nt ? 1 : 0;
+            const unsigned d = col == 2 ? (unsigned)(W - 2) : 1u;
+            shift += nt ? d : 0u;
+            col = nt ? (col == 2 ? 0 : col + 1) : col;
+            oX = nt ? shift * KB : oX;
+            oSX = nt ? shift * 4u : oSX;
+        }
+    }
+};
+
+// The 16-channel blocks of a wave tile that starts at block ob0.  A tile may end past the padded
+// channels (a multiple of 32, where a tile has up to 64): such a block reads the last one again and
+// is not stored, so that no offset passes the end of the weights.
+WQ_HD unsigned wq_direct_block(int ob0, int e, int Cout_pad) {
+    const int last = Cout_pad / 16 - 1;
+    return (unsigned)(ob0 + e < last ? ob0 + e : last);
+}
