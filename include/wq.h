@@ -285,7 +285,6 @@ wq_status_t wq_conv_forward_debug_slab(const wq_plan_t *plan, void *stream, cons
  *   workspace   : xq int8 [Cin/kstep][4][N*H*W][kstep/4]           at ws_xq_off
  *                   (planes of one K-quarter of one MFMA K-step, pixels in order inside a plane)
  *                 sx fp32 [groups][N*H*W]                          at ws_sx_off
- *                   (a 3x3 plan keeps W+1 zero scales right before it)
  * Conventions as above: caller-owned device memory, calls enqueue on `stream`
  * and never synchronise, every argument is checked on the host.  Errors:
  * non-positive sizes, NULL pointers, Cin not a multiple of group_size ->

@@ -32,8 +32,6 @@ struct wq_direct_plan {
 
 namespace {
 
-constexpr unsigned kInvalid = kPastEnd;
-
 // ------------------------------------------------------------ activations
 // xq is stored as [Cin/kstep][4][P][kstep/4]: planes of one K-quarter of one MFMA K-step, pixels
 // in order inside a plane.  The wave that multiplies 16 consecutive pixels then reads four runs of
@@ -46,9 +44,7 @@ template <int CPL>
 __global__ __launch_bounds__(256) void k_quantize_pixels(const float *__restrict__ x,
                                                          int8_t *__restrict__ xq,
                                                          float *__restrict__ sx, int P, int Cin,
-                                                         int groups, int gpairs, int guard) {
-    if (blockIdx.x == 0)   // the scales a window position before the first pixel would read
-        for (int e = threadIdx.x; e < guard; e += 256) sx[e - guard] = 0.0f;
+                                                         int groups, int gpairs) {
     const int tid = threadIdx.x, l8 = tid & 7, unit = tid >> 3;
     const int pb = blockIdx.x / gpairs, gi = (blockIdx.x % gpairs) * 2 + (unit >> 4);
     const int row = unit & 15, p = pb * 16 + row;
@@ -141,35 +137,33 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     if (logical >= a.total) return;   // the whole workgroup leaves, before any barrier
     const int ob0 = ((logical % a.nOt) * a.wo + wo) * NO, p0 = ((logical / a.nOt) * a.wt + wt) * 16 * NB;
     const int Cin = a.Cin, P = a.P, groups = Cin >> a.log2g, back = Walk::back(a.W);
-    // (lanes whose pixel leaves the image load nothing)
 
     const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int8_t *>(a.Wq), 0, (int)Walk::bytes_w(a.Cout_pad, Cin), kBufFlags);
     const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int8_t *>(a.xq) - back * KB, 0, (int)((unsigned)P * (unsigned)Cin + (unsigned)(back * KB)), kBufFlags);
+        const_cast<int8_t *>(a.xq) - back * KB, 0, (int)Walk::bytes_x(P, a.W, Cin), kBufFlags);
     const __amdgpu_buffer_rsrc_t rSW = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(a.sW), 0, (int)Walk::bytes_sw(a.Cout_pad, groups), kBufFlags);
     const __amdgpu_buffer_rsrc_t rSX = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(a.sx) - back, 0, (int)(((unsigned)P * (unsigned)groups + (unsigned)back) * 4u), kBufFlags);
+        const_cast<float *>(a.sx) - back, 0, (int)Walk::bytes_sx(P, a.W, groups), kBufFlags);
 
-    // which of the 9 window positions of the lane's pixel of each row block lie OUTSIDE the image
-    // (columns past the last pixel compute on whatever is there and are not stored)
+    // The lane's pixel of each row block, and the one whose scale it loads: a position that lies outside
+    // the image, or past the last pixel, loads neither codes nor scale (its neighbour in memory is a
+    // pixel of another row or image, whose scale may be infinite: 0 * Inf would reach this pixel's sum)
     unsigned out[NB], vX[NB];
 #pragma unroll
     for (int f = 0; f < NB; ++f) {
         const int p = p0 + 16 * f + l16;
-        vX[f] = (unsigned)(q * P + p) * (unsigned)KB;
-        if constexpr (T9) {
-            const int ww = p % a.W, hh = (p / a.W) % a.H;
-            out[f] = (hh == 0 ? 0x007u : 0u) | (hh == a.H - 1 ? 0x1c0u : 0u) | (ww == 0 ? 0x049u : 0u) |
-                     (ww == a.W - 1 ? 0x124u : 0u);
-        }
+        vX[f] = p < P ? Walk::lane_x(q, p, P) : kPastEnd;
+        out[f] = Walk::outside(p, a.H, a.W);
     }
+    const int ps = p0 + (lane & (16 * NB - 1));
+    const unsigned vSX = ps < P ? Walk::lane_sx(ps) : kPastEnd, outS = Walk::outside(ps, a.H, a.W);
 
     // ---- the loader: its cursor walks (tap, K-step) of the wave's slice and stops at the end ----
     Walk at(P, a.W, Cin, a.Cout_pad, a.log2g, ks, a.slices);
     const int NI = at.steps, cpg = at.cpg;
-    const unsigned vW = Walk::lane_w(lane), vSW = Walk::lane_sw(lane), vSX = (unsigned)(p0 + (lane & (16 * NB - 1))) * 4u;
+    const unsigned vW = Walk::lane_w(lane), vSW = Walk::lane_sw(lane);
     unsigned oe[NO];
 #pragma unroll
     for (int e = 0; e < NO; ++e) oe[e] = wq_direct_block(ob0, e, a.Cout_pad);
@@ -189,8 +183,8 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
             }
         }
 #pragma unroll
-        for (int f = 0; f < NB; ++f) {   // a pixel outside the image: bit 31 of the offset, past the end
-            const unsigned vo = T9 ? vX[f] | ((out[f] << (31 - at.t)) & 0x80000000u) : vX[f];
+        for (int f = 0; f < NB; ++f) {
+            const unsigned vo = at.masked(vX[f], out[f]);
             if constexpr (K64) {
                 bv[slot][f] = __builtin_amdgcn_raw_buffer_load_b128(rX, vo, at.oX, 0);
             } else {
@@ -201,8 +195,7 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
 #pragma unroll
         for (int e = 0; e < NO; ++e)
             swv[slot][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSW, vSW, at.weight_scales(oe[e]), 0));
-        // (a pixel outside the image takes some other pixel's scale, or the zeros before the first: its codes are 0)
-        sxv[slot] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX, at.oSX, 0));
+        sxv[slot] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, at.masked(vSX, outS), at.oSX, 0));
         at.advance();
     };
     auto unpack = [](const v4i &pk) {
@@ -409,8 +402,7 @@ static wq_status_t make_plan(wq_direct_plan_t **out, int N, int H, int W, int Ci
     L.blob_bias_off = L.blob_sW_off + align256((uint64_t)taps * p->groups * p->Cout_pad * 4);
     L.blob_bytes = L.blob_bias_off + align256((uint64_t)p->Cout_pad * 4);
     L.ws_xq_off = 0;
-    // (a window row and a pixel of zero scales lie before the first pixel's)
-    L.ws_sx_off = align256((uint64_t)P * Cin + (taps == 9 ? (uint64_t)(W + 1) * 4 : 0));
+    L.ws_sx_off = align256((uint64_t)P * Cin);
     p->splits = 1;
     choose_tile(p);
     L.splits = p->splits;
@@ -485,15 +477,15 @@ wq_status_t wq_direct_quantize(const wq_direct_plan_t *plan, void *stream, const
     char *ws = (char *)workspace_dev;
     int8_t *xq = (int8_t *)(ws + plan->lay.ws_xq_off);
     float *sx = (float *)(ws + plan->lay.ws_sx_off);
-    const int gpairs = (plan->groups + 1) / 2, guard = plan->taps == 9 ? plan->W + 1 : 0;
+    const int gpairs = (plan->groups + 1) / 2;
     const dim3 grid((unsigned)((plan->P + 15) / 16) * (unsigned)gpairs), block(256);
     hipStream_t s = (hipStream_t)stream;
     switch (plan->g) {
-        case 32: hipLaunchKernelGGL((k_quantize_pixels<4>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
-        case 64: hipLaunchKernelGGL((k_quantize_pixels<8>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
-        case 128: hipLaunchKernelGGL((k_quantize_pixels<16>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
-        case 256: hipLaunchKernelGGL((k_quantize_pixels<32>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
-        default: hipLaunchKernelGGL((k_quantize_pixels<64>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs, guard); break;
+        case 32: hipLaunchKernelGGL((k_quantize_pixels<4>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs); break;
+        case 64: hipLaunchKernelGGL((k_quantize_pixels<8>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs); break;
+        case 128: hipLaunchKernelGGL((k_quantize_pixels<16>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs); break;
+        case 256: hipLaunchKernelGGL((k_quantize_pixels<32>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs); break;
+        default: hipLaunchKernelGGL((k_quantize_pixels<64>), grid, block, 0, s, x_dev, xq, sx, plan->P, plan->Cin, plan->groups, gpairs); break;
     }
     return hipGetLastError() == hipSuccess ? WQ_OK : WQ_ERR_DEVICE;
 }

@@ -69,12 +69,30 @@ struct wq_direct_walk {
     unsigned oW, oSW, shift, oX, oSX;   // shift: pixels from the pixel buffer's start, = back + the tap's shift
 
     // the pixel buffers start the largest backward shift of a filter tap (a row and a pixel) early, so
-    // that shifts are non-negative scalar offsets
+    // that shifts are non-negative scalar offsets, and end the largest forward shift late, so that those
+    // do not pass the end; nothing is loaded from either margin (see masked)
     static WQ_HD int back(int W) { return T9 ? W + 1 : 0; }
+    // which of the 9 window positions of a pixel lie outside the image
+    static WQ_HD unsigned outside(int p, int H, int W) {
+        if (!T9) return 0;
+        const int ww = p % W, hh = (p / W) % H;
+        return (hh == 0 ? 0x007u : 0u) | (hh == H - 1 ? 0x1c0u : 0u) | (ww == 0 ? 0x049u : 0u) | (ww == W - 1 ? 0x124u : 0u);
+    }
+    // a lane's offset at the current tap: bit 31, past the end of every buffer, where the window position
+    // lies outside the image
+    WQ_HD unsigned masked(unsigned lane, unsigned out) const {
+        return T9 ? lane | ((out << (31 - t)) & 0x80000000u) : lane;
+    }
     // lane parts
+    static WQ_HD unsigned lane_x(int quarter, int p, int P) { return ((unsigned)quarter * (unsigned)P + (unsigned)p) * KB; }
+    static WQ_HD unsigned lane_sx(int p) { return (unsigned)p * 4u; }
     static WQ_HD unsigned lane_w(int lane) { return ((unsigned)lane * KB) >> (W4 ? 1 : 0); }
     static WQ_HD unsigned lane_sw(int lane) { return (unsigned)(4 * (lane >> 4) + (lane & 3)) * 4u; }
     // buffer sizes
+    static WQ_HD unsigned bytes_x(int P, int W, int Cin) { return (unsigned)P * (unsigned)Cin + 2u * (unsigned)back(W) * KB; }
+    static WQ_HD unsigned bytes_sx(int P, int W, int groups) {
+        return ((unsigned)P * (unsigned)groups + 2u * (unsigned)back(W)) * 4u;
+    }
     static WQ_HD unsigned bytes_w(int Cout_pad, int Cin) {
         return ((T9 ? 9u : 1u) * (unsigned)Cout_pad * (unsigned)Cin) >> (W4 ? 1 : 0);
     }

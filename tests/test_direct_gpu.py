@@ -158,3 +158,45 @@ def test_slices_of_the_quantized_convolution(wq, shape, splits):
     got = y.cpu().numpy().astype(np.float64)
     assert np.isfinite(got).all()
     assert np.abs(got - ref["y64"]).max() <= Y_TOL * np.abs(ref["y64"]).max()
+
+
+def forward_on_poisoned_buffers(wq, x, w, bias, g, bits=8):
+    """y of one forward pass with every byte of the workspace 0xff beforehand (NaN as a scale)."""
+    N, H, W, Cin = x.shape
+    plan = wq.DirectPlan(N, H, W, Cin, w.shape[0], g, weight_bits=bits)
+    blob, ws, y = plan.alloc_blob(), plan.alloc_workspace(), plan.alloc_output()
+    ws.fill_(0xff)
+    y.fill_(float("nan"))
+    plan.weight_prepare(torch.from_numpy(w).cuda(), None if bias is None else torch.from_numpy(bias).cuda(), blob)
+    plan.forward(torch.from_numpy(x).cuda(), blob, ws, y)
+    return y.cpu().numpy()
+
+
+@pytest.mark.parametrize("bits", [8, 4], ids=["w8", "w4"])
+@pytest.mark.parametrize("Cout", [20, 200])
+@pytest.mark.parametrize("g", [32, 64, 128])
+def test_an_infinite_input_reaches_only_the_windows_that_hold_it(wq, g, Cout, bits):
+    """An Inf at the edges of image 1: outputs whose 3x3 window does not hold it, in the same image and
+    in its neighbours in the batch, are what they are without it."""
+    d = workloads.small_layer(500 + g, 3, 9, 14, 2 * g, Cout, 4, g)
+    clean = forward_on_poisoned_buffers(wq, d.x, d.w, d.bias, g, bits)
+    assert np.isfinite(clean).all()
+    x, held = d.x.copy(), np.zeros(d.x.shape[:3], bool)
+    for h, v in ((0, 0), (0, 13), (4, 13), (5, 0), (8, 0), (8, 13)):
+        x[1, h, v, (h + v) % (2 * g)] = np.inf if h % 2 else -np.inf
+        held[1, max(0, h - 1):h + 2, max(0, v - 1):v + 2] = True
+    got = forward_on_poisoned_buffers(wq, x, d.w, d.bias, g, bits)
+    assert np.array_equal(got[~held].view(np.uint32), clean[~held].view(np.uint32))
+    assert not np.isfinite(got[held]).any()
+
+
+@pytest.mark.parametrize("W", [1, 5, 64, 200])
+@pytest.mark.parametrize("Cout", [1, 32, 33])
+def test_a_single_row_of_pixels(wq, W, Cout):
+    """One image one pixel high: every tap above and below it lies outside, and a row is as long as all
+    the pixels together."""
+    d = workloads.small_layer(600 + W, 1, 1, W, 96, Cout, 4, 32)
+    ref = oracle.direct_pipeline(d.x, d.w, d.bias, 32)
+    got = forward_on_poisoned_buffers(wq, d.x, d.w, d.bias, 32).astype(np.float64)
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref["y64"]).max() <= Y_TOL * np.abs(ref["y64"]).max()
