@@ -59,10 +59,15 @@ __device__ __forceinline__ void store_y(T v, T *p) {
 // 1.5 * 2^23 + sum while |sum| < 2^22 (any group of up to 256 int8 products): the float of the sum
 // is then one exact subtraction (2.4 cycles of a SIMD with two waves) instead of a conversion (4.3).
 constexpr int kMagic = 0x4B400000;
+// The same for sums that are multiples of 16 (4-bit weight codes, unpacked as 16 * code): from the bits
+// of 1.5 * 2^19, whose last place is 2^-4, the result is 1.5 * 2^19 + sum / 16.
+constexpr int kMagic16 = 0x49400000;
 
-template <bool MAGIC>
+// the float of a group's int32 sum, or of a sixteenth of it (exact: a multiple of 16 below 2^24)
+template <bool MAGIC, bool SIXTEENTH = false>
 __device__ __forceinline__ float group_sum(int v) {
-    return MAGIC ? __int_as_float(v) - 12582912.0f : (float)v;
+    if constexpr (MAGIC) return __int_as_float(v) - (SIXTEENTH ? 786432.0f : 12582912.0f);
+    return SIXTEENTH ? (float)v * 0.0625f : (float)v;
 }
 
 // Broadcast of 16-lane rows: lane l of `v` holds the value of pixel l of the wave's 64 (16) pixels;

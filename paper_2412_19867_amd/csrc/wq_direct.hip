@@ -120,8 +120,9 @@ struct DArgs {
 //   conversion (4.3).  Exact while |sum| < 2^22: 64 * 127 * 127 and, for 4-bit weights, 64 * 16 * 7 * 127.
 // W4: the weight codes are 4 bits wide, two per byte (see the weight kernels for the packing of a
 // 16-byte piece into 8).  A lane loads the packed half of its piece and unpacks it as 16 * code
-// (a nibble moved to the top of its byte), so the MFMA loop is the 8-bit one; the factor 16 leaves
-// with the sums (exact), and 16 * |sum| stays below 2^24 for every group size.
+// (a nibble moved to the top of its byte), so the MFMA loop is the 8-bit one; 16 * |sum| stays below
+// 2^24 for every group size, and the factor leaves where the sum becomes a float (exact), before any
+// scale: outputs reach as far as the 8-bit path's.
 template <bool K64, bool CPG1, bool W4, bool T9, int NO, int NB, int D, int NWMAX>
 __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     constexpr int KSTEP = K64 ? 64 : 32, KB = KSTEP / 4;
@@ -221,7 +222,8 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
         fetch(d);
         __builtin_amdgcn_sched_barrier(0);
     }
-    const v4i magic = {kMagic, kMagic, kMagic, kMagic};
+    constexpr int start = W4 ? kMagic16 : kMagic;
+    const v4i magic = {start, start, start, start};
     int k_c = 0;
     auto compute = [&](int u) {   // the K-step in slot u (a constant after unrolling)
         const bool done = CPG1 || ++k_c == cpg;   // the step completes a group: dequantize
@@ -248,10 +250,10 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
                             s2 = quad_bcast<2>(swv[u][e]), s3 = quad_bcast<3>(swv[u][e]);
 #pragma unroll
                 for (int f = 0; f < NB; ++f) {
-                    Mc[e][f].x = __builtin_fmaf(group_sum<CPG1>(P4[f][0]), s0 * sx[f], Mc[e][f].x);
-                    Mc[e][f].y = __builtin_fmaf(group_sum<CPG1>(P4[f][1]), s1 * sx[f], Mc[e][f].y);
-                    Mc[e][f].z = __builtin_fmaf(group_sum<CPG1>(P4[f][2]), s2 * sx[f], Mc[e][f].z);
-                    Mc[e][f].w = __builtin_fmaf(group_sum<CPG1>(P4[f][3]), s3 * sx[f], Mc[e][f].w);
+                    Mc[e][f].x = __builtin_fmaf(group_sum<CPG1, W4>(P4[f][0]), s0 * sx[f], Mc[e][f].x);
+                    Mc[e][f].y = __builtin_fmaf(group_sum<CPG1, W4>(P4[f][1]), s1 * sx[f], Mc[e][f].y);
+                    Mc[e][f].z = __builtin_fmaf(group_sum<CPG1, W4>(P4[f][2]), s2 * sx[f], Mc[e][f].z);
+                    Mc[e][f].w = __builtin_fmaf(group_sum<CPG1, W4>(P4[f][3]), s3 * sx[f], Mc[e][f].w);
                     P4[f] = v4i{0, 0, 0, 0};
                 }
             }
@@ -300,9 +302,7 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
                 const float4 t = *reinterpret_cast<const float4 *>(&tile[(z * 16 + r0) * RS]);
                 s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
             }
-            constexpr float unscale = W4 ? 0.0625f : 1.0f;
-            const float sum[4] = {s.x * unscale + bv4[0], s.y * unscale + bv4[1], s.z * unscale + bv4[2],
-                                  s.w * unscale + bv4[3]};
+            const float sum[4] = {s.x + bv4[0], s.y + bv4[1], s.z + bv4[2], s.w + bv4[3]};
             float *dst = a.y + (size_t)p * a.Cout + o;
             if ((a.Cout & 3) == 0) {   // o is a multiple of 4, so o + 3 < Cout and the address is 16-byte aligned
                 __builtin_nontemporal_store(v4f{sum[0], sum[1], sum[2], sum[3]}, reinterpret_cast<v4f *>(dst));

@@ -200,3 +200,17 @@ def test_a_single_row_of_pixels(wq, W, Cout):
     got = forward_on_poisoned_buffers(wq, d.x, d.w, d.bias, 32).astype(np.float64)
     assert np.isfinite(got).all()
     assert np.abs(got - ref["y64"]).max() <= Y_TOL * np.abs(ref["y64"]).max()
+
+
+@pytest.mark.parametrize("exponent", [124, -90])
+@pytest.mark.parametrize("bits", [8, 4], ids=["w8", "w4"])
+@pytest.mark.parametrize("g", [32, 64, 128])
+def test_outputs_near_the_ends_of_the_range(wq, g, bits, exponent):
+    """Activations scaled by a power of two scale the outputs by it, exactly, up to the largest floats."""
+    d = workloads.small_layer(700 + g, 2, 6, 7, 2 * g, 40, 4, g)
+    d.x /= np.float32(8.0)   # |y| stays below 16
+    base = forward_on_poisoned_buffers(wq, d.x, d.w, None, g, bits)
+    assert 1.0 < np.abs(base).max() < 16.0
+    got = forward_on_poisoned_buffers(wq, np.ldexp(d.x, exponent), d.w, None, g, bits)
+    want = np.ldexp(base.astype(np.float64), exponent).astype(np.float32)
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
