@@ -103,6 +103,11 @@ struct DArgs {
     int nOt, total, per_xcd;   // workgroup tiles along channels, workgroups, share of each XCD
 };
 
+// Pixel rows of a wave tile that go through LDS at a time: two blocks where eight (16) waves' rows fit 64 KB,
+// so that more of the waves that share a reduction take part in the sums behind it.
+template <int NO, int NB>
+constexpr int kRowsPerPass = (NB > 1 && NO <= 2) ? 32 : 16;
+
 // A wave owns a (16 NO channels) x (16 NB pixels) tile and one slice of its reduction (whole
 // groups of the flat sequence tap-major, then channels).  Operands go from memory straight into
 // the registers the MFMA reads (both tensors are in its operand order) and are requested D
@@ -128,7 +133,7 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     constexpr int KSTEP = K64 ? 64 : 32, KB = KSTEP / 4;
     using Walk = wq_direct_walk<KSTEP, W4, T9>;
     constexpr int RS = 16 * NO + 4;                        // floats per pixel row of the LDS staging
-    extern __shared__ __attribute__((aligned(16))) float part_s[];   // [waves][16][RS]
+    extern __shared__ __attribute__((aligned(16))) float part_s[];   // [waves][kRowsPerPass][RS]
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ks = w % a.slices, wtile = w / a.slices, wo = wtile % a.wo, wt = wtile / a.wo;
@@ -151,15 +156,17 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     // The lane's pixel of each row block, and the one whose scale it loads: a position that lies outside
     // the image, or past the last pixel, loads neither codes nor scale (its neighbour in memory is a
     // pixel of another row or image, whose scale may be infinite: 0 * Inf would reach this pixel's sum)
-    unsigned out[NB], vX[NB];
+    // (one pixel's divisions per lane, its mask spread over the row blocks)
+    const int ps = p0 + (lane & (16 * NB - 1));
+    const unsigned vSX = ps < P ? Walk::lane_sx(ps) : kPastEnd, outS = Walk::outside((unsigned)ps, (unsigned)a.H, (unsigned)a.W);
+    unsigned vX[NB];
+    float out[NB];
+    if constexpr (T9) spread_rows<NB>(__uint_as_float(outS), out);
 #pragma unroll
     for (int f = 0; f < NB; ++f) {
         const int p = p0 + 16 * f + l16;
         vX[f] = p < P ? Walk::lane_x(q, p, P) : kPastEnd;
-        out[f] = Walk::outside(p, a.H, a.W);
     }
-    const int ps = p0 + (lane & (16 * NB - 1));
-    const unsigned vSX = ps < P ? Walk::lane_sx(ps) : kPastEnd, outS = Walk::outside(ps, a.H, a.W);
 
     // ---- the loader: its cursor walks (tap, K-step) of the wave's slice and stops at the end ----
     Walk at(P, a.W, Cin, a.Cout_pad, a.log2g, ks, a.slices);
@@ -185,7 +192,7 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
         }
 #pragma unroll
         for (int f = 0; f < NB; ++f) {
-            const unsigned vo = at.masked(vX[f], out[f]);
+            const unsigned vo = at.masked(vX[f], T9 ? __float_as_uint(out[f]) : 0u);
             if constexpr (K64) {
                 bv[slot][f] = __builtin_amdgcn_raw_buffer_load_b128(rX, vo, at.oX, 0);
             } else {
@@ -208,13 +215,17 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
         return v4i{(int)((a0 << 4) & 0xf0f0f0f0u), (int)(a0 & 0xf0f0f0f0u), 0, 0};
     };
 
-    float4 Mc[NO][NB];
+    // 16 x 16 tiles add the sums of every twelve groups up in a second set of registers: their slices may be
+    // a quarter of the reduction, a longer chain of fp32 additions than the sum's precision allows
+    constexpr bool TOTALS = NB == 1;
+    static_assert(!TOTALS || D == 6, "twelve groups are two rounds of K-steps each");
+    float4 Mc[NO][NB], Mt[NO][NB];
     v4i acc[NO][NB];
 #pragma unroll
     for (int e = 0; e < NO; ++e)
 #pragma unroll
         for (int f = 0; f < NB; ++f) {
-            Mc[e][f] = make_float4(0.f, 0.f, 0.f, 0.f);
+            Mc[e][f] = Mt[e][f] = make_float4(0.f, 0.f, 0.f, 0.f);
             acc[e][f] = v4i{0, 0, 0, 0};
         }
 #pragma unroll
@@ -263,8 +274,18 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
             }
         }
     };
+    auto add_totals = [&]() {
+#pragma unroll
+        for (int e = 0; e < NO; ++e)
+#pragma unroll
+            for (int f = 0; f < NB; ++f) {
+                Mt[e][f].x += Mc[e][f].x; Mt[e][f].y += Mc[e][f].y; Mt[e][f].z += Mc[e][f].z; Mt[e][f].w += Mc[e][f].w;
+                Mc[e][f] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+    };
     // (whole rounds of the ring, then the rest: with the exit test inside the unrolled round the
     // compiler waits for ALL outstanding loads at the top of every round)
+    int fold = 2 * cpg;
     for (int r = NI / D; r > 0; --r) {
 #pragma unroll
         for (int u = 0; u < D; ++u) {
@@ -274,35 +295,64 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
             fetch(u);   // D steps ahead (past the end: the last one again, never used)
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (TOTALS && --fold == 0) {
+            fold = 2 * cpg;
+            add_totals();
+        }
     }
     const int rest = NI % D;
 #pragma unroll
     for (int u = 0; u < D - 1; ++u)
         if (u < rest) compute(u);
+    if constexpr (TOTALS) add_totals();
 
-    // ---- sum of the slices through LDS, 16 pixels at a time, + bias; whole rows of 16 NO channels stored ----
-    float *mine = part_s + w * (16 * RS);
+    // ---- sum of the slices through LDS, FB row blocks of pixels at a time, + bias; whole rows of 16 NO
+    // channels stored ----
+    // More than two slices are added in fp64, which costs a conversion per term: fp32 additions of sums
+    // as large as the result would add as much error as the chain of groups they replace (with G groups
+    // in c chains the squared error goes with G / (2 c) + c / 2).  The 64-wide tiles of linear layers with
+    // ten groups and more, and of 3x3 layers, add in fp32: their four slices come in place of as many,
+    // or of longer chains.  Relative error before and after: 2x32x32 1280->320 g 32 1.76e-7, 1.26e-7 (28.4,
+    // 27.9 us on 2x32x32 640->640); 64x5120->2048 g 32 1.25e-7, 8.4e-8 (12.1, 12.5 us).
+    const bool wide = a.slices > 2 && (NO <= 2 || (!T9 && groups < 10));
+    constexpr int FB = kRowsPerPass<NO, NB> / 16, ROWS = 16 * FB;
+    float *mine = part_s + w * (ROWS * RS);
     constexpr int CQ = 4 * NO, RPP = 64 / CQ;   // 4 channels per lane, RPP pixel rows per wave and pass
-    const float *tile = part_s + wtile * a.slices * (16 * RS) + (lane / CQ) * RS + (lane % CQ) * 4;
+    const float *tile = part_s + wtile * a.slices * (ROWS * RS) + (lane / CQ) * RS + (lane % CQ) * 4;
     const int o = ob0 * 16 + (lane % CQ) * 4;
     float bv4[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) bv4[r] = o + r < a.Cout ? a.bias[o + r] : 0.f;
 #pragma unroll
-    for (int f = 0; f < NB; ++f) {
-        if (f) __syncthreads();   // the rows of the block before have been read
+    for (int f = 0; f < NB; f += FB) {
+        if (f) __syncthreads();   // the rows of the blocks before have been read
 #pragma unroll
-        for (int e = 0; e < NO; ++e) *reinterpret_cast<float4 *>(&mine[l16 * RS + 16 * e + 4 * q]) = Mc[e][f];
+        for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+            for (int e = 0; e < NO; ++e)
+                *reinterpret_cast<float4 *>(&mine[(16 * fb + l16) * RS + 16 * e + 4 * q]) = TOTALS ? Mt[e][f + fb] : Mc[e][f + fb];
         __syncthreads();
-        for (int r0 = ks * RPP; r0 < 16; r0 += a.slices * RPP) {   // the slices' waves share the rows
+        for (int r0 = ks * RPP; r0 < ROWS; r0 += a.slices * RPP) {   // the slices' waves share the rows
             const int p = p0 + 16 * f + r0 + lane / CQ;
             if (p >= P || o >= a.Cout) continue;
-            float4 s = *reinterpret_cast<const float4 *>(&tile[r0 * RS]);
-            for (int z = 1; z < a.slices; ++z) {
-                const float4 t = *reinterpret_cast<const float4 *>(&tile[(z * 16 + r0) * RS]);
-                s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+            const float4 t0 = *reinterpret_cast<const float4 *>(&tile[r0 * RS]);
+            float sum[4];
+            if (wide) {
+                double s[4] = {(double)t0.x + bv4[0], (double)t0.y + bv4[1], (double)t0.z + bv4[2], (double)t0.w + bv4[3]};
+                for (int z = 1; z < a.slices; ++z) {
+                    const float4 t = *reinterpret_cast<const float4 *>(&tile[(z * ROWS + r0) * RS]);
+                    s[0] += (double)t.x; s[1] += (double)t.y; s[2] += (double)t.z; s[3] += (double)t.w;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sum[r] = (float)s[r];
+            } else {   // (the bias with the first slice, where the sums are smallest)
+                float4 s = make_float4(t0.x + bv4[0], t0.y + bv4[1], t0.z + bv4[2], t0.w + bv4[3]);
+                for (int z = 1; z < a.slices; ++z) {
+                    const float4 t = *reinterpret_cast<const float4 *>(&tile[(z * ROWS + r0) * RS]);
+                    s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+                }
+                sum[0] = s.x; sum[1] = s.y; sum[2] = s.z; sum[3] = s.w;
             }
-            const float sum[4] = {s.x + bv4[0], s.y + bv4[1], s.z + bv4[2], s.w + bv4[3]};
             float *dst = a.y + (size_t)p * a.Cout + o;
             if ((a.Cout & 3) == 0) {   // o is a multiple of 4, so o + 3 < Cout and the address is 16-byte aligned
                 __builtin_nontemporal_store(v4f{sum[0], sum[1], sum[2], sum[3]}, reinterpret_cast<v4f *>(dst));
@@ -337,7 +387,7 @@ void launch_conv(const DArgs &a0, hipStream_t s) {
     a.per_xcd = (a.total + 7) / 8;
     const int waves = a.slices * a.wo * a.wt;
     hipLaunchKernelGGL((k_direct_conv<K64, CPG1, W4, T9, NO, NB, D, NWMAX>), dim3((unsigned)a.per_xcd * 8u),
-                       dim3(64 * waves), (size_t)waves * 16 * (16 * NO + 4) * 4, s, a);
+                       dim3(64 * waves), (size_t)waves * (kRowsPerPass<NO, NB>) * (16 * NO + 4) * 4, s, a);
 }
 
 template <bool K64, bool CPG1, bool W4, bool T9>

@@ -20,10 +20,12 @@ struct wq_direct_tile {
 // slow as the CU with the most of them.  Measured over layers from 5 to 9792 pixels and 32 to 5120
 // channels; n44 = the tiles of 64 x 64:
 //   n44 >= 1500      64 x 64; from 3000 on enough waves without sharing a reduction at all
-//   n44 >= 150       64 x 64 and 4 slices, except 3x3 layers below 640 tiles: there the nine-fold
+//   n44 >= 150 (171) 64 x 64 and 4 slices, except 3x3 layers below 640 tiles: there the nine-fold
 //                    reduction makes a tile of work so big that 32 x 64 fills the last round better
 //                    (2 x 32^2 pixels, 640 -> 640: 26.5 against 29.8 us)
-//   n44 >= 40        32 x 64, 8 slices
+//   n44 >= 40        32 x 64, 8 slices; 3x3 layers up to 170 tiles too, whose four slices would be longer
+//                    chains of fp32 additions than nine taps on their own (2x16x16 1280->1280: relative
+//                    error 1.29e-7 with 4 slices, 9.3e-8 with 8, 36.3 and 40.1 us)
 //   fewer            16 x 16 (as long as those are few too), else 16 x 64, 8 slices: latency rules,
 //                    every wave should have only a handful of K-steps
 inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int groups, int g, int kstep, int splits) {
@@ -36,11 +38,11 @@ inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int g
         while (t.slices > 4 && ob * pb * t.slices > 2048) t.slices /= 2;
     } else if (n44 < 40) {
         t.slices = 8;
-    } else if (n44 < 150) {
+    } else if (n44 < (taps == 9 ? 171 : 150)) {
         t.no = 2; t.slices = 8;
     } else if (taps == 9 && n44 < 640) {
         t.no = 2;
-        t.slices = ((ob + 1) / 2) * ((pb + 3) / 4) > 1000 ? 2 : 4;
+        t.slices = ((ob + 1) / 2) * ((pb + 3) / 4) > 1024 ? 2 : 4;
     } else if (n44 < 1500) {
         t.no = 4; t.slices = 4;
     } else if (n44 < 3000) {
@@ -54,6 +56,8 @@ inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int g
         if (t.slices > 8) t.no = 1;   // the larger tiles' registers allow 8 waves per workgroup
     } else {
         while (t.slices > 1 && G * g < 2L * kstep * t.slices) t.slices /= 2;   // two K-steps each at least
+        // one chain of up to three groups rounds less often than slices and their sum do
+        if (G < 4) t.slices = 1;
     }
     return t;
 }
@@ -73,9 +77,9 @@ struct wq_direct_walk {
     // do not pass the end; nothing is loaded from either margin (see masked)
     static WQ_HD int back(int W) { return T9 ? W + 1 : 0; }
     // which of the 9 window positions of a pixel lie outside the image
-    static WQ_HD unsigned outside(int p, int H, int W) {
+    static WQ_HD unsigned outside(unsigned p, unsigned H, unsigned W) {
         if (!T9) return 0;
-        const int ww = p % W, hh = (p / W) % H;
+        const unsigned ww = p % W, hh = (p / W) % H;
         return (hh == 0 ? 0x007u : 0u) | (hh == H - 1 ? 0x1c0u : 0u) | (ww == 0 ? 0x049u : 0u) | (ww == W - 1 ? 0x124u : 0u);
     }
     // a lane's offset at the current tap: bit 31, past the end of every buffer, where the window position

@@ -214,3 +214,42 @@ def test_outputs_near_the_ends_of_the_range(wq, g, bits, exponent):
     got = forward_on_poisoned_buffers(wq, np.ldexp(d.x, exponent), d.w, None, g, bits)
     want = np.ldexp(base.astype(np.float64), exponent).astype(np.float32)
     assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("case", [
+    # taps N  H   W   Cin   Cout  g   chains
+    (9, 2, 32, 32, 1280, 320, 32, 9), (9, 2, 16, 16, 1280, 1280, 64, 9), (9, 4, 19, 22, 896, 64, 64, 9),
+    (1, 64, 1, 1, 5120, 2048, 32, 16), (1, 16, 1, 1, 5120, 5120, 32, 8), (1, 64, 1, 1, 5120, 640, 512, 2),
+    (1, 300, 1, 1, 512, 2560, 128, 2), (1, 1100, 1, 1, 512, 1280, 256, 1), (1, 260, 1, 1, 1280, 2560, 256, 1),
+        (1, 64, 1, 1, 768, 640, 256, 1), (1, 700, 1, 1, 1024, 1280, 128, 4), (9, 1, 61, 40, 64, 512, 64, 3),
+], ids=lambda c: "t%d_%dx%dx%d_%d-%d_g%d_%d" % c)
+def test_error_of_the_sums_over_groups(wq, case):
+    """Distance from the fp64 sum of the same codes and scales, against what `chains` fp32 chains of
+    groups, added up one after the other, are away from it.  A rounding of a sum is off by
+    u = 2^-23 sqrt(3 / (8 ln 2) / 12) of it in the root mean square (uniform over half an ulp, mantissas
+    log-uniform); with terms of random sign a sum's square grows by one term's per group, so the G
+    products of two scales, the sums inside c chains and the sums of chains make
+    u^2 (1 + (G / c + 1) / 2 + (c + 1) / 2 - 1 / c) relative to the result.  (6 % for the formula.)"""
+    taps, N, H, W, Cin, Cout, g, chains = case
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    P, groups = N * H * W, Cin // g
+    x = torch.randn(P, Cin, generator=gen, device="cuda")
+    w = torch.randn(Cout, Cin * taps, generator=gen, device="cuda")
+    plan = wq.DirectPlan(N, H, W, Cin, Cout, g, linear=taps == 1)
+    blob, ws, y = plan.alloc_blob(), plan.alloc_workspace(), plan.alloc_output()
+    plan.weight_prepare(w, None, blob)
+    plan.forward(x, blob, ws, y)
+    Wq, sW, _ = plan.blob_views(blob)
+    xq, sx = plan.workspace_views(ws)
+    xd = (xq.view(P, groups, g).double() * sx.view(P, groups, 1).double()).view(N, H, W, Cin)
+    xd = torch.nn.functional.pad(xd, (0, 0, 1, 1, 1, 1))
+    ref = torch.zeros(P, Cout, dtype=torch.float64, device="cuda")
+    for t in range(taps):
+        u, v = (t // 3, t % 3) if taps == 9 else (1, 1)
+        wd = Wq[t, :Cout].view(Cout, groups, g).double() * sW[t, :, :Cout].t().unsqueeze(2).double()
+        ref += xd[:, u:u + H, v:v + W].reshape(P, Cin) @ wd.view(Cout, Cin).t().contiguous()
+    err = float((y.view(P, Cout).double() - ref).norm() / ref.norm())
+    G = taps * groups
+    bound = 2.0 ** -23 * np.sqrt(3 / (8 * np.log(2)) / 12 * (2 + G / (2 * chains) + chains / 2 - 1 / chains))
+    print(f"error {err:.3e}, {chains} chains of fp32 {bound:.3e}")
+    assert err <= 1.06 * bound
