@@ -295,11 +295,11 @@ typedef struct wq_direct_plan wq_direct_plan_t;
 
 typedef struct {
     int32_t N, H, W, Cin, Cout, group_size, groups, P, Cout_pad, kstep;
-    int32_t splits, taps; /* splits: 1 = the plan's own choice of how many waves share the reduction of
-                             an output tile, else the number wq_direct_plan_tune asked for;
+    int32_t splits, taps; /* splits: how many waves wq_direct_plan_tune asked to share the reduction of an
+                             output tile, 1 in a plan that was not tuned (what runs is in `launch`);
                              taps: 9 for the 3x3 convolution, 1 for a linear layer */
     int32_t weight_bits;  /* 8, or 4 (W4A8) */
-    int32_t reserved;     /* 0 */
+    int32_t launch;       /* what runs: channels << 16 | pixels << 8 of a wave's output tile | waves that share it */
     uint64_t blob_bytes, blob_Wq_off, blob_sW_off, blob_bias_off;
     uint64_t ws_bytes, ws_xq_off, ws_sx_off, ws_part_off;   /* ws_part_off: the end of sx (nothing lies behind it) */
 } wq_direct_layout_t;
@@ -327,9 +327,8 @@ wq_status_t wq_direct_plan_create_bits(wq_direct_plan_t **out, int N, int H, int
 wq_status_t wq_linear_plan_create_bits(wq_direct_plan_t **out, int R, int Cin, int Cout, int group_size,
                                        int weight_bits);
 /* Tuning override for tests and sweeps: the number of waves that share the reduction of an output
- * tile (wq_direct_layout_t::splits).  0 keeps the plan as it is, 1 is the plan's own choice; a 3x3
- * plan takes 1, 3 or 9, a linear plan a power of two up to 16 that divides its group count; anything
- * else -> UNSUPPORTED. */
+ * tile (wq_direct_layout_t::splits).  0 keeps the plan as it is; a 3x3 plan takes 1, 3 or 9, a linear
+ * plan a power of two up to 16 that divides its group count; anything else -> UNSUPPORTED. */
 wq_status_t wq_direct_plan_tune(wq_direct_plan_t *plan, int splits);
 wq_status_t wq_direct_plan_destroy(wq_direct_plan_t *plan);
 wq_status_t wq_direct_plan_layout(const wq_direct_plan_t *plan, wq_direct_layout_t *out);

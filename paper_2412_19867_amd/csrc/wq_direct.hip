@@ -25,7 +25,7 @@ struct wq_direct_plan {
     int taps;     // 9 = 3x3 convolution, 1 = linear layer (every row is its own "image")
     int wbits;    // width of the weight codes: 8, or 4 (W4A8: two codes per byte)
     wq_direct_tile tile;   // the kernel instance and its launch shape
-    int splits;   // 1, or the number of slices wq_direct_plan_tune asked for
+    int splits;   // the number of slices wq_direct_plan_tune asked for, 0 = the plan's own choice
     wq_direct_layout_t lay;
     std::atomic<int> prepared;
 };
@@ -375,6 +375,8 @@ uint64_t align256(uint64_t v) { return (v + 255) / 256 * 256; }
 
 void choose_tile(wq_direct_plan *p) {
     p->tile = wq_direct_choose_tile(p->P, p->Cout_pad, p->taps, p->groups, p->g, p->kstep, p->splits);
+    p->lay.splits = p->splits ? p->splits : 1;
+    p->lay.launch = (16 * p->tile.no) << 16 | (16 * p->tile.nb) << 8 | p->tile.slices;
 }
 
 template <bool K64, bool CPG1, bool W4, bool T9, int NO, int NB, int D, int NWMAX>
@@ -446,16 +448,14 @@ static wq_status_t make_plan(wq_direct_plan_t **out, int N, int H, int W, int Ci
     L.groups = p->groups; L.P = p->P; L.Cout_pad = p->Cout_pad; L.kstep = p->kstep;
     L.taps = taps;
     L.weight_bits = weight_bits;
-    L.reserved = 0;
     L.blob_Wq_off = 0;
     L.blob_sW_off = align256(((uint64_t)taps * p->Cout_pad * Cin * weight_bits) / 8);
     L.blob_bias_off = L.blob_sW_off + align256((uint64_t)taps * p->groups * p->Cout_pad * 4);
     L.blob_bytes = L.blob_bias_off + align256((uint64_t)p->Cout_pad * 4);
     L.ws_xq_off = 0;
     L.ws_sx_off = align256((uint64_t)P * Cin);
-    p->splits = 1;
+    p->splits = 0;
     choose_tile(p);
-    L.splits = p->splits;
     L.ws_part_off = L.ws_sx_off + align256((uint64_t)P * p->groups * 4);
     L.ws_bytes = L.ws_part_off;
     p->prepared.store(0);
@@ -491,7 +491,6 @@ wq_status_t wq_direct_plan_tune(wq_direct_plan_t *plan, int splits) {
     if (!ok) return WQ_ERR_UNSUPPORTED;
     plan->splits = splits;
     choose_tile(plan);
-    plan->lay.splits = splits;
     return WQ_OK;
 }
 

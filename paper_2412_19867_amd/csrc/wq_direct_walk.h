@@ -28,6 +28,7 @@ struct wq_direct_tile {
 //                    error 1.29e-7 with 4 slices, 9.3e-8 with 8, 36.3 and 40.1 us)
 //   fewer            16 x 16 (as long as those are few too), else 16 x 64, 8 slices: latency rules,
 //                    every wave should have only a handful of K-steps
+// `splits`: the slices asked for by a caller, 0 for the choice above.
 inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int groups, int g, int kstep, int splits) {
     const long ob = Cout_pad / 16, pb = (P + 15) / 16, G = (long)taps * groups;
     const long n44 = ((ob + 3) / 4) * ((pb + 3) / 4);
@@ -50,7 +51,7 @@ inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int g
     } else {
         t.no = 4; t.wo = t.wt = 2;
     }
-    if (splits > 1) {
+    if (splits > 0) {
         t.slices = splits;
         t.wo = t.wt = 1;
         if (t.slices > 8) t.no = 1;   // the larger tiles' registers allow 8 waves per workgroup

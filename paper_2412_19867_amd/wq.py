@@ -44,7 +44,7 @@ class Layout(ctypes.Structure):
 class DirectLayout(ctypes.Structure):
     _fields_ = ([(k, ctypes.c_int32) for k in
                  ("N", "H", "W", "Cin", "Cout", "group_size", "groups", "P", "Cout_pad", "kstep",
-                  "splits", "taps", "weight_bits", "reserved")] +
+                  "splits", "taps", "weight_bits", "launch")] +
                 [(k, ctypes.c_uint64) for k in
                  ("blob_bytes", "blob_Wq_off", "blob_sW_off", "blob_bias_off",
                   "ws_bytes", "ws_xq_off", "ws_sx_off", "ws_part_off")])
@@ -401,10 +401,16 @@ class DirectPlan:
         _check(lib().wq_direct_plan_layout(self._h, ctypes.byref(self.layout)), "wq_direct_plan_layout")
 
     def tune(self, splits: int):
-        """Override how many workgroups share an output tile's reduction (wq_direct_plan_tune)."""
+        """Override how many waves share an output tile's reduction (wq_direct_plan_tune)."""
         _check(lib().wq_direct_plan_tune(self._h, int(splits)), "wq_direct_plan_tune")
         _check(lib().wq_direct_plan_layout(self._h, ctypes.byref(self.layout)), "wq_direct_plan_layout")
         return self
+
+    @property
+    def launch(self):
+        """(channels, pixels, waves): a wave's output tile and how many waves share its reduction"""
+        v = self.layout.launch
+        return v >> 16, (v >> 8) & 0xff, v & 0xff
 
     def __del__(self):
         h = getattr(self, "_h", None)

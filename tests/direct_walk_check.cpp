@@ -81,7 +81,7 @@ static void shapes(int g) {
             for (auto &p : pixels) {
                 const int P = p[0], H = p[1], W = p[2], Cin = n * g;
                 for (int taps = 1; taps <= 9; taps += 8) {
-                    wq_direct_tile own = wq_direct_choose_tile(P, c, taps, n, g, KSTEP, 1);
+                    wq_direct_tile own = wq_direct_choose_tile(P, c, taps, n, g, KSTEP, 0);
                     for (int k = -1; k < 4 * 7 * 2; ++k) {
                         wq_direct_tile t = own;
                         if (k >= 0) {

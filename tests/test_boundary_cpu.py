@@ -309,3 +309,15 @@ def test_integer_transform_mode_is_host_state_only(wq):
         assert (p.layout.ws_bytes, p.layout.blob_bytes) == before[2:]
     p.set_integer_transforms(0)
     assert (p.layout.k2_variant, p.layout.k1_rows, p.layout.ws_bytes, p.layout.blob_bytes) == before
+
+
+def test_a_tuned_direct_plan_runs_the_waves_it_was_asked_for(wq):
+    """wq_direct_plan_tune and what the layout reports, one wave per tile among them."""
+    own = wq.DirectPlan(2, 32, 32, 640, 640, 64)
+    assert own.layout.splits == 1 and own.launch == (32, 64, 4)
+    for s in (1, 3, 9):
+        assert own.tune(s).layout.splits == s and own.launch[2] == s
+        assert own.tune(0).launch[2] == s
+    for s in (1, 2, 4, 8, 16):
+        lin = wq.DirectPlan(4096, 1, 1, 1024, 640, 64, linear=True).tune(s)
+        assert lin.layout.splits == s and lin.launch[2] == s
