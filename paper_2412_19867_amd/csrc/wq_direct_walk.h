@@ -19,7 +19,8 @@ struct wq_direct_tile {
 // tile moves fewer operand bytes per product; but a CU takes only 8 waves of it, and a launch is as
 // slow as the CU with the most of them.  Measured over layers from 5 to 9792 pixels and 32 to 5120
 // channels; n44 = the tiles of 64 x 64:
-//   n44 >= 1500      64 x 64; from 3000 on enough waves without sharing a reduction at all
+//   n44 >= 1500      64 x 64; from 3000 on enough waves without sharing a reduction at all (four tiles in
+//                    a workgroup, so that its stores and loads stay together)
 //   n44 >= 150 (171) 64 x 64 and 4 slices, except 3x3 layers below 640 tiles: there the nine-fold
 //                    reduction makes a tile of work so big that 32 x 64 fills the last round better
 //                    (2 x 32^2 pixels, 640 -> 640: 26.5 against 29.8 us)
@@ -28,6 +29,10 @@ struct wq_direct_tile {
 //                    error 1.29e-7 with 4 slices, 9.3e-8 with 8, 36.3 and 40.1 us)
 //   fewer            16 x 16 (as long as those are few too), else 16 x 64, 8 slices: latency rules,
 //                    every wave should have only a handful of K-steps
+// No tile is wider than the layer's padded channels, and a workgroup's tiles lie along the pixels where
+// one covers all channels: a wave that has no channels of its own costs as much as one that has (us at
+// 64 x 64 tiles and 2 x 2 of them in a workgroup, and so: 640^2 pixels 128->24 183, 87; 448^2 64->64 59,
+// 41; 50000x640->16 38.6, 32.7).
 // `splits`: the slices asked for by a caller, 0 for the choice above.
 inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int groups, int g, int kstep, int splits) {
     const long ob = Cout_pad / 16, pb = (P + 15) / 16, G = (long)taps * groups;
@@ -50,6 +55,10 @@ inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int g
         t.no = 4; t.slices = 2; t.wt = 2;
     } else {
         t.no = 4; t.wo = t.wt = 2;
+    }
+    if (ob <= t.no / 2) t.no /= 2;   // (ob is even, and 2 or more)
+    if (t.wo == 2 && ob <= t.no) {
+        t.wo = 1; t.wt = 4;
     }
     if (splits > 0) {
         t.slices = splits;

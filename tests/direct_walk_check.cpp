@@ -2,6 +2,7 @@
 // and slice counts, and reports every access that leaves its buffer.  Exit status: 0 = none.
 #include <cstdio>
 #include <cstdlib>
+#include <initializer_list>
 
 #include "wq_direct_walk.h"
 
@@ -95,7 +96,21 @@ static void shapes(int g) {
             }
 }
 
+// a workgroup's tiles do not lie past the channels where the channels of one tile are all there are
+static void narrow() {
+    for (int P = 1; P < 500000; P += 1 + P / 7)
+        for (int c = 32; c <= 160; c += 32)
+            for (int groups : {1, 3, 9, 40})
+                for (int taps : {1, 9}) {
+                    const wq_direct_tile t = wq_direct_choose_tile(P, c, taps, groups, 64, 64, 0);
+                    ++checked;
+                    if (((t.no > 1 && t.no * 8 >= c) || (t.wo > 1 && t.no * 16 >= c)) && ++bad <= 20)
+                        printf("P %d outputs %d: tile of %d blocks, %d in a workgroup\n", P, c, t.no, t.wo);
+                }
+}
+
 int main() {
+    narrow();
     shapes<32>(32);
     shapes<64>(64);
     shapes<64>(128);

@@ -321,3 +321,14 @@ def test_a_tuned_direct_plan_runs_the_waves_it_was_asked_for(wq):
     for s in (1, 2, 4, 8, 16):
         lin = wq.DirectPlan(4096, 1, 1, 1024, 640, 64, linear=True).tune(s)
         assert lin.layout.splits == s and lin.launch[2] == s
+
+
+@pytest.mark.parametrize("taps", [1, 9])
+@pytest.mark.parametrize("Cout", [1, 32, 33, 64, 65])
+def test_a_wave_tile_is_no_wider_than_the_padded_outputs(wq, taps, Cout):
+    """Over pixel counts that reach every tile of the choice: no 16-channel block of a wave's tile is past
+    the padded channels where half the tile would have covered them."""
+    for P in (5, 40, 700, 3000, 9000, 20000, 45000, 70000, 130000, 300000):
+        for g, groups in ((32, 3), (64, 9), (256, 2)):
+            plan = wq.DirectPlan(P, 1, 1, g * groups, Cout, g, linear=taps == 1)
+            assert plan.launch[0] < 2 * plan.layout.Cout_pad

@@ -122,7 +122,8 @@ def test_direct_largest_pixel_count(wq):
 @pytest.mark.parametrize("case", [
     # P    Cin  Cout  g   (linear: every launch shape of the tile choice, with ragged pixels and channels)
     (16, 64, 33, 32), (17, 128, 16, 64), (257, 192, 260, 64), (400, 128, 1000, 32), (700, 256, 500, 128),
-    (1601, 64, 2050, 64), (3300, 64, 2100, 32), (12500, 32, 1030, 32),
+    (1601, 64, 2050, 64), (3300, 64, 2100, 32), (12500, 32, 1030, 32), (192003, 32, 16, 32), (192003, 32, 50, 32),
+    (100009, 64, 30, 32), (50003, 128, 32, 32),
 ], ids=lambda c: "p%d_%d-%d_g%d" % c)
 def test_every_tile_choice_of_the_quantized_gemm(wq, case):
     """Rows and channels that end inside a tile, for every wave tile and slice count the plan picks
