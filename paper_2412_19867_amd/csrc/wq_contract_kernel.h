@@ -21,14 +21,17 @@
 // NHWC with the ragged right/bottom edge masked.
 //
 // A wave waits for nothing but its own loads, so what counts is that the compiler can count them:
-// the request of the K-step D ahead is unconditional (the cursor stops at the last one), whole
-// rounds of the ring make up a wave's walk, and it is placed between the MFMAs and the
-// dequantization, which covers their latency.  Scales cost one word per lane and load (a v4 load of
+// the request of the K-step D ahead is unconditional, whole rounds of the ring make up a wave's walk,
+// and it is placed between the MFMAs and the dequantization, which covers their latency.  The last
+// round is written out without requests: a walk has only (m + 2) Cin / K-step of them, so requests
+// past its end cost up to a half more (whole forward with and without: 29x43x43 64->992 F(2,3), one
+// round, 201, 130 us; 8x78x78 192->512 F(2,3) 168, 135; 1x32x32 64->64 F(4,3) 11.1, 10.1; 32x56x56
+// 64->64 F(6,3) 33.0, 32.1).  Scales cost one word per lane and load (a v4 load of
 // the four channel scales moves four times the bytes through the load path) and reach the lanes by
 // DPP quad broadcasts and a row swap; groups of one K-step start their sums at kMagic.  Measured
 // against conditional requests, v4 scales and conversions: 32x28^2 128->128 F(6,3) 26.1 -> 24.6 us,
 // 8x100x128 192->64 F(4,3) g 32 69.8 -> 61.4 us, 2x64x64 320->320 F(4,3) at one block per wave
-// 32.3 -> 26.5 us (whole forward).
+// 32.3 -> 26.5 us (whole forward; 25.1 without the requests past the end).
 //
 // Workgroups are numbered so that the eight XCDs (which receive consecutive
 // workgroup ids round-robin and have private L2s) each own a slice of the
@@ -36,6 +39,8 @@
 // channels (weights stay in its L2), with xcd_mode 1 every 8th block of tiles,
 // with xcd_mode 2 every 4th block of tiles and one half of the channels.
 #pragma once
+
+#include <type_traits>
 
 #include "wq_device.h"
 #include "wq_internal.h"
@@ -140,7 +145,7 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
     const unsigned dW = planeW - (unsigned)cps * stepOp, dX = planeX - (unsigned)cps * stepOp;
     const unsigned dSW = planeSW - (unsigned)gps * stepSW, dSX = planeSX - (unsigned)gps * 64u;
     const int NI = n * cps;                      // the wave's K-steps, a multiple of D
-    int k_ld = 0, kg_ld = 0, left_ld = NI;
+    int k_ld = 0, kg_ld = 0;
 
     auto load_stage = [&](Stage<K64, NT, NO> &s) {
 #pragma unroll
@@ -165,15 +170,13 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
         for (int no = 0; no < NO; ++no)
             s.sw[no] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSW, vSW, oSW + 64u * no, 0));
         s.sx = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX, oSX, 0));
-        // branch-free scalar bookkeeping; the cursor stops at the last K-step, which the last D
-        // requests repeat
-        const bool go = --left_ld > 0;
-        k_ld += go ? 1 : 0;
-        kg_ld += go ? 1 : 0;
-        const bool next_group = go && (CPG1 || (kg_ld & cpg_mask) == 0), next_tap = go && k_ld == cps;
+        // branch-free scalar bookkeeping
+        ++k_ld;
+        ++kg_ld;
+        const bool next_group = CPG1 || (kg_ld & cpg_mask) == 0, next_tap = k_ld == cps;
         k_ld = next_tap ? 0 : k_ld;
-        oW += (go ? stepOp : 0u) + (next_tap ? dW : 0u);
-        oX += (go ? stepOp : 0u) + (next_tap ? dX : 0u);
+        oW += stepOp + (next_tap ? dW : 0u);
+        oX += stepOp + (next_tap ? dX : 0u);
         oSW += (next_group ? stepSW : 0u) + (next_tap ? dSW : 0u);
         oSX += (next_group ? 64u : 0u) + (next_tap ? dSX : 0u);
     };
@@ -212,9 +215,9 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
     for (int b = 0; b < M; ++b) atc[b] = a.xf.AT[b * n];   // column of tap j = 0
 
     const v4i magic = {kMagic, kMagic, kMagic, kMagic};
-    // (no exit test and no conditional request inside a round: with either of them the compiler
-    // cannot count the loads in flight and waits for all of them at the top of every round)
-    for (int it = 0; it < NI; it += D) {
+    // (no exit test and no run-time condition on a request inside a round: with either of them the
+    // compiler cannot count the loads in flight and waits for all of them at the top of every round)
+    auto round = [&](auto last) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             Stage<K64, NT, NO> &s = st[d];
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
-            load_stage(s);   // D steps ahead
+            if constexpr (!last.value) load_stage(s);   // D steps ahead
             __builtin_amdgcn_sched_barrier(0);
             if (group_end) {
 #pragma unroll
@@ -317,7 +320,9 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
                 for (int b = 0; b < M; ++b) atc[b] = a.xf.AT[b * n + jn];
             }
         }
-    }
+    };
+    for (int it = NI - D; it > 0; it -= D) round(std::false_type{});
+    round(std::true_type{});
 
     // Every thread finishes the same (tile, channel) position of each sub-block: where
     // that tile's outputs start, how much of it lies inside the image, and the bias.
