@@ -232,10 +232,13 @@ int default_k2_variant(const wq_plan *p) {
     // a single group per tap leaves a bigger tile nothing to reuse (12x80x90 64->416 F(6,3): one block
     // 73, two 87, four 83)
     if (p->groups == 1) return WQ_K2_FUSED_16x16;
-    // fewer blocks than CUs: more and shorter waves (2x97x67 256->64: split 20.3, one block 22.6, two
-    // 26.4; 3x20x20 384->480: split 15.5, one block 16.7)
+    // fewer blocks than CUs: more and shorter waves, split in two where a wave still reduces three groups,
+    // up to five (2x97x67 256->64: one block 18.1, two 23; 3x20x20 384->480: split 15.7, one 16.7).
+    // Longer slices are longer chains of fp32 additions than the one wave's fp64 totals of four
+    // (relative error of 1x93x101 896->33: split 6.7e-7, one wave 6.4e-7; 33.2 and 35.1 us; of
+    // 3x60x82 640->64, slices of five: 6.2e-7, 6.3e-7; 30.0 and 31.7 us)
     if (tb * ob < 256 && p->m == 4)
-        return (can_split && p->groups >= 6) ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
+        return (can_split && p->groups >= 6 && p->groups <= 10) ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
     // one block each where those workgroups just fit the GPU at once, three on a CU, while pairs
     // would be one CU's worth and a few (3x45x61 192->200: 19.7 against 20.7; 2x64x64 320->320: 26.5
     // against 27.4)

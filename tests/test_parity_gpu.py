@@ -399,3 +399,40 @@ def test_adversarially_rounded_column_scales_take_the_dense_output_transform(wq)
     for key in ("y", "y_split"):
         err = np.abs(got[key].astype(np.float64) - ref["y64"]).max()
         assert err <= Y_TOL * scale, (key, err / scale)
+
+
+@pytest.mark.parametrize("case", [
+    # N H  W    Cin Cout m g    (few workgroups: 14, 12, 10, 8 and 6 groups a tap)
+    (1, 93, 101, 896, 33, 4, 64), (27, 18, 18, 448, 32, 4, 32), (18, 31, 31, 768, 32, 4, 64), (3, 60, 82, 640, 64, 4, 64),
+    (3, 31, 93, 512, 57, 4, 64), (8, 25, 27, 384, 93, 4, 64),
+], ids=lambda c: "%dx%dx%d_%d-%d_F%d_g%d" % c)
+def test_a_split_the_plan_picks_is_as_precise_as_one_wave(wq, case):
+    """Distance from the fp64 result of the same codes and scales: the plan's own choice against one wave
+    per tap row.  (2 %: the root mean square of N independent errors is known to 1 / sqrt(2 N), with
+    N > 30000 outputs to 0.4 %.)"""
+    N, H, W, Cin, Cout, m, g = case
+    gen = torch.Generator(device="cuda").manual_seed(Cin + Cout)
+    x = torch.randn(N, H, W, Cin, generator=gen, device="cuda")
+    w = torch.randn(Cout, Cin, 3, 3, generator=gen, device="cuda") * 0.02
+    AT = torch.from_numpy(np.array(ct.standard_matrices(m)[0], np.float64)).cuda()
+    ref, errors = None, {}
+    for variant in ("auto", "fused_16x16"):
+        plan = wq.Plan(N, H, W, Cin, Cout, m, g).tune(0, variant)
+        L, n = plan.layout, m + 2
+        blob, ws, y = plan.alloc_blob(), plan.alloc_workspace(), plan.alloc_output()
+        plan.weight_prepare(w, None, blob)
+        plan.forward(x, blob, ws, y)
+        if ref is None:
+            Wq, sW, _ = plan.blob_views(blob)
+            Xq, sX = plan.workspace_views(ws)
+            M = torch.empty(n, n, L.T, Cout, dtype=torch.float64, device="cuda")
+            for t in range(n * n):
+                xd = Xq[t, :L.T].view(L.T, L.groups, g).double() * sX[t, :L.T].view(L.T, L.groups, 1).double()
+                wd = Wq[t, :Cout].view(Cout, L.groups, g).double() * sW[t, :, :Cout].t().unsqueeze(2).double()
+                M[t // n, t % n] = xd.view(L.T, Cin) @ wd.view(Cout, Cin).t().contiguous()
+            rows = (AT @ M.view(n, -1)).view(m, n, L.T * Cout)
+            ref = torch.stack([AT @ rows[a] for a in range(m)]).view(m, m, N, L.TH, L.TW, Cout)
+            ref = ref.permute(2, 3, 0, 4, 1, 5).reshape(N, L.TH * m, L.TW * m, Cout)[:, :H, :W]
+        errors[variant] = float((y.double() - ref).norm() / ref.norm())
+    print(case, errors)
+    assert errors["auto"] <= 1.02 * errors["fused_16x16"]
