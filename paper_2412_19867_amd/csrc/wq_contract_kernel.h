@@ -392,14 +392,7 @@ hipError_t launch_cfg(const Args &a, hipStream_t s) {
     Args b = a;
     b.nTB = a.T_pad / (16 * NT);
     b.nOB = a.Cout_pad / (16 * NO);
-    // the XCDs partition the blocks of the larger operand
-    const long wbytes = (long)a.Cout_pad * a.Cin, xbytes = (long)a.T_pad * a.Cin;
-    b.xcd_mode = wbytes >= xbytes ? 0 : 1;
-    // tiles split over the XCDs, but all taps' weights would fill an XCD's 4 MB L2 on their own:
-    // split the channels in two as well, so that half of the weights stays resident next to the
-    // streaming activations
-    const long wall = wbytes * (M + 2) * (M + 2);
-    if (b.xcd_mode == 1 && wall > (5L << 19) && wall <= (8L << 20) && b.nOB >= 2) b.xcd_mode = 2;
+    b.xcd_mode = wq_fused_xcd_mode(a.T_pad, a.Cout_pad, a.Cin, M + 2, b.nOB);
     const int split = b.xcd_mode == 0 ? b.nOB : b.nTB, other = b.xcd_mode == 0 ? b.nTB : b.nOB;
     const unsigned grid = b.xcd_mode == 2 ? (unsigned)(((b.nTB + 3) / 4) * ((b.nOB + 1) / 2) * 8)
                                           : (unsigned)(((split + 7) / 8) * 8 * other);

@@ -196,13 +196,26 @@ int default_k2_variant(const wq_plan *p) {
     // operands too often.
     const bool two_kernel = (p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128))) ||
                             p->Cin >= 1024 || p->g >= 128;
-    // one group of 128 or more per tap: nothing is re-read between groups, and the product of a tap
+    // one group of 128 or 256 per tap: nothing is re-read between groups, and the product of a tap
     // written out costs more than the fused kernel's one block per wave (22x54x54 128->96 F(2,3) 48
     // against 69 us, 10x20x20 128->70 F(4,3) 12.5 against 13.9; F(6,3)'s 64 taps go either way; a
     // handful of blocks does not fill the GPU without the taps side by side: 29x39 128->39 11.6
-    // against 11.2)
-    if (p->g >= 128 && p->groups == 1 && p->m != 6 && (long)(p->T_pad / 16) * (p->Cout_pad / 16) >= 64)
-        return WQ_K2_FUSED_16x16;
+    // against 11.2).  The longer the group, the more a wave's walk of all its taps costs against the
+    // taps side by side: F(4,3) wants twice the blocks at 256 (26x8x8 256->108, 64 blocks, 16.2
+    // against 13.8; 1x16x16 256->560, 72, 14.1 against 13.3; 2x41x41 256->128, 128, 16.1 against
+    // 17.1) and what every XCD reads again in its L2 (4x52x52 256->928 68 against 62; 10x81x81
+    // 256->704 211 against 338), and at 512 loses at every size (11x11x11 512->128 22 against 17,
+    // 12x26x23 512->1046 118 against 69); F(2,3) at 512 loses only to the 128x128 tiles below
+    // (3x75x75 512->512 130 against 119; 9x73x73 512->230 227 against 263)
+    if (p->g >= 128 && p->groups == 1 && p->m != 6) {
+        const long blocks = (long)(p->T_pad / 16) * (p->Cout_pad / 16);
+        const bool in_l2 = wq_fused_xcd_mode(p->T_pad, p->Cout_pad, p->Cin, p->n, p->Cout_pad / 16) == 0
+                               ? (long)p->T_pad * p->Cin * p->n * p->n <= (4L << 20)
+                               : (long)p->Cout_pad * p->Cin * p->n * p->n <= (8L << 20);   // (half of them each)
+        if (p->m == 2 ? blocks >= 64 && (p->g <= 256 || p->T_pad < 1024 || p->Cout_pad < 256)
+                      : blocks >= p->g / 2 && (p->g == 128 || (p->g == 256 && in_l2)))
+            return WQ_K2_FUSED_16x16;
+    }
     if (two_kernel) {
         // 128x128 tiles: groups of 128 and more on layers with at least 1024 tiles and 256 channels
         if (p->g >= 128 && p->groups <= 8 && p->T_pad >= 1024 && p->Cout_pad >= 256)

@@ -103,6 +103,16 @@ inline bool wq_is_lds_variant(int v) {
     return wq_is_lds_full_variant(v) || wq_is_lds_row_variant(v) || wq_is_lds_tap_variant(v);
 }
 
+// How the fused kernel's workgroups are shared out to the eight XCDs: 0 = every 8th block of output
+// channels each, 1 = every 8th block of tiles (whichever operand is larger), 2 = every 4th block of tiles
+// and one half of the channels: where all taps' weights would fill an XCD's 4 MB L2 on their own, half of
+// them stays resident next to the streaming activations.  nOB: blocks of output channels.
+inline int wq_fused_xcd_mode(int T_pad, int Cout_pad, int Cin, int n, int nOB) {
+    const long wbytes = (long)Cout_pad * Cin, xbytes = (long)T_pad * Cin, wall = wbytes * n * n;
+    if (wbytes >= xbytes) return 0;
+    return wall > (5L << 19) && wall <= (8L << 20) && nOB >= 2 ? 2 : 1;
+}
+
 // Which part of the int32 group sums a debug call stores: taps [tap0, tap0+ntaps) x tiles
 // [tile0, tile0+ntiles), P [ntaps][ntiles][groups][Cout].  P == nullptr: no dump.
 struct wq_dump {

@@ -332,3 +332,22 @@ def test_a_wave_tile_is_no_wider_than_the_padded_outputs(wq, taps, Cout):
         for g, groups in ((32, 3), (64, 9), (256, 2)):
             plan = wq.DirectPlan(P, 1, 1, g * groups, Cout, g, linear=taps == 1)
             assert plan.launch[0] < 2 * plan.layout.Cout_pad
+
+
+@pytest.mark.parametrize("shape,fused", [
+    # N  H   W   Cin Cout m  g       the whole forward with one fused launch / with a product written out (us)
+    ((11, 11, 11, 512, 128, 4, 512), False),    # 22.3 / 16.8
+    ((12, 26, 23, 512, 1046, 4, 512), False),   # 118 / 69
+    ((3, 75, 75, 512, 512, 2, 512), False),     # 130 / 119
+    ((9, 73, 73, 512, 230, 2, 512), True),      # 227 / 263
+    ((26, 8, 8, 256, 108, 4, 256), False),      # 16.2 / 13.8
+    ((1, 16, 16, 256, 560, 4, 256), False),     # 14.1 / 13.1
+    ((2, 41, 41, 256, 128, 4, 256), True),      # 16.1 / 17.1
+    ((4, 52, 52, 256, 928, 4, 256), False),     # 68 / 62
+    ((10, 81, 81, 256, 704, 4, 256), True),     # 211 / 338
+    ((10, 20, 20, 128, 70, 4, 128), True),      # 12.5 / 13.9
+    ((22, 54, 54, 128, 96, 2, 128), True),      # 48 / 69
+], ids=lambda v: "%dx%dx%d_%d-%d_F%d_g%d" % v if isinstance(v, tuple) else "fused" if v else "product")
+def test_layers_with_one_long_group_take_the_faster_form(wq, shape, fused):
+    """A single group of 128 to 512 per tap: one fused launch only where its walk of all taps pays."""
+    assert wq.Plan(*shape).k2_variant_name.startswith("fused") == fused
