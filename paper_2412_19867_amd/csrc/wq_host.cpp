@@ -203,15 +203,15 @@ int default_k2_variant(const wq_plan *p) {
     // against 11.2).  The longer the group, the more a wave's walk of all its taps costs against the
     // taps side by side: F(4,3) wants twice the blocks at 256 (26x8x8 256->108, 64 blocks, 16.2
     // against 13.8; 1x16x16 256->560, 72, 14.1 against 13.3; 2x41x41 256->128, 128, 16.1 against
-    // 17.1) and what every XCD reads again in its L2 (4x52x52 256->928 68 against 62; 10x81x81
-    // 256->704 211 against 338), and at 512 loses at every size (11x11x11 512->128 22 against 17,
-    // 12x26x23 512->1046 118 against 69); F(2,3) at 512 loses only to the 128x128 tiles below, on more than 256 channels
+    // 17.1) and, where the XCDs share out the channels, what each of them reads over and over in its L2
+    // (2x55x55 256->812 42.8 against 40.5, 4x52x52 256->928 68 against 62; 1x78x76 256->512 25.6 against
+    // 31), and at 512 loses at every size (11x11x11 512->128 22 against 17, 12x26x23 512->1046 118
+    // against 69); F(2,3) at 512 loses only to the 128x128 tiles below, on more than 256 channels
     // (3x75x75 512->512 130 against 119; 9x73x73 512->230 227 against 263)
     if (p->g >= 128 && p->groups == 1 && p->m != 6) {
-        const long blocks = (long)(p->T_pad / 16) * (p->Cout_pad / 16);
-        const bool in_l2 = wq_fused_xcd_mode(p->T_pad, p->Cout_pad, p->Cin, p->n, p->Cout_pad / 16) == 0
-                               ? (long)p->T_pad * p->Cin * p->n * p->n <= (4L << 20)
-                               : (long)p->Cout_pad * p->Cin * p->n * p->n <= (8L << 20);   // (half of them each)
+        const long blocks = (long)(p->T_pad / 16) * (p->Cout_pad / 16), taps = p->n * p->n;
+        const bool in_l2 = wq_fused_xcd_mode(p->T_pad, p->Cout_pad, p->Cin, p->n, p->Cout_pad / 16) != 0 ||
+                           (p->T_pad + p->Cout_pad / 8) * taps * p->Cin <= (4L << 20);
         if (p->m == 2 ? blocks >= 64 && (p->g <= 256 || p->T_pad < 1024 || p->Cout_pad <= 256)
                       : blocks >= p->g / 2 && (p->g == 128 || (p->g == 256 && in_l2)))
             return WQ_K2_FUSED_16x16;

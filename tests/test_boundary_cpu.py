@@ -344,7 +344,10 @@ def test_a_wave_tile_is_no_wider_than_the_padded_outputs(wq, taps, Cout):
     ((1, 16, 16, 256, 560, 4, 256), False),     # 14.1 / 13.1
     ((2, 41, 41, 256, 128, 4, 256), True),      # 16.1 / 17.1
     ((4, 52, 52, 256, 928, 4, 256), False),     # 68 / 62
+    ((2, 55, 55, 256, 812, 4, 256), False),     # 42.8 / 40.5
+    ((1, 78, 76, 256, 512, 4, 256), True),      # 25.6 / 31.0
     ((10, 81, 81, 256, 704, 4, 256), True),     # 211 / 338
+    ((29, 34, 34, 256, 1088, 4, 256), True),    # 248 / 262
     ((10, 20, 20, 128, 70, 4, 128), True),      # 12.5 / 13.9
     ((22, 54, 54, 128, 96, 2, 128), True),      # 48 / 69
 ], ids=lambda v: "%dx%dx%d_%d-%d_F%d_g%d" % v if isinstance(v, tuple) else "fused" if v else "product")
