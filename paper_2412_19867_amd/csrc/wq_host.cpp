@@ -176,6 +176,17 @@ bool variant_applicable(const wq_plan *p, int v) {
     }
 }
 
+// workgroups of the fused kernel on the XCD that gets the most of them, with tiles of nt x no blocks of
+// 16 tiles x 16 channels (the order of launch_cfg)
+long fused_xcd_load(const wq_plan *p, int nt, int no) {
+    const int nTB = p->T_pad / (16 * nt), nOB = p->Cout_pad / (16 * no);
+    switch (wq_fused_xcd_mode(p->T_pad, p->Cout_pad, p->Cin, p->n, nOB)) {
+        case 0: return (long)((nOB + 7) / 8) * nTB;
+        case 1: return (long)((nTB + 7) / 8) * nOB;
+        default: return (long)((nTB + 3) / 4) * ((nOB + 1) / 2);
+    }
+}
+
 int default_k2_variant(const wq_plan *p) {
     if (p->integer_transforms) {
         if (p->T_pad <= 32 || ((p->T_pad % 64) == 32 && p->T_pad <= 160)) return WQ_K2_GEMM_32x128;
@@ -245,30 +256,44 @@ int default_k2_variant(const wq_plan *p) {
     // a single group per tap leaves a bigger tile nothing to reuse (12x80x90 64->416 F(6,3): one block
     // 73, two 87, four 83)
     if (p->groups == 1) return WQ_K2_FUSED_16x16;
-    // fewer blocks than CUs: more and shorter waves, split in two where a wave still reduces three groups,
-    // up to five (2x97x67 256->64: one block 18.1, two 23; 3x20x20 384->480: split 15.7, one 16.7).
-    // Longer slices are longer chains of fp32 additions than the one wave's fp64 totals of four
-    // (relative error of 1x93x101 896->33: split 6.7e-7, one wave 6.4e-7; 33.2 and 35.1 us; of
-    // 3x60x82 640->64, slices of five: 6.2e-7, 6.3e-7; 30.0 and 31.7 us)
-    if (tb * ob < 256 && p->m == 4)
-        return (can_split && p->groups >= 6 && p->groups <= 10) ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
-    // one block each where those workgroups just fit the GPU at once, three on a CU, while pairs
-    // would be one CU's worth and a few (3x45x61 192->200: 19.7 against 20.7; 2x64x64 320->320: 26.5
-    // against 27.4)
-    if (p->m == 4 && p->g == 64 && tb * ob >= 448 && tb * ob <= 704) return WQ_K2_FUSED_16x16;
+    // a launch is as slow as the XCD with the most of it (32 CUs): workgroups there, by tile
+    const long one = fused_xcd_load(p, 1, 1), two = fused_xcd_load(p, 2, 1), four = fused_xcd_load(p, 2, 2);
+    if (p->m == 4) {
+        // a block each where every workgroup gets a CU of its own: more and shorter waves (2x97x67 256->64:
+        // one block 18, two 23; 12x29x26 224->96, 36 on an XCD: 24.5, 21.7).  Split in two where a wave still
+        // reduces three groups, up to five (3x20x20 384->480: split 15.7, one block 16.7).  Longer slices are
+        // longer chains of fp32 additions than the one wave's fp64 totals of four (relative error of
+        // 1x93x101 896->33: split 6.8e-7, one wave 6.3e-7; 33.2 and 35.1 us; of 3x60x82 640->64, slices of
+        // five: 6.2e-7, 6.3e-7; 30.0 and 31.7 us)
+        if (one <= 32) return (can_split && p->groups >= 6 && p->groups <= 10) ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
+        // and where they fit the CUs at once, three on each, but pairs would not, one on each (one block,
+        // two: 1x70x48 128->576 15.9, 18.0; 4x40x52 256->256 22.0, 23.5; 1x54x67 96->608 17.9, 20.0; where
+        // pairs do: 3x70x86 320->96 25.1, 24.1; 25x31x21 640->71 43.5, 39.4; where blocks do not: 30x15x15
+        // 192->406 24.2, 23.4)
+        if (two > 32 && one <= 96) return WQ_K2_FUSED_16x16;
+    }
     if (tb * ob >= 600) {
-        // four blocks pay for their registers where a tap reduces four groups or more and their
-        // workgroups fill the CUs evenly, once or at least three times (3x89x89 320->256 F(6,3)
-        // 40.5 against 49.5; 18x59x59 512->320 164 against 189; 3x76x63 448->384, 348 workgroups,
-        // 56 against 52; with two groups 11x33x23 128->640 32.9 against 26.4), and on wide F(6,3)
-        // layers in any case (14x32x32 128->1074 97 against 101)
+        // four blocks pay for their registers on wide layers (14x32x32 128->1074 F(6,3): two blocks 101,
+        // four 97; 5x27x27 448->896 33, 30), and on others with groups of 64 where a tap reduces enough of
+        // them and their workgroups fill the CUs evenly: once or many times (two blocks, four)
+        //   F(6,3), 4 groups   one on a CU: 2x61x102 256->416 41.7, 34.5; 5x64x64 704->256 88, 72; a few
+        //                      more: 11x46x70 256->215, 36 on an XCD, 65, 82; 378 in all: 28x68x68 256->88
+        //                      99, 106; from three on a CU: 18x78x78 256->256 127, 109
+        //   F(4,3), 7 groups   one on a CU: 8x47x43 576->192 49, 45; with 4: 5x41x58 256->206 26.7, 29.2; a few
+        //                      more: 1x82x66 384->544, 36 on an XCD, 32, 45; four and a half on a CU:
+        //                      18x59x59 512->320 174, 164; 12x62x62 576->480 217, 193; less: 4x114x114
+        //                      512->293 155, 173; with 4: 28x40x46 256->485 128, 164
+        //            10 groups three on a CU: 2x119x128 768->416 173, 158; 15x38x45 640->480 155, 135
+        //   groups of 32       go either way: 28x33x33 128->163 F(6,3) 38, 45; 2x68x68 576->352 F(4,3) 61, 54
         const long quads = tb * ob / 4;
-        if (p->groups >= 4 && (ob >= 40 || (p->g == 64 && (quads <= 256 || quads >= 768)))) return WQ_K2_FUSED_32x32;
-        if (p->m == 6 && ob >= 40) return WQ_K2_FUSED_32x32;
+        if (ob >= 40 && (p->groups >= 4 || p->m == 6)) return WQ_K2_FUSED_32x32;
+        if (p->g == 64 && (p->m == 6 ? p->groups >= 4 && (four <= 32 || quads >= 768)
+                                     : (p->groups >= 7 && (four <= 32 || quads >= 1152)) ||
+                                           (p->groups >= 10 && quads >= 768)))
+            return WQ_K2_FUSED_32x32;
         return WQ_K2_FUSED_32x16;
     }
-    if (tb >= 16) return WQ_K2_FUSED_32x16;
-    return (can_split && p->groups >= 16) ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
+    return tb >= 16 ? WQ_K2_FUSED_32x16 : WQ_K2_FUSED_16x16;
 }
 
 void publish_choices(wq_plan *p) {

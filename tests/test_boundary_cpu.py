@@ -354,3 +354,24 @@ def test_a_wave_tile_is_no_wider_than_the_padded_outputs(wq, taps, Cout):
 def test_layers_with_one_long_group_take_the_faster_form(wq, shape, fused):
     """A single group of 128 to 512 per tap: one fused launch only where its walk of all taps pays."""
     assert wq.Plan(*shape).k2_variant_name.startswith("fused") == fused
+
+
+@pytest.mark.parametrize("shape,variant", [
+    # fewer blocks than CUs are no reason for one block each where an XCD gets more than its 32
+    ((2, 97, 67, 256, 64, 4, 64), "fused_16x16"), ((12, 29, 26, 224, 96, 4, 32), "fused_32x16"),
+    # three blocks on a CU against one pair, groups of 32 as well
+    ((1, 70, 48, 128, 576, 4, 64), "fused_16x16"), ((1, 54, 67, 96, 608, 4, 32), "fused_16x16"),
+    ((3, 70, 86, 320, 96, 4, 64), "fused_32x16"), ((30, 15, 15, 192, 406, 4, 64), "fused_32x16"),
+    # four blocks: one workgroup on a CU, not one and a few more
+    ((8, 47, 43, 576, 192, 4, 64), "fused_32x32"), ((1, 82, 66, 384, 544, 4, 64), "fused_32x16"),
+    ((14, 15, 23, 448, 544, 4, 64), "fused_32x16"), ((5, 41, 58, 256, 206, 4, 64), "fused_32x16"),
+    ((5, 64, 64, 704, 256, 6, 64), "fused_32x32"), ((11, 46, 70, 256, 215, 6, 64), "fused_32x16"),
+    # or many
+    ((18, 59, 59, 512, 320, 4, 64), "fused_32x32"), ((6, 119, 119, 512, 146, 4, 64), "fused_32x16"),
+    ((28, 40, 46, 256, 485, 4, 64), "fused_32x16"), ((15, 38, 45, 640, 480, 4, 64), "fused_32x32"),
+    ((18, 78, 78, 256, 256, 6, 64), "fused_32x32"),
+], ids=lambda v: "%dx%dx%d_%d-%d_F%d_g%d" % v if isinstance(v, tuple) else v)
+def test_the_fused_tile_follows_how_its_workgroups_fill_the_xcds(wq, shape, variant):
+    """The tile of the fused kernel on both sides of every line of the choice (the measured times stand
+    at the rule)."""
+    assert wq.Plan(*shape).k2_variant_name == variant
