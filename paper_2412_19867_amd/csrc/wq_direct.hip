@@ -160,8 +160,15 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     const int ps = p0 + (lane & (16 * NB - 1));
     const unsigned vSX = ps < P ? Walk::lane_sx(ps) : kPastEnd, outS = Walk::outside((unsigned)ps, (unsigned)a.H, (unsigned)a.W);
     unsigned vX[NB];
-    float out[NB];
-    if constexpr (T9) spread_rows<NB>(__uint_as_float(outS), out);
+    // (two row blocks' masks in one register: with one each the 32 x 64 tile of 4-bit weights takes 170
+    // registers and a wave less fits a SIMD: 8x19x19 896->832 g 128 79 us, 69 so)
+    unsigned out[(NB + 1) / 2] = {};
+    if constexpr (T9) {
+        float o[NB];
+        spread_rows<NB>(__uint_as_float(outS), o);
+#pragma unroll
+        for (int f = 0; f < NB; ++f) out[f / 2] |= __float_as_uint(o[f]) << (f % 2 * 16);
+    }
 #pragma unroll
     for (int f = 0; f < NB; ++f) {
         const int p = p0 + 16 * f + l16;
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
         }
 #pragma unroll
         for (int f = 0; f < NB; ++f) {
-            const unsigned vo = at.masked(vX[f], T9 ? __float_as_uint(out[f]) : 0u);
+            const unsigned vo = at.masked(vX[f], out[f / 2], f % 2);
             if constexpr (K64) {
                 bv[slot][f] = __builtin_amdgcn_raw_buffer_load_b128(rX, vo, at.oX, 0);
             } else {

@@ -93,9 +93,9 @@ struct wq_direct_walk {
         return (hh == 0 ? 0x007u : 0u) | (hh == H - 1 ? 0x1c0u : 0u) | (ww == 0 ? 0x049u : 0u) | (ww == W - 1 ? 0x124u : 0u);
     }
     // a lane's offset at the current tap: bit 31, past the end of every buffer, where the window position
-    // lies outside the image
-    WQ_HD unsigned masked(unsigned lane, unsigned out) const {
-        return T9 ? lane | ((out << (31 - t)) & 0x80000000u) : lane;
+    // lies outside the image (`out`: the positions of two pixels, 16 bits each)
+    WQ_HD unsigned masked(unsigned lane, unsigned out, int half = 0) const {
+        return T9 ? lane | ((out << (31 - 16 * half - t)) & 0x80000000u) : lane;
     }
     // lane parts
     static WQ_HD unsigned lane_x(int quarter, int p, int P) { return ((unsigned)quarter * (unsigned)P + (unsigned)p) * KB; }

@@ -58,12 +58,14 @@ static void layer(int P, int H, int W, int Cin, int Cout_pad, int g, wq_direct_t
                     const int dv = T9 ? tap % 3 - 1 : 0, du = T9 ? tap / 3 - 1 : 0, ww = p % W + dv, hh = p / W % H + du;
                     const bool in = p < P && (!T9 || (ww >= 0 && ww < W && hh >= 0 && hh < H));
                     const unsigned long q = (unsigned long)p + du * W + dv;
-                    const unsigned out = Walk::outside(p, H, W);
+                    // (every other row block's mask lies in the upper half, next to another one's)
+                    const int half = p / 16 % 2;
+                    const unsigned out = Walk::outside(p, H, W) << (16 * half) | 0x1ffu << (16 - 16 * half);
                     for (int quarter = 0; quarter < 4; ++quarter)
-                        pixel("codes", at.oX, at.masked(p < P ? Walk::lane_x(quarter, p, P) : 1u << 31, out), KSTEP / 4,
+                        pixel("codes", at.oX, at.masked(p < P ? Walk::lane_x(quarter, p, P) : 1u << 31, out, half), KSTEP / 4,
                               Walk::bytes_x(P, W, Cin), Walk::back(W) * (KSTEP / 4), in,
                               ((kstep * 4ul + quarter) * P + q) * (KSTEP / 4), name);
-                    pixel("scales", at.oSX, at.masked(p < P ? Walk::lane_sx(p) : 1u << 31, out), 4, Walk::bytes_sx(P, W, groups),
+                    pixel("scales", at.oSX, at.masked(p < P ? Walk::lane_sx(p) : 1u << 31, Walk::outside(p, H, W)), 4, Walk::bytes_sx(P, W, groups),
                           Walk::back(W) * 4, in, ((unsigned long)(kstep * KSTEP / g) * P + q) * 4, name);
                 }
             }
