@@ -63,11 +63,11 @@ constexpr int kMagic = 0x4B400000;
 // of 1.5 * 2^19, whose last place is 2^-4, the result is 1.5 * 2^19 + sum / 16.
 constexpr int kMagic16 = 0x49400000;
 
-// the float of a group's int32 sum, or of a sixteenth of it (exact: a multiple of 16 below 2^24)
+// the float of a group's int32 sum (with MAGIC and SIXTEENTH: of a sixteenth of it)
 template <bool MAGIC, bool SIXTEENTH = false>
 __device__ __forceinline__ float group_sum(int v) {
     if constexpr (MAGIC) return __int_as_float(v) - (SIXTEENTH ? 786432.0f : 12582912.0f);
-    return SIXTEENTH ? (float)v * 0.0625f : (float)v;
+    return (float)v;
 }
 
 // Broadcast of 16-lane rows: lane l of `v` holds the value of pixel l of the wave's 64 (16) pixels;

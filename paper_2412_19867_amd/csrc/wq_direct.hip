@@ -126,8 +126,10 @@ constexpr int kRowsPerPass = (NB > 1 && NO <= 2) ? 32 : 16;
 // W4: the weight codes are 4 bits wide, two per byte (see the weight kernels for the packing of a
 // 16-byte piece into 8).  A lane loads the packed half of its piece and unpacks it as 16 * code
 // (a nibble moved to the top of its byte), so the MFMA loop is the 8-bit one; 16 * |sum| stays below
-// 2^24 for every group size, and the factor leaves where the sum becomes a float (exact), before any
-// scale: outputs reach as far as the 8-bit path's.
+// 2^24 for every group size, and the factor leaves before the running sum, so that outputs reach as far as
+// the 8-bit path's: with one K-step per group by the subtraction that makes the sum a float, otherwise with
+// the channel scales (one product per 16 channels and group, where on the sums it is four per block:
+// 14x33x33 640->584 g 128 131 us, 137 on the sums; exact for scales of 2^-122 and more).
 template <bool K64, bool CPG1, bool W4, bool T9, int NO, int NB, int D, int NWMAX>
 __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     constexpr int KSTEP = K64 ? 64 : 32, KB = KSTEP / 4;
@@ -264,8 +266,8 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
                 }
             }
             if (done) {
-                const float s0 = quad_bcast<0>(swv[u][e]), s1 = quad_bcast<1>(swv[u][e]),
-                            s2 = quad_bcast<2>(swv[u][e]), s3 = quad_bcast<3>(swv[u][e]);
+                const float sw = W4 && !CPG1 ? swv[u][e] * 0.0625f : swv[u][e];
+                const float s0 = quad_bcast<0>(sw), s1 = quad_bcast<1>(sw), s2 = quad_bcast<2>(sw), s3 = quad_bcast<3>(sw);
 #pragma unroll
                 for (int f = 0; f < NB; ++f) {
                     Mc[e][f].x = __builtin_fmaf(group_sum<CPG1, W4>(P4[f][0]), s0 * sx[f], Mc[e][f].x);
