@@ -319,10 +319,10 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_direct_conv(const DArgs a) {
     // channels stored ----
     // More than two slices are added in fp64, which costs a conversion per term: fp32 additions of sums
     // as large as the result would add as much error as the chain of groups they replace (with G groups
-    // in c chains the squared error goes with G / (2 c) + c / 2).  The 64-wide tiles of linear layers with
-    // ten groups and more, and of 3x3 layers, add in fp32: their four slices come in place of as many,
-    // or of longer chains.  Relative error before and after: 2x32x32 1280->320 g 32 1.76e-7, 1.26e-7 (28.4,
-    // 27.9 us on 2x32x32 640->640); 64x5120->2048 g 32 1.25e-7, 8.4e-8 (12.1, 12.5 us).
+    // in c chains the squared error goes with G / (2 c) + c / 2).  The four slices of the 64-wide tiles
+    // add in fp32: they come in place of as many, or of longer chains.  Relative error before and after:
+    // 2x32x32 1280->320 g 32 1.76e-7, 1.26e-7 (28.4, 27.9 us on 2x32x32 640->640); 64x5120->2048 g 32
+    // 1.25e-7, 8.4e-8 (12.1, 12.5 us).
     const bool wide = a.slices > 2 && (NO <= 2 || (!T9 && groups < 10));
     constexpr int FB = kRowsPerPass<NO, NB> / 16, ROWS = 16 * FB;
     float *mine = part_s + w * (ROWS * RS);

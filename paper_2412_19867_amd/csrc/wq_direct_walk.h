@@ -24,11 +24,24 @@ struct wq_direct_tile {
 //   n44 >= 150 (171) 64 x 64 and 4 slices, except 3x3 layers below 640 tiles: there the nine-fold
 //                    reduction makes a tile of work so big that 32 x 64 fills the last round better
 //                    (2 x 32^2 pixels, 640 -> 640: 26.5 against 29.8 us)
-//   n44 >= 40        32 x 64, 8 slices; 3x3 layers up to 170 tiles too, whose four slices would be longer
-//                    chains of fp32 additions than nine taps on their own (2x16x16 1280->1280: relative
-//                    error 1.29e-7 with 4 slices, 9.3e-8 with 8, 36.3 and 40.1 us)
+//   n44 >= 40        32 x 64, 8 slices; 3x3 layers of more than six groups up to 170 tiles too, whose four
+//                    slices would be longer chains of fp32 additions than nine taps on their own
+//                    (2x16x16 1280->1280: relative error 1.29e-7 with 4 slices, 9.3e-8 with 8, 36.3 and
+//                    40.1 us; 3x20x19 128->544 g 128, nine groups in all, takes four: 12.1, 16.1 us)
 //   fewer            16 x 16 (as long as those are few too), else 16 x 64, 8 slices: latency rules,
 //                    every wave should have only a handful of K-steps
+//   up to 9 groups   of a linear layer, from 150 tiles: two slices, 32 x 64 below 600 (354x768->3936 g 128
+//                    11.2 us, 64 x 64 in four 13.2; 3224x1024->384 g 256 14.1, 15.9), 64 x 64 below 900
+//                    (1746x1792->2016 g 256 23.4, 27.9; 32 x 64 28.3); then one, 32 x 64 below 1500
+//                    (1817x512->3264 g 128 15.8, 24.4; 64 x 64 17.7), 64 x 64 from there (2356x320->3040
+//                    14.9, in two 18.6; 32 x 64 15.6) and for groups of 256 (2681x1536->2067 34.4, 37.6)
+//   up to 3 groups   one chain rounds less often than slices and their sum would, so the waves come from
+//                    smaller tiles instead: 16 x 16 below 90 tiles (340x192->672 6.3 us, 32 x 64 7.7;
+//                    5538x192->64 7.1, 8.3), 16 x 64 below 300 (2699x384->384 9.9, 64 x 64 12.5, 11.1 in four
+//                    slices; 2512x512->256 9.3, 12.5), 32 x 64 below 1500 (3516x128->704 9.2, 10.4;
+//                    6618x512->832 17.9, 18.5; from there 5441x256->1440 16.9, 16.3).  Three waves with a
+//                    long group each, whose fp64 sum rounds as often, where 16 x 16 tiles are few
+//                    (223x768->96 g 256 6.7, one chain 7.6)
 // No tile is wider than the layer's padded channels, and a workgroup's tiles lie along the pixels where
 // one covers all channels: a wave that has no channels of its own costs as much as one that has (us at
 // 64 x 64 tiles and 2 x 2 of them in a workgroup, and so: 640^2 pixels 128->24 183, 87; 448^2 64->64 59,
@@ -44,17 +57,24 @@ inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int g
         while (t.slices > 4 && ob * pb * t.slices > 2048) t.slices /= 2;
     } else if (n44 < 40) {
         t.slices = 8;
-    } else if (n44 < (taps == 9 ? 171 : 150)) {
+    } else if (n44 < (taps == 9 && groups > 6 ? 171 : 150)) {
         t.no = 2; t.slices = 8;
     } else if (taps == 9 && n44 < 640) {
         t.no = 2;
         t.slices = ((ob + 1) / 2) * ((pb + 3) / 4) > 1024 ? 2 : 4;
+    } else if (n44 < 3000 && taps == 1 && G < 10) {
+        t.no = n44 < 600 || (n44 >= 900 && n44 < 1500 && g < 256) ? 2 : 4;
+        t.slices = n44 < 900 ? 2 : 1;
     } else if (n44 < 1500) {
         t.no = 4; t.slices = 4;
     } else if (n44 < 3000) {
         t.no = 4; t.slices = 2; t.wt = 2;
     } else {
         t.no = 4; t.wo = t.wt = 2;
+    }
+    if (G < 4 && n44 < 1500 && pb > 1) {
+        t.no = n44 < 300 ? 1 : 2;
+        t.nb = n44 < 90 ? 1 : 4;
     }
     if (ob <= t.no / 2) t.no /= 2;   // (ob is even, and 2 or more)
     if (t.wo == 2 && ob <= t.no) {
@@ -65,9 +85,10 @@ inline wq_direct_tile wq_direct_choose_tile(int P, int Cout_pad, int taps, int g
         t.wo = t.wt = 1;
         if (t.slices > 8) t.no = 1;   // the larger tiles' registers allow 8 waves per workgroup
     } else {
-        while (t.slices > 1 && G * g < 2L * kstep * t.slices) t.slices /= 2;   // two K-steps each at least
-        // one chain of up to three groups rounds less often than slices and their sum do
-        if (G < 4) t.slices = 1;
+        // two K-steps each at least, and a whole group (3x2048->510 g 512 in 8 slices of its four groups 8.3,
+        // in four 7.2; 445x2560->128 g 512, five groups, 10.6, 10.1)
+        while (t.slices > 1 && (G * g < 2L * kstep * t.slices || t.slices > G)) t.slices /= 2;
+        if (G < 4) t.slices = G == 3 && g >= 128 && t.nb == 1 && ob * pb <= 512 ? 3 : 1;
     }
     return t;
 }

@@ -375,3 +375,19 @@ def test_the_fused_tile_follows_how_its_workgroups_fill_the_xcds(wq, shape, vari
     """The tile of the fused kernel on both sides of every line of the choice (the measured times stand
     at the rule)."""
     assert wq.Plan(*shape).k2_variant_name == variant
+
+
+@pytest.mark.parametrize("g", [32, 64, 128, 256, 512])
+@pytest.mark.parametrize("groups", [1, 2, 3, 4, 5, 7, 12])
+def test_every_wave_of_the_quantized_gemm_has_a_group(wq, groups, g):
+    """A slice of the reduction is whole groups: no more waves share a tile than there are groups.  Up to
+    three groups stay one chain of additions (or a wave each), on tiles small enough that the launch fills
+    the GPU."""
+    for P in (5, 100, 700, 2699, 9000):
+        for Cout in (48, 384, 2100):
+            channels, pixels, waves = wq.DirectPlan(P, 1, 1, g * groups, Cout, g, linear=True).launch
+            assert waves <= groups
+            if groups < 4:
+                assert waves == 1 or waves == groups == 3
+                launched = -(-P // pixels) * -(-Cout // channels)
+                assert channels * pixels == 256 or launched >= 400

@@ -222,7 +222,9 @@ def test_outputs_near_the_ends_of_the_range(wq, g, bits, exponent):
     (9, 2, 32, 32, 1280, 320, 32, 9), (9, 2, 16, 16, 1280, 1280, 64, 9), (9, 4, 19, 22, 896, 64, 64, 9),
     (1, 64, 1, 1, 5120, 2048, 32, 16), (1, 16, 1, 1, 5120, 5120, 32, 8), (1, 64, 1, 1, 5120, 640, 512, 2),
     (1, 300, 1, 1, 512, 2560, 128, 2), (1, 1100, 1, 1, 512, 1280, 256, 1), (1, 260, 1, 1, 1280, 2560, 256, 1),
-        (1, 64, 1, 1, 768, 640, 256, 1), (1, 700, 1, 1, 1024, 1280, 128, 4), (9, 1, 61, 40, 64, 512, 64, 3),
+    (1, 64, 1, 1, 768, 640, 256, 1), (1, 700, 1, 1, 1024, 1280, 128, 4), (1, 1817, 1, 1, 512, 3264, 128, 1), (9, 1, 61, 40, 64, 512, 64, 3),
+    (9, 3, 18, 18, 640, 640, 128, 9), (9, 3, 20, 19, 128, 544, 128, 9), (9, 1, 30, 41, 384, 640, 64, 9),
+    (1, 2699, 1, 1, 384, 384, 128, 1), (1, 700, 1, 1, 1280, 1280, 256, 1), (1, 100, 1, 1, 1024, 480, 256, 1),
 ], ids=lambda c: "t%d_%dx%dx%d_%d-%d_g%d_%d" % c)
 def test_error_of_the_sums_over_groups(wq, case):
     """Distance from the fp64 sum of the same codes and scales, against what `chains` fp32 chains of
