@@ -126,8 +126,8 @@ def test_direct_largest_pixel_count(wq):
     (100009, 64, 30, 32), (50003, 128, 32, 32),
 ], ids=lambda c: "p%d_%d-%d_g%d" % c)
 def test_every_tile_choice_of_the_quantized_gemm(wq, case):
-    """Rows and channels that end inside a tile, for every wave tile and slice count the plan picks
-    from (against the oracle in fp64)."""
+    """Rows and channels that end inside a tile, from 16 rows to narrow layers of 192003 (against the
+    oracle in fp64); every kernel instance runs in test_every_instance_of_the_quantized_gemm."""
     R, Cin, Cout, g = case
     rng = np.random.default_rng(R)
     x, w = rng.standard_normal((R, Cin)).astype(np.float32), rng.standard_normal((Cout, Cin)).astype(np.float32)
@@ -217,6 +217,32 @@ def test_outputs_near_the_ends_of_the_range(wq, g, bits, exponent):
     assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
+def forward_and_fp64_reference(wq, taps, N, H, W, Cin, Cout, g, bits=8, launch=None):
+    """y of a layer of random data, and the fp64 sums of the codes and scales it was computed from."""
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    P, groups = N * H * W, Cin // g
+    x = torch.randn(P, Cin, generator=gen, device="cuda")
+    w = torch.randn(Cout, Cin * taps, generator=gen, device="cuda")
+    plan = wq.DirectPlan(N, H, W, Cin, Cout, g, linear=taps == 1, weight_bits=bits)
+    if launch:
+        assert plan.launch == launch
+    blob, ws, y = plan.alloc_blob(), plan.alloc_workspace(), plan.alloc_output()
+    ws.fill_(0xff)
+    y.fill_(float("nan"))
+    plan.weight_prepare(w, None, blob)
+    plan.forward(x, blob, ws, y)
+    Wq, sW, _ = plan.blob_views(blob)
+    xq, sx = plan.workspace_views(ws)
+    xd = (xq.view(P, groups, g).double() * sx.view(P, groups, 1).double()).view(N, H, W, Cin)
+    xd = torch.nn.functional.pad(xd, (0, 0, 1, 1, 1, 1))
+    ref = torch.zeros(P, Cout, dtype=torch.float64, device="cuda")
+    for t in range(taps):
+        u, v = (t // 3, t % 3) if taps == 9 else (1, 1)
+        wd = Wq[t, :Cout].view(Cout, groups, g).double() * sW[t, :, :Cout].t().unsqueeze(2).double()
+        ref += xd[:, u:u + H, v:v + W].reshape(P, Cin) @ wd.view(Cout, Cin).t().contiguous()
+    return y.view(P, Cout).double(), ref
+
+
 @pytest.mark.parametrize("case", [
     # taps N  H   W   Cin   Cout  g   chains
     (9, 2, 32, 32, 1280, 320, 32, 9), (9, 2, 16, 16, 1280, 1280, 64, 9), (9, 4, 19, 22, 896, 64, 64, 9),
@@ -234,25 +260,49 @@ def test_error_of_the_sums_over_groups(wq, case):
     products of two scales, the sums inside c chains and the sums of chains make
     u^2 (1 + (G / c + 1) / 2 + (c + 1) / 2 - 1 / c) relative to the result.  (6 % for the formula.)"""
     taps, N, H, W, Cin, Cout, g, chains = case
-    gen = torch.Generator(device="cuda").manual_seed(31)
-    P, groups = N * H * W, Cin // g
-    x = torch.randn(P, Cin, generator=gen, device="cuda")
-    w = torch.randn(Cout, Cin * taps, generator=gen, device="cuda")
-    plan = wq.DirectPlan(N, H, W, Cin, Cout, g, linear=taps == 1)
-    blob, ws, y = plan.alloc_blob(), plan.alloc_workspace(), plan.alloc_output()
-    plan.weight_prepare(w, None, blob)
-    plan.forward(x, blob, ws, y)
-    Wq, sW, _ = plan.blob_views(blob)
-    xq, sx = plan.workspace_views(ws)
-    xd = (xq.view(P, groups, g).double() * sx.view(P, groups, 1).double()).view(N, H, W, Cin)
-    xd = torch.nn.functional.pad(xd, (0, 0, 1, 1, 1, 1))
-    ref = torch.zeros(P, Cout, dtype=torch.float64, device="cuda")
-    for t in range(taps):
-        u, v = (t // 3, t % 3) if taps == 9 else (1, 1)
-        wd = Wq[t, :Cout].view(Cout, groups, g).double() * sW[t, :, :Cout].t().unsqueeze(2).double()
-        ref += xd[:, u:u + H, v:v + W].reshape(P, Cin) @ wd.view(Cout, Cin).t().contiguous()
-    err = float((y.view(P, Cout).double() - ref).norm() / ref.norm())
+    y, ref = forward_and_fp64_reference(wq, *case[:7])
+    groups = Cin // g
+    err = float((y - ref).norm() / ref.norm())
     G = taps * groups
     bound = 2.0 ** -23 * np.sqrt(3 / (8 * np.log(2)) / 12 * (2 + G / (2 * chains) + chains / 2 - 1 / chains))
     print(f"error {err:.3e}, {chains} chains of fp32 {bound:.3e}")
     assert err <= 1.06 * bound
+
+
+@pytest.mark.parametrize("tile", [
+    # N  H   W   Cout  wave tile       (pixels and channels that end inside it, rows that do not match it)
+    ((1, 9, 7, 33), (16, 16)), ((4, 21, 25, 57), (16, 64)), ((2, 22, 25, 130), (32, 64)), ((3, 67, 69, 130), (64, 64)),
+], ids=lambda t: "%dx%d" % t[1])
+@pytest.mark.parametrize("taps", [1, 9])
+@pytest.mark.parametrize("bits", [8, 4], ids=["w8", "w4"])
+@pytest.mark.parametrize("g", [32, 64, 128])
+def test_every_instance_of_the_quantized_gemm(wq, g, bits, taps, tile):
+    """K-step and group class x width of the weight codes x 3x3 or linear x wave tile, each as the plan's own
+    choice."""
+    (N, H, W, Cout), (channels, pixels) = tile
+    groups = 2 if taps == 9 else 4
+    plan = wq.DirectPlan(N, H, W, groups * g, Cout, g, linear=taps == 1, weight_bits=bits)
+    assert plan.launch[:2] == (channels, pixels)
+    y, ref = forward_and_fp64_reference(wq, taps, N, H, W, groups * g, Cout, g, bits)
+    assert bool(torch.isfinite(y).all())
+    assert float((y - ref).abs().max()) <= Y_TOL * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("bits", [8, 4], ids=["w8", "w4"])
+@pytest.mark.parametrize("case", [
+    # taps N  H   W   Cin  Cout  g   (channels, pixels, waves)
+    (1, 20, 1, 1, 1280, 500, 64, (16, 16, 8)), (1, 100, 1, 1, 768, 100, 256, (16, 16, 3)),
+    (1, 2100, 1, 1, 1280, 57, 64, (16, 64, 8)), (9, 2, 12, 13, 448, 250, 64, (16, 16, 4)),
+    (9, 3, 23, 24, 128, 330, 64, (32, 64, 4)), (9, 1, 30, 41, 448, 500, 64, (32, 64, 8)),
+    (9, 3, 31, 33, 64, 500, 64, (32, 64, 4)), (9, 3, 45, 46, 64, 330, 64, (32, 64, 2)),
+    (9, 4, 63, 65, 64, 300, 64, (64, 64, 4)), (9, 3, 67, 69, 64, 450, 64, (64, 64, 2)),
+    (9, 5, 67, 69, 64, 600, 64, (64, 64, 1)), (1, 3300, 1, 1, 640, 130, 64, (64, 64, 4)),
+    (1, 2700, 1, 1, 384, 290, 64, (32, 64, 2)), (1, 4000, 1, 1, 320, 700, 64, (64, 64, 2)),
+    (1, 4000, 1, 1, 320, 1250, 64, (32, 64, 1)), (1, 6000, 1, 1, 320, 1250, 64, (64, 64, 1)),
+    (1, 2700, 1, 1, 192, 290, 64, (16, 64, 1)), (1, 12500, 1, 1, 640, 1030, 64, (64, 64, 1)),
+], ids=lambda c: "t%d_%dx%dx%d_%d-%d_g%d_%s" % (c[:7] + ("x".join(map(str, c[7])),)))
+def test_every_slice_count_the_plan_picks(wq, case, bits):
+    """The waves that share a tile's reduction, as chosen for the shape, with ragged pixels and channels."""
+    y, ref = forward_and_fp64_reference(wq, *case[:7], bits=bits, launch=case[7])
+    assert bool(torch.isfinite(y).all())
+    assert float((y - ref).abs().max()) <= Y_TOL * float(ref.abs().max())

@@ -21,7 +21,7 @@ CASES = [
     (6, 9, 1024, 16, 512),
     (7, 1000, 320, 320, 32),
     (8, 4096, 1280, 640, 64),     # an attention-sized projection
-    (9, 16, 2048, 256, 64),       # few rows: the reduction is split over 16 workgroups per tile
+    (9, 16, 2048, 256, 64),       # few rows: eight waves share the reduction of a tile
     (10, 77, 768, 768, 32),       # a text-encoder sized layer
 ]
 
@@ -39,7 +39,7 @@ def test_linear_layers(wq, case, bits):
 
     plan = wq.DirectPlan(R, 1, 1, Cin, Cout, g, linear=True, weight_bits=bits)
     L = plan.layout
-    assert L.taps == 1 and L.P == R and L.weight_bits == bits and (Cin // g) % L.splits == 0
+    assert L.taps == 1 and L.P == R and L.weight_bits == bits and 1 <= plan.launch[2] <= Cin // g
     assert L.blob_sW_off >= L.Cout_pad * Cin * bits // 8 and L.blob_sW_off < L.Cout_pad * Cin * bits // 8 + 256
     blob, ws, y = plan.alloc_blob(), plan.alloc_workspace(), plan.alloc_output()
     y.fill_(float("nan"))
