@@ -20,24 +20,34 @@
 // finishes Y[a][b] = sum_i A^T[a][i] (sum_ks R_{i,ks}[b]), adds bias and stores
 // NHWC with the ragged right/bottom edge masked.
 //
+// What bounds it: a 1 KiB operand load costs the CU's load path 17 cycles, whatever its width a load costs 8
+// at least, and a SIMD issues a block's 12 dequantization instructions and its MFMA in 46 (the two do not
+// overlap).  With NT x NO blocks of operands per wave the load path takes 17 (NT + NO) / (NT NO) cycles of a
+// CU per block, 34 with one and 17 with four, against 11.5 of its four SIMDs.
+//
 // A wave waits for nothing but its own loads, so what counts is that the compiler can count them:
-// the request of the K-step D ahead is unconditional, whole rounds of the ring make up a wave's walk,
-// and it is placed between the MFMAs and the dequantization, which covers their latency.  The last
-// round is written out without requests: a walk has only (m + 2) Cin / K-step of them, so requests
-// past its end cost up to a half more (whole forward with and without: 29x43x43 64->992 F(2,3), one
-// round, 201, 130 us; 8x78x78 192->512 F(2,3) 168, 135; 1x32x32 64->64 F(4,3) 11.1, 10.1; 32x56x56
-// 64->64 F(6,3) 33.0, 32.1).  Scales cost one word per lane and load (a v4 load of
-// the four channel scales moves four times the bytes through the load path) and reach the lanes by
-// DPP quad broadcasts and a row swap; groups of one K-step start their sums at kMagic.  Measured
-// against conditional requests, v4 scales and conversions: 32x28^2 128->128 F(6,3) 26.1 -> 24.6 us,
-// 8x100x128 192->64 F(4,3) g 32 69.8 -> 61.4 us, 2x64x64 320->320 F(4,3) at one block per wave
-// 32.3 -> 26.5 us (whole forward; 25.1 without the requests past the end).
+// the request of the K-step D ahead is unconditional, a walk is whole rounds of n K-steps, and the request
+// is placed between the MFMAs and the dequantization, which covers their latency.  The last
+// round is written out without the requests past its end: a walk has only (m + 2) Cin / K-step steps, so those
+// would cost up to a half more (whole forward with and without: 29x43x43 64->992 F(2,3), one
+// round, 201, 130 us; 8x78x78 192->512 F(2,3) 168, 135).
+//
+// Scales of groups of one K-step: a round's scales of n groups come in one load per tensor straight into LDS
+// that is the wave's own (no barrier: the wave's count of loads in flight says when they are there), a round
+// ahead, and reach the lanes as broadcast LDS reads, which cost neither the load path nor the vector ALU
+// anything.  (One word per lane, load and K-step, spread by DPP, took two of five loads, and a DPP
+// instruction among others keeps the SIMD from issuing for two waves at once: 2.4 -> 4.4 cycles for the
+// instructions around it.)  Kernel, before and after, with one, two and four blocks: 2x128x128 320->320 F(4,3)
+// 52.2, 44.8, 51.6 -> 49.9, 42.6, 41.5 us; 32x56x56 64->64 F(6,3) 18.2, 16.4, 16.9 -> 17.5, 15.7, 14.6;
+// 1x32x32 64->64 F(4,3) 5.5 -> 4.8.  Longer groups keep the DPP form.
 //
 // Workgroups are numbered so that the eight XCDs (which receive consecutive
 // workgroup ids round-robin and have private L2s) each own a slice of the
 // larger operand: with xcd_mode 0 an XCD owns every 8th block of output
 // channels (weights stay in its L2), with xcd_mode 1 every 8th block of tiles,
-// with xcd_mode 2 every 4th block of tiles and one half of the channels.
+// with xcd_mode 2 every 4th block of tiles and one half of the channels.  Where the other operand does not fit
+// that L2 it passes in bands of 1 MB (all of the XCD's own blocks meet a band before the next comes): 26x46 tile
+// and channel blocks of 960 channels 73 -> 56 us, 80 x 62 blocks of 448 140 -> 98.
 #pragma once
 
 #include <type_traits>
@@ -47,11 +57,10 @@
 
 namespace {   // every including file instantiates its own tile size; nothing here is exported
 
-// K-steps in flight of a wave, a divisor of the taps of a row.  (F(4,3) with 6 in flight: 2x64x64
-// 320->320 with two blocks per wave 33.9 against 27.4 us, the registers cost a workgroup per CU.)
-template <int M, int NT, int NO>
-constexpr int kDepth = M == 4 ? 3 : (NT * NO == 4 ? 2 : 4);
-constexpr int RS_STRIDE = 20;           // floats per tile row of the LDS exchange (16 + pad)
+// K-steps in flight of a wave, a divisor of the taps of a row.  Two with four blocks per wave, and with two of
+// F(6,3) at K 64: two workgroups then fit a CU where the registers of more in flight leave one.
+template <int M, int NT, int NO, bool K64 = true>
+constexpr int kDepth = NT * NO == 4 || (M == 6 && NT * NO == 2 && K64) ? 2 : (M == 4 ? 3 : 4);
 
 struct Args {
     wq_xf xf;
@@ -63,17 +72,23 @@ struct Args {
     float *y;
     wq_dump dump;   // debug calls: where to store the int32 group sums (P == nullptr otherwise)
     int H, W, Cin, Cout, TH, TW, T, T_pad, Cout_pad, log2g;
-    int nTB, nOB, xcd_mode;
+    int nTB, nOB, xcd_mode, band;
+    // Store y with plain instead of streaming stores: the next layer's input kernel finds 32 to 64 MB in the
+    // caches (2x128x128 320->320, chained: this kernel 42.1 -> 43.4 us, that one 20.8 -> 16.7).  Smaller outputs
+    // gain as much as they lose (32x56x56 64->64: 15.0 -> 16.4 and 16.2 -> 14.8), far larger ones lose (115 MB in
+    // half lines: 44 -> 68).
+    int plain_y;
+    int dense_rows;   // see wq_plan
 };
 
 template <bool K64, int NT, int NO>
 struct Stage {
     v4i a[NO], b[NT];   // K64: 16 operand bytes per lane; otherwise .xy only
-    float sw[NO];       // weight scale of channel 4 q + lane % 4 of each sub-block
-    float sx;           // activation scale of tile lane % (16 NT)
+    float sw[NO];       // longer groups: weight scale of channel 4 q + lane % 4 of each sub-block
+    float sx;           // and activation scale of tile lane % (16 NT)
 };
 
-template <int M, bool K64, bool CPG1, bool WIDE, bool ATSP, bool DUMP, int NT, int NO, int KS, int D>
+template <int M, bool K64, bool CPG1, bool WIDE, bool ATSP, bool DUMP, int NT, int NO, int KS, int D, bool ONE>
 __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Args a) {
     constexpr int n = M + 2;
     static_assert(n % D == 0, "a tap row is a whole number of rounds of the ring");
@@ -82,23 +97,29 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
     constexpr int KSTEP = K64 ? 64 : 32;   // K per MFMA
     constexpr int KB = KSTEP / 4;          // operand bytes per lane per MFMA
     constexpr int NW = n * KS;             // waves
-    // output columns per LDS pass: all M when the exchange area fits 64 KiB, else half of them
-    constexpr int BP = NW * M * 16 * RS_STRIDE * 4 <= 65536 ? M : M / 2;
-    constexpr int NTH = (64 * NW / 256) * 256;   // threads of the final phase: a multiple of 256,
-                                                 // so that a thread keeps its (tile, channel) position
-    using Pat = wq_pattern<M>;
-    __shared__ float Rs[NW][BP][16 * RS_STRIDE];
+    constexpr int RS = 16 * NO + 4;              // floats per tile row of the exchange (the channels + pad)
+    constexpr int RSW = 16 * RS;                 // floats of one wave's column
+    // output columns per LDS pass: all M, or half of them (with two channel blocks their stores then fill
+    // lines of 128 bytes)
+    constexpr int BP = ONE ? M : M / 2;
+    constexpr int SLOT = 2048;                   // bytes of a wave's scales of one round: 1 KiB per tensor
+    static_assert(n * 16 * (NO > NT ? NO : NT) * 4 <= 1024, "a round's scales are one wave-wide load per tensor");
+    constexpr int LDS_BYTES = NW * (BP * RSW * 4 > 2 * SLOT || !CPG1 ? BP * RSW * 4 : 2 * SLOT);
+    // the scales of the rounds in flight while the walk lasts, then the exchange of the row sums
+    __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
+    float *const Rs = reinterpret_cast<float *>(lds);
 
     // ---- which block (uniform) ----
     int tb, ob;
     {
         const int id = blockIdx.x, xcd = id & 7, s = id >> 3;
-        if (a.xcd_mode == 0) {
-            ob = (s / a.nTB) * 8 + xcd;
-            tb = s % a.nTB;
-        } else if (a.xcd_mode == 1) {
-            tb = (s / a.nOB) * 8 + xcd;
-            ob = s % a.nOB;
+        if (a.xcd_mode != 2) {
+            // in bands of the other operand's blocks: all of the XCD's own blocks pass a band while it is in the L2
+            const int others = a.xcd_mode == 0 ? a.nTB : a.nOB, own = ((a.xcd_mode == 0 ? a.nOB : a.nTB) + 7) >> 3;
+            const int first = s / (own * a.band) * a.band, r = s - first * own, width = min(a.band, others - first);
+            const int mine8 = (r / width) * 8 + xcd, other = first + r % width;
+            ob = a.xcd_mode == 0 ? mine8 : other;
+            tb = a.xcd_mode == 0 ? other : mine8;
         } else {   // 4 parts of the tiles x 2 halves of the channels
             const int hob = (a.nOB + 1) >> 1;
             tb = (s / hob) * 4 + (xcd >> 1);
@@ -144,7 +165,6 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
     unsigned oSX = t0 * planeSX + (unsigned)(ks * gps) * 64u;
     const unsigned dW = planeW - (unsigned)cps * stepOp, dX = planeX - (unsigned)cps * stepOp;
     const unsigned dSW = planeSW - (unsigned)gps * stepSW, dSX = planeSX - (unsigned)gps * 64u;
-    const int NI = n * cps;                      // the wave's K-steps, a multiple of D
     int k_ld = 0, kg_ld = 0;
 
     auto load_stage = [&](Stage<K64, NT, NO> &s) {
@@ -166,19 +186,58 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
                 s.b[nt] = v4i{t.x, t.y, 0, 0};
             }
         }
+        if constexpr (!CPG1) {
 #pragma unroll
-        for (int no = 0; no < NO; ++no)
-            s.sw[no] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSW, vSW, oSW + 64u * no, 0));
-        s.sx = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX, oSX, 0));
+            for (int no = 0; no < NO; ++no)
+                s.sw[no] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSW, vSW, oSW + 64u * no, 0));
+            s.sx = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rSX, vSX, oSX, 0));
+        }
         // branch-free scalar bookkeeping
         ++k_ld;
         ++kg_ld;
-        const bool next_group = CPG1 || (kg_ld & cpg_mask) == 0, next_tap = k_ld == cps;
+        const bool next_group = (kg_ld & cpg_mask) == 0, next_tap = k_ld == cps;
         k_ld = next_tap ? 0 : k_ld;
         oW += stepOp + (next_tap ? dW : 0u);
         oX += stepOp + (next_tap ? dX : 0u);
-        oSW += (next_group ? stepSW : 0u) + (next_tap ? dSW : 0u);
-        oSX += (next_group ? 64u : 0u) + (next_tap ? dSX : 0u);
+        if constexpr (!CPG1) {
+            oSW += (next_group ? stepSW : 0u) + (next_tap ? dSW : 0u);
+            oSX += (next_group ? 64u : 0u) + (next_tap ? dSX : 0u);
+        }
+    };
+
+    // ---- scales of groups of one K-step: n groups of the walk a round, loaded into the wave's own LDS ----
+    // One load per tensor and round; lane l fetches four channels (tiles) of the round's group l / (4 NO)
+    // (l / (4 NT)).  `at`: that group's position in its tap, `off`: its byte offset.
+    char *const mine = lds + w * (2 * SLOT);
+    struct ScaleWalk {
+        int at;
+        unsigned off;
+    };
+    auto scale_walk = [&](int gl, unsigned lane_off, unsigned base, unsigned plane, unsigned step) {
+        ScaleWalk c;
+        const int tap = gl / gps;
+        c.at = gl - tap * gps;
+        c.off = gl < n ? base + (unsigned)tap * plane + (unsigned)c.at * step + lane_off : kPastEnd;
+        return c;
+    };
+    ScaleWalk cW = {}, cX = {};
+    const int skip_taps = n / gps, skip_groups = n - skip_taps * gps;   // n groups further on
+    if constexpr (CPG1) {
+        cW = scale_walk(lane / (4 * NO), (unsigned)(o0 + 4 * (lane % (4 * NO))) * 4u, oSW, planeSW, stepSW);
+        const int tile = 4 * (lane % (4 * NT));   // sX [tap][16-tile block][group][16]
+        cX = scale_walk(lane / (4 * NT), (unsigned)(((tau0 + tile) >> 4) * groups * 64 + (tile & 15) * 4), oSX, planeSX, 64u);
+    }
+    auto load_scales = [&](int slot) {
+        lds_load16(rSW, mine + slot * SLOT, cW.off, 0);
+        lds_load16(rSX, mine + slot * SLOT + 1024, cX.off, 0);
+        auto advance = [&](ScaleWalk &c, unsigned plane, unsigned step) {   // (past its last tap a wave loads what it never reads)
+            c.at += skip_groups;
+            const bool wrap = c.at >= gps;
+            c.at -= wrap ? gps : 0;
+            c.off += (unsigned)skip_taps * plane + (unsigned)skip_groups * step + (wrap ? plane - (unsigned)gps * step : 0u);
+        };
+        advance(cW, planeSW, stepSW);
+        advance(cX, planeSX, 64u);
     };
 
     float4 R[M][NO][NT];
@@ -189,6 +248,10 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) R[b][no][nt] = make_float4(0.f, 0.f, 0.f, 0.f);
 
+    if constexpr (CPG1) {
+        load_scales(0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     Stage<K64, NT, NO> st[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) {   // in the order the loop expects them back
@@ -217,10 +280,28 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
     const v4i magic = {kMagic, kMagic, kMagic, kMagic};
     // (no exit test and no run-time condition on a request inside a round: with either of them the
     // compiler cannot count the loads in flight and waits for all of them at the top of every round)
+    int slot = 0;
     auto round = [&](auto last) {
+        const char *sc = mine + slot * SLOT;
+        if constexpr (CPG1) {
+            if constexpr (!last.value) load_scales(slot ^ 1);
+            slot ^= 1;
+            // everything but the operands in flight (and the scales just asked for) has landed: this round's scales
+            wait_loads<D * (NT + NO) + (last.value ? 0 : 2)>();
+        }
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            Stage<K64, NT, NO> &s = st[d];
+        for (int step = 0; step < n; ++step) {
+            Stage<K64, NT, NO> &s = st[step % D];
+            v4f sw4[NO];
+            float sx1[NT];
+            if constexpr (CPG1) {
+#pragma unroll
+                for (int no = 0; no < NO; ++no)
+                    sw4[no] = *reinterpret_cast<const v4f *>(sc + (step * NO + no) * 64 + q * 16);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    sx1[nt] = *reinterpret_cast<const float *>(sc + 1024 + (step * NT + nt) * 64 + l16 * 4);
+            }
             const bool group_end = CPG1 || ((++kg_cp & cpg_mask) == 0);
 #pragma unroll
             for (int no = 0; no < NO; ++no)
@@ -235,32 +316,26 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
                         acc[no][nt] = __builtin_amdgcn_mfma_i32_16x16x32_i8(av, bv, c0, 0, 0, 0);
                     }
                 }
-            // the scale products leave the stage, whose registers are then refilled while the MFMAs run
-            float4 c[NO][NT];
-            {
-                float sx[NT];
-                spread_rows<NT>(s.sx, sx);
+            // the scales of longer groups leave the stage, whose registers are then refilled while the MFMAs run
+            if constexpr (!CPG1) {
+                spread_rows<NT>(s.sx, sx1);
 #pragma unroll
-                for (int no = 0; no < NO; ++no) {
-                    const float sw0 = quad_bcast<0>(s.sw[no]), sw1 = quad_bcast<1>(s.sw[no]),
-                                sw2 = quad_bcast<2>(s.sw[no]), sw3 = quad_bcast<3>(s.sw[no]);
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        c[no][nt] = make_float4(sw0 * sx[nt], sw1 * sx[nt], sw2 * sx[nt], sw3 * sx[nt]);
-                }
+                for (int no = 0; no < NO; ++no)
+                    sw4[no] = v4f{quad_bcast<0>(s.sw[no]), quad_bcast<1>(s.sw[no]), quad_bcast<2>(s.sw[no]), quad_bcast<3>(s.sw[no])};
             }
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!last.value) load_stage(s);   // D steps ahead
+            else if (step + D < n) load_stage(s);
             __builtin_amdgcn_sched_barrier(0);
             if (group_end) {
 #pragma unroll
                 for (int no = 0; no < NO; ++no)
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
-                        Mc[no][nt].x = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][0]), c[no][nt].x, Mc[no][nt].x);
-                        Mc[no][nt].y = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][1]), c[no][nt].y, Mc[no][nt].y);
-                        Mc[no][nt].z = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][2]), c[no][nt].z, Mc[no][nt].z);
-                        Mc[no][nt].w = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][3]), c[no][nt].w, Mc[no][nt].w);
+                        Mc[no][nt].x = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][0]), sw4[no].x * sx1[nt], Mc[no][nt].x);
+                        Mc[no][nt].y = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][1]), sw4[no].y * sx1[nt], Mc[no][nt].y);
+                        Mc[no][nt].z = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][2]), sw4[no].z * sx1[nt], Mc[no][nt].z);
+                        Mc[no][nt].w = __builtin_fmaf(group_sum<MAGIC>(acc[no][nt][3]), sw4[no].w * sx1[nt], Mc[no][nt].w);
                         if constexpr (DUMP) {   // the debug entry point's instance of this kernel
                             constexpr int off = MAGIC ? kMagic : 0;
                             const int v[4] = {acc[no][nt][0] - off, acc[no][nt][1] - off, acc[no][nt][2] - off,
@@ -321,91 +396,119 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
             }
         }
     };
-    for (int it = NI - D; it > 0; it -= D) round(std::false_type{});
+    for (int it = cps - 1; it > 0; --it) round(std::false_type{});
     round(std::true_type{});
 
-    // Every thread finishes the same (tile, channel) position of each sub-block: where
-    // that tile's outputs start, how much of it lies inside the image, and the bias.
-    const int tl = (tid >> 4) & 15, ol = tid & 15;
-    int out_off[NT], out_lim[NT];
-    float bias_v[NO];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int tau = tau0 + nt * 16 + tl;
-        out_off[nt] = 0;
-        out_lim[nt] = 0;
-        if (tau < a.T) {
+    // ---- output transform across tap rows, 16 tiles and BP columns at a time ----
+    // A thread forms V neighbouring channels of one column of a tile.  Four with two channel blocks (a store
+    // instruction covers 8 lines of 128 bytes: 2x128x128 320->320 42.1 us, with one channel per thread 54), one
+    // with a single block (4 half lines; four channels per thread, 16 half lines: 8x60x60 64->992 F(6,3) 45, 44).
+    auto finish = [&](auto vec, auto plain, int nt, int p) {
+        constexpr int V = decltype(vec)::value, Q = 16 * NO / V, PC = 16 * Q;   // PC threads form a column
+        constexpr int TH = 64 * NW, COLS = TH >= PC ? TH / PC : 1;              // columns at a time
+        if (TH >= PC && tid >= COLS * PC) return;
+        for (int pos = TH >= PC ? tid % PC : tid; pos < PC; pos += TH >= PC ? PC : TH) {
+            const int ch = (pos % Q) * V, tl = pos / Q;
+            const int tau = tau0 + nt * 16 + tl, o = o0 + ch;
+            if (tau >= a.T || o >= a.Cout) continue;
             const int tw = tau % a.TW, th = (tau / a.TW) % a.TH, bb = tau / (a.TW * a.TH);
-            out_off[nt] = ((bb * a.H + th * M) * a.W + tw * M) * a.Cout;
-            out_lim[nt] = min(M, a.H - th * M) | (min(M, a.W - tw * M) << 8);
-        }
-    }
+            const int hv = min(M, a.H - th * M), wv = min(M, a.W - tw * M);
+            float bias[V];
 #pragma unroll
-    for (int no = 0; no < NO; ++no) {
-        const int o = o0 + no * 16 + ol;
-        bias_v[no] = o < a.Cout ? a.bias[o] : 0.f;
-    }
-
-    // ---- output transform across tap rows, one 16x16 sub-block and BP columns at a time ----
-    bool first = true;
+            for (int v = 0; v < V; ++v) bias[v] = a.bias[o + v];   // (padded to Cout_pad)
+            float *const base = a.y + ((size_t)(bb * a.H + th * M) * a.W + tw * M) * a.Cout + o;
+            for (int bp = TH >= PC ? tid / PC : 0; bp < BP; bp += COLS) {
+                const int b = p * BP + bp;
+                if (b >= wv) break;
+                float rv[V][n], Yv[V][M];
 #pragma unroll
-    for (int no = 0; no < NO; ++no)
+                for (int ii = 0; ii < n; ++ii) {
+                    const float *src = Rs + (ii * BP + bp) * RSW + tl * RS + ch;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+                    for (int v = 0; v < V; ++v) rv[v][ii] = src[v];
 #pragma unroll
-            for (int p = 0; p < M / BP; ++p) {
-                if (!first) __syncthreads();
-                first = false;
+                    for (int k2 = 1; k2 < KS; ++k2)
 #pragma unroll
-                for (int bp = 0; bp < BP; ++bp)
-                    *reinterpret_cast<float4 *>(&Rs[w][bp][l16 * RS_STRIDE + 4 * q]) =
-                        R[p * BP + bp][no][nt];
-                __syncthreads();
-                for (int idx = tid < NTH ? tid : BP * 256; idx < BP * 256; idx += NTH) {
-                    const int bp = idx >> 8;   // idx & 255 == tid & 255 for every iteration
-                    const int bcol = p * BP + bp;
-                    float Yv[M], rv[n];
+                        for (int v = 0; v < V; ++v) rv[v][ii] += src[k2 * n * BP * RSW + v];
+                }
 #pragma unroll
-                    for (int ii = 0; ii < n; ++ii) {
-                        rv[ii] = Rs[ii][bp][tl * RS_STRIDE + ol];
+                for (int v = 0; v < V; ++v) {
+                    if (M == 4 && a.dense_rows) wq_apply_at<M, false>(a.xf, rv[v], Yv[v]);
+                    else wq_apply_at<M, ATSP>(a.xf, rv[v], Yv[v]);
+                }
+                float *const dst = base + b * a.Cout;
 #pragma unroll
-                        for (int k2 = 1; k2 < KS; ++k2) rv[ii] += Rs[k2 * n + ii][bp][tl * RS_STRIDE + ol];
-                    }
-                    wq_apply_at<M, ATSP>(a.xf, rv, Yv);
-                    const int hv = out_lim[nt] & 0xff, wv = out_lim[nt] >> 8;
-                    const int o = o0 + no * 16 + ol;
-                    if (bcol < wv && o < a.Cout) {
-                        float *dst = a.y + (size_t)out_off[nt] + bcol * a.Cout + o;
+                for (int aa = 0; aa < M; ++aa) {
+                    if (aa >= hv) break;
+                    float *d = dst + (size_t)aa * a.W * a.Cout;
+                    typedef float vec_t __attribute__((ext_vector_type(V)));
+                    vec_t out;
 #pragma unroll
-                        for (int aa = 0; aa < M; ++aa)
-                            if (aa < hv)   // streaming store: y is not read again by this layer
-                                store_y(Yv[aa] + bias_v[no],
-                                                            &dst[(size_t)aa * a.W * a.Cout]);
-                    }
+                    for (int v = 0; v < V; ++v) out[v] = Yv[v][aa] + bias[v];
+                    if constexpr (decltype(plain)::value) *reinterpret_cast<vec_t *>(d) = out;
+                    else store_y(out, reinterpret_cast<vec_t *>(d));
                 }
             }
+        }
+    };
+    // four channels per thread where every pixel's channels start at a multiple of 16 bytes, otherwise one:
+    // scalar stores of a lane's four channels would be scattered
+    const bool vec4 = (a.Cout & 3) == 0;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int p = 0; p < M / BP; ++p) {
+            __syncthreads();   // the scales, or the tiles before, have been read
+#pragma unroll
+            for (int bp = 0; bp < BP; ++bp)
+#pragma unroll
+                for (int no = 0; no < NO; ++no)
+                    *reinterpret_cast<float4 *>(&Rs[(w * BP + bp) * RSW + l16 * RS + 16 * no + 4 * q]) = R[p * BP + bp][no][nt];
+            __syncthreads();
+            constexpr std::integral_constant<int, NO == 2 ? 4 : 1> many;
+            constexpr std::integral_constant<int, 1> one;
+            if (!vec4) finish(one, std::false_type{}, nt, p);
+            else if (a.plain_y) finish(many, std::true_type{}, nt, p);   // (a branch at the store would be merged)
+            else finish(many, std::false_type{}, nt, p);
+        }
 }
 
-template <int M, bool K64, bool CPG1, bool WIDE, bool ATSP, int NT, int NO, int KS, int D>
-hipError_t launch_cfg(const Args &a, hipStream_t s) {
+template <int M, bool K64, bool CPG1, bool WIDE, bool ATSP, int NT, int NO, int KS, int D, bool ONE>
+hipError_t launch_one(const Args &a, hipStream_t s) {
     // the debug entry point runs the same template with the stores of the int32 sums compiled in
     Args b = a;
     b.nTB = a.T_pad / (16 * NT);
     b.nOB = a.Cout_pad / (16 * NO);
     b.xcd_mode = wq_fused_xcd_mode(a.T_pad, a.Cout_pad, a.Cin, M + 2, b.nOB);
+    {   // all blocks where they fit an XCD's 4 MB L2 (all taps of them), otherwise bands of 1 MB
+        const long bytes = (long)(M + 2) * (M + 2) * a.Cin * 16 * (b.xcd_mode == 0 ? NT : NO);
+        const int others = b.xcd_mode == 0 ? b.nTB : b.nOB;
+        b.band = others * bytes <= (4L << 20) ? others : max(1, (int)((1L << 20) / bytes));
+    }
     const int split = b.xcd_mode == 0 ? b.nOB : b.nTB, other = b.xcd_mode == 0 ? b.nTB : b.nOB;
     const unsigned grid = b.xcd_mode == 2 ? (unsigned)(((b.nTB + 3) / 4) * ((b.nOB + 1) / 2) * 8)
                                           : (unsigned)(((split + 7) / 8) * 8 * other);
     if (a.dump.P)
-        hipLaunchKernelGGL((k_contract_output<M, K64, CPG1, WIDE, ATSP, true, NT, NO, KS, D>), dim3(grid),
+        hipLaunchKernelGGL((k_contract_output<M, K64, CPG1, WIDE, ATSP, true, NT, NO, KS, D, ONE>), dim3(grid),
                            dim3(64 * (M + 2) * KS), 0, s, b);
     else
-        hipLaunchKernelGGL((k_contract_output<M, K64, CPG1, WIDE, ATSP, false, NT, NO, KS, D>), dim3(grid),
+        hipLaunchKernelGGL((k_contract_output<M, K64, CPG1, WIDE, ATSP, false, NT, NO, KS, D, ONE>), dim3(grid),
                            dim3(64 * (M + 2) * KS), 0, s, b);
     return hipGetLastError();
 }
 
-// fp64 chunk totals only where a wave reduces more than 8 groups per tap
+template <int M, bool K64, bool CPG1, bool WIDE, bool ATSP, int NT, int NO, int KS, int D>
+hipError_t launch_cfg(const Args &a, hipStream_t s) {
+    // The exchange of all columns at once is a pass less, of half of them half the LDS, which lets more
+    // workgroups of F(6,3) onto a CU (F(4,3)'s fit as they are): where there are any more than two.
+    if constexpr (M == 6 && NT * NO == 1 && KS == 1 && CPG1) {
+        if ((long)(a.T_pad / 16) * (a.Cout_pad / 16) <= 512 || (a.Cin >> a.log2g) <= 2) return launch_one<M, K64, CPG1, WIDE, ATSP, NT, NO, KS, D, true>(a, s);
+    }
+    constexpr bool one = NO == 1 && M != 6;
+    return launch_one<M, K64, CPG1, WIDE, ATSP, NT, NO, KS, D, one>(a, s);
+}
+
+// fp64 chunk totals only where a wave reduces more than the plan's fp32_groups (8 or 16) per tap
 template <int M, bool K64, bool CPG1, bool ATSP>
 hipError_t launch_base(const Args &a, hipStream_t s, bool wide) {
     return wide ? launch_cfg<M, K64, CPG1, true, ATSP, 1, 1, 1, kDepth<M, 1, 1>>(a, s)
@@ -419,8 +522,8 @@ hipError_t launch_fast(const Args &a, hipStream_t s, int variant, bool wide) {
         return wide ? launch_cfg<M, K64, true, true, true, 1, 1, 2, kDepth<M, 1, 1>>(a, s)
                     : launch_cfg<M, K64, true, false, true, 1, 1, 2, kDepth<M, 1, 1>>(a, s);
     if (variant == WQ_K2_FUSED_32x16)
-        return wide ? launch_cfg<M, K64, true, true, true, 2, 1, 1, kDepth<M, 2, 1>>(a, s)
-                    : launch_cfg<M, K64, true, false, true, 2, 1, 1, kDepth<M, 2, 1>>(a, s);
+        return wide ? launch_cfg<M, K64, true, true, true, 2, 1, 1, kDepth<M, 2, 1, K64>>(a, s)
+                    : launch_cfg<M, K64, true, false, true, 2, 1, 1, kDepth<M, 2, 1, K64>>(a, s);
     return wide ? launch_cfg<M, K64, true, true, true, 2, 2, 1, kDepth<M, 2, 2>>(a, s)
                 : launch_cfg<M, K64, true, false, true, 2, 2, 1, kDepth<M, 2, 2>>(a, s);
 }
@@ -436,10 +539,15 @@ hipError_t launch_m(const wq_plan *p, hipStream_t s, const int8_t *Xq, const flo
     a.T = p->T; a.T_pad = p->T_pad; a.Cout_pad = p->Cout_pad;
     a.log2g = 0;
     while ((1 << a.log2g) < p->g) ++a.log2g;
-    a.nTB = a.nOB = a.xcd_mode = 0;
+    a.nTB = a.nOB = a.xcd_mode = a.band = 0;
+    {   // see finish
+        const long long bytes = (long long)p->N * p->H * p->W * p->Cout * 4;
+        a.plain_y = M == 4 && p->k2_variant == WQ_K2_FUSED_32x32 && bytes >= (32LL << 20) && bytes <= (64LL << 20);
+    }
     const bool k64 = p->kstep == 64, cpg1 = p->g == p->kstep;
     const int variant = p->k2_variant;   // a fused one, checked for this plan when it was chosen
-    const bool wide = p->groups / (variant == WQ_K2_FUSED_KSPLIT ? 2 : 1) > 8;
+    const bool wide = p->groups / (variant == WQ_K2_FUSED_KSPLIT ? 2 : 1) > p->fp32_groups;
+    a.dense_rows = p->dense_rows;
     if constexpr (M != 2) {
         if (variant != WQ_K2_FUSED_16x16)
             return k64 ? launch_fast<M, true>(a, s, variant, wide) : launch_fast<M, false>(a, s, variant, wide);

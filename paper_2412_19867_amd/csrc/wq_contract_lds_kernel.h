@@ -72,15 +72,7 @@ struct LArgs {
     int plain_stores;
 };
 
-#define WQ_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-
-// Buffer loads whose destination is LDS: lane l's 16 (4) bytes land at lds + 16 l (4 l); `lds` and
-// `soff` are wave-uniform.  Completion is counted by the wave's vector-memory counter.  (Plain
-// device functions on purpose: called from a lambda inside the kernel template, the builtin makes
-// the host pass drop the kernel's launch stub without a diagnostic.)
-__device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, char *lds, unsigned voff, unsigned soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, WQ_LDS_PTR(lds), 16, voff, soff, 0, 0);
-}
+// the same for 4 bytes per lane
 __device__ __forceinline__ void lds_load4(__amdgpu_buffer_rsrc_t r, char *lds, unsigned voff, unsigned soff) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, WQ_LDS_PTR(lds), 4, voff, soff, 0, 0);
 }

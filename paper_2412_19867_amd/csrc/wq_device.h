@@ -98,3 +98,22 @@ template <int R>
 __device__ __forceinline__ float quad_bcast(float v) {   // lane 4k + R of every quad to its four lanes
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), R * 0x55, 0xf, 0xf, true));
 }
+
+#define WQ_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+
+// Buffer loads whose destination is LDS: lane l's 16 bytes land at lds + 16 l; `lds` and
+// `soff` are wave-uniform.  Completion is counted by the wave's vector-memory counter.  (Plain
+// device functions on purpose: called from a lambda inside the kernel template, the builtin makes
+// the host pass drop the kernel's launch stub without a diagnostic.)
+__device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, char *lds, unsigned voff, unsigned soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, WQ_LDS_PTR(lds), 16, voff, soff, 0, 0);
+}
+
+// s_waitcnt until at most VM of the wave's vector-memory operations are outstanding (they complete in
+// order); the "memory" clobber keeps LDS accesses behind it.  (gfx9 encoding: vmcnt in bits 3:0 and 15:14,
+// the other counters left alone.)
+template <int VM>
+__device__ __forceinline__ void wait_loads() {
+    static_assert(VM >= 0 && VM < 64, "vmcnt is a 6-bit counter");
+    asm volatile("s_waitcnt %0" ::"n"(0x0f70 | (VM & 0xf) | ((VM >> 4) << 14)) : "memory");
+}

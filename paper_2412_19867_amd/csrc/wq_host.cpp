@@ -187,6 +187,52 @@ long fused_xcd_load(const wq_plan *p, int nt, int no) {
     }
 }
 
+// layers of the row form's size: 64 tiles x 64 channels x one tap row fill the GPU once at two to three
+// workgroups per CU, or are large in tiles AND output channels, where the Winograd-domain product of the
+// two-kernel forms would reach hundreds of MB
+bool row_form_layer(const wq_plan *p) {
+    if (p->m == 2 || p->g != p->kstep || p->groups < 8) return false;
+    const long wgs = (long)((p->T_pad + 63) / 64) * ((p->Cout_pad + 63) / 64) * (p->m + 2);
+    return wgs >= 384 && (wgs <= 768 || (p->T_pad >= 1024 && p->Cout_pad >= 512));
+}
+
+// layers of the full LDS form's size: many tiles and a short reduction
+bool full_form_layer(const wq_plan *p) {
+    if (p->m != 4 || p->g != p->kstep || p->groups > 6 || p->Cout % 4 != 0) return false;
+    if (p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128))) return false;
+    return (long)((p->T_pad + 31) / 32) * ((p->Cout_pad + 31) / 32) >= 512;
+}
+
+// The fused kernel's tile of a workgroup: one, two or four blocks of 16 tiles x 16 channels.  More blocks
+// read fewer operand bytes per product, and leave fewer workgroups to share out.  A launch is as slow as the
+// XCD with the most of it (32 CUs): `one`, `four` = workgroups there.  (us of the forward with one, two, four
+// blocks, from 200 layers drawn over the sizes of UNet and ResNet layers)
+int fused_tile(const wq_plan *p) {
+    const int G = p->groups;
+    const long one = fused_xcd_load(p, 1, 1), four = fused_xcd_load(p, 2, 2);
+    // a block each while every workgroup gets a CU of its own (28 tile blocks x 6, G 7: 19.2, 23.4, 26.7), and
+    // with a group or two per tap, whose operands a bigger tile hardly re-reads less (F(4,3) 380 x 6, G 2: 41,
+    // 43, 49; 98 x 60, G 1: 45, 54, 53)
+    if (one <= 32) return WQ_K2_FUSED_16x16;
+    if (p->m == 4) {   // two workgroups of four blocks fit a CU, 64 an XCD
+        if (G <= 2 || (G == 3 && one <= 96)) return WQ_K2_FUSED_16x16;   // 62 x 12, G 3: 18.1, 20.1, 18.5
+        if (G == 3) return WQ_K2_FUSED_32x16;                            // 234 x 26: 70, 68, 73
+        if (G == 4) return four > 45 && four <= 64 ? WQ_K2_FUSED_32x32 : WQ_K2_FUSED_32x16;   // 176 x 10: 47, 45, 42
+        // with more groups four blocks once half of the CUs have them (38 x 12, G 11: 37, 32.5, 37; 62 x 78, G 7: 137,
+        // 116, 98; 38 x 24, G 6: 27.8, 26.5, 22.6), unless the last ones are a second workgroup on few CUs (44 x 30,
+        // G 8: 62, 50, 52) or a few more than fit at once (34 x 64, G 20: 136, 116, 118; 36 x 50, G 24: 154, 122, 140)
+        const long over = four % 64;
+        return four <= 16 || (four > 32 && four <= 45) || (four > 64 && over >= 1 && over <= 8) ? WQ_K2_FUSED_32x16
+                                                                                                : WQ_K2_FUSED_32x32;
+    }
+    // F(6,3): one workgroup of four blocks fits a CU, 32 an XCD
+    if (G == 1) return four <= 42 ? WQ_K2_FUSED_16x16 : WQ_K2_FUSED_32x16;   // 132 x 34: 69.5, 69.6, 74
+    if (four <= 16) return G <= 3 ? WQ_K2_FUSED_16x16 : WQ_K2_FUSED_32x16;   // 36 x 12, G 4: 30, 29, 33
+    if (four <= 32) return WQ_K2_FUSED_32x32;                               // 222 x 4, G 3: 41, 39, 36
+    if (four <= 42) return G <= 3 ? WQ_K2_FUSED_16x16 : G == 4 ? WQ_K2_FUSED_32x16 : WQ_K2_FUSED_32x32;
+    return G == 2 ? WQ_K2_FUSED_32x16 : WQ_K2_FUSED_32x32;                  // 94 x 24, G 2: 51, 51, 56; 58 x 28, G 5: 81, 72, 63
+}
+
 int default_k2_variant(const wq_plan *p) {
     if (p->integer_transforms) {
         if (p->T_pad <= 32 || ((p->T_pad % 64) == 32 && p->T_pad <= 160)) return WQ_K2_GEMM_32x128;
@@ -195,18 +241,26 @@ int default_k2_variant(const wq_plan *p) {
     // The row form with operand tiles shared through LDS: measured ahead of the others where its
     // workgroups (64 tiles x 64 channels x one tap row) fill the GPU once at two to three per CU
     // and each of them walks a reduction long enough to pay for the second kernel.
-    if (variant_applicable(p, WQ_K2_LDS_ROW_64x64) && p->g == p->kstep && p->groups >= 8) {
-        const long wgs = (long)((p->T_pad + 63) / 64) * ((p->Cout_pad + 63) / 64) * (p->m + 2);
-        // also layers large in tiles AND output channels, where the Winograd-domain product the
-        // two-kernel forms write would reach hundreds of MB
-        if (wgs >= 384 && (wgs <= 768 || (p->T_pad >= 1024 && p->Cout_pad >= 512))) return WQ_K2_LDS_ROW_64x64;
-    }
+    // (not for F(6,3), whose fused kernel with four blocks is ahead: 100 tile blocks x 56, G 8 g 32, 425 against
+    // 252 us, 36 x 40, G 13, 132, 105; nor on fewer than 384 channels, where F(4,3)'s is: 250 x 8, G 17, 132,
+    // 120; but 84 x 24, G 25, 131, 152; nor up to eight groups, which a wave sums in fp32: 44 x 30, G 8, 62, 50;
+    // 54 x 34, G 9, 59, 75)
+    const bool row = row_form_layer(p);
+    if (row && p->m == 4 && p->Cout_pad >= 384 && p->groups >= 9) return WQ_K2_LDS_ROW_64x64;
     // With few tiles the Winograd-domain result is small next to the operands, and a tiled GEMM
     // per tap plus a separate output transform beats the fused kernel; so it does for very wide
     // layers and for groups of 128 and more, where the fused kernel's register tiles re-read the
     // operands too often.
-    const bool two_kernel = (p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128))) ||
-                            p->Cin >= 1024 || p->g >= 128;
+    // (Groups of 32: up to a handful of groups the fused kernel's one launch is ahead once its blocks fill
+    // half of the CUs, later for the longer rows of F(6,3): F(4,3) 6 x 22 tile and channel blocks, G 5, 14.1
+    // against 12.3 us; 2 x 6, G 6, 12.5, 12.9; 14 x 16, G 13, 22.6, 23.3; F(6,3) 26 x 8, G 7, 27, 22.4; 14 x 6,
+    // G 7, 20.7, 21.3; 16 x 34, G 4, 34.7, 27; 26 x 6, G 12, 28.7, 30.5)
+    const long blocks = (long)(p->T_pad / 16) * (p->Cout_pad / 16);
+    const bool few_groups = p->m != 2 && p->T_pad >= 128 && !((p->T_pad % 64) == 32 && p->T_pad <= 160) &&
+                            (p->m == 4 ? p->groups <= 5 || (p->groups == 6 && blocks >= 60)
+                                       : (p->groups <= 6 && blocks >= 90) || (p->groups <= 8 && blocks >= 180));
+    const bool two_kernel = !row && ((p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128 && !few_groups))) ||
+                                     p->Cin >= 1024 || p->g >= 128);
     // one group of 128 or 256 per tap: nothing is re-read between groups, and the product of a tap
     // written out costs more than the fused kernel's one block per wave (22x54x54 128->96 F(2,3) 48
     // against 69 us, 10x20x20 128->70 F(4,3) 12.5 against 13.9; F(6,3)'s 64 taps go either way; a
@@ -220,7 +274,7 @@ int default_k2_variant(const wq_plan *p) {
     // against 69); F(2,3) at 512 loses only to the 128x128 tiles below, on more than 256 channels
     // (3x75x75 512->512 130 against 119; 9x73x73 512->230 227 against 263)
     if (p->g >= 128 && p->groups == 1 && p->m != 6) {
-        const long blocks = (long)(p->T_pad / 16) * (p->Cout_pad / 16), taps = p->n * p->n;
+        const long taps = p->n * p->n;
         const bool in_l2 = wq_fused_xcd_mode(p->T_pad, p->Cout_pad, p->Cin, p->n, p->Cout_pad / 16) != 0 ||
                            (p->T_pad + p->Cout_pad / 8) * taps * p->Cin <= (4L << 20);
         if (p->m == 2 ? blocks >= 64 && (p->g <= 256 || p->T_pad < 1024 || p->Cout_pad <= 256)
@@ -238,62 +292,18 @@ int default_k2_variant(const wq_plan *p) {
             return WQ_K2_LDS_TAP_64x64;
         return WQ_K2_GEMM_64x64;
     }
-    // Many tiles and a short reduction (the 128 x 128, 320-channel layer): one 16x16 block per wave with
-    // the operands shared through LDS, four workgroups of 32 tiles x 32 channels per CU.  A workgroup
-    // walks all n*n taps in sequence, so the reduction must be short and the workgroups must fill
-    // the GPU at least twice over; the fused kernel below has the same traffic but fewer, fatter waves.
-    // Its lanes store four channels each: with Cout not a multiple of 4 those stores are scalar and
-    // scattered (5x79x68 128->654: 242 against 66 us of the fused kernel, whose lanes store a row).
-    if (p->m == 4 && p->g == p->kstep && p->Cout % 4 == 0 && variant_applicable(p, WQ_K2_LDS_FULL_32x32)) {
-        const long wgs = (long)((p->T_pad + 31) / 32) * ((p->Cout_pad + 31) / 32);
-        if (wgs >= 512 && p->groups <= 6) return WQ_K2_LDS_FULL_32x32;
-    }
+    // two groups per tap and output far beyond the caches: the full LDS form, whose plain stores fill whole lines
+    // (32x56x56 128->256 71.5 us, fused 74.4, 75.5, 76.1 with one, two, four blocks; 8x96x96 58.6, 55.4, 58.3, 56.7)
+    if (full_form_layer(p) && p->groups == 2 && p->T_pad >= 6144) return WQ_K2_LDS_FULL_32x32;
     if (!variant_applicable(p, WQ_K2_FUSED_32x16)) return WQ_K2_FUSED_16x16;
-    // The fused kernel's tile of a workgroup, in blocks of 16 tiles x 16 channels (us of the forward):
-    const long tb = p->T_pad / 16, ob = p->Cout_pad / 16;
-    const bool can_split = p->groups % 2 == 0 && p->groups >= 4;
-    if (tb <= 2) return can_split ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
-    // a single group per tap leaves a bigger tile nothing to reuse (12x80x90 64->416 F(6,3): one block
-    // 73, two 87, four 83)
-    if (p->groups == 1) return WQ_K2_FUSED_16x16;
-    // a launch is as slow as the XCD with the most of it (32 CUs): workgroups there, by tile
-    const long one = fused_xcd_load(p, 1, 1), two = fused_xcd_load(p, 2, 1), four = fused_xcd_load(p, 2, 2);
-    if (p->m == 4) {
-        // a block each where every workgroup gets a CU of its own: more and shorter waves (2x97x67 256->64:
-        // one block 18, two 23; 12x29x26 224->96, 36 on an XCD: 24.5, 21.7).  Split in two where a wave still
-        // reduces three groups, up to five (3x20x20 384->480: split 15.7, one block 16.7).  Longer slices are
-        // longer chains of fp32 additions than the one wave's fp64 totals of four (relative error of
-        // 1x93x101 896->33: split 6.8e-7, one wave 6.3e-7; 33.2 and 35.1 us; of 3x60x82 640->64, slices of
-        // five: 6.2e-7, 6.3e-7; 30.0 and 31.7 us)
-        if (one <= 32) return (can_split && p->groups >= 6 && p->groups <= 10) ? WQ_K2_FUSED_KSPLIT : WQ_K2_FUSED_16x16;
-        // and where they fit the CUs at once, three on each, but pairs would not, one on each (one block,
-        // two: 1x70x48 128->576 15.9, 18.0; 4x40x52 256->256 22.0, 23.5; 1x54x67 96->608 17.9, 20.0; where
-        // pairs do: 3x70x86 320->96 25.1, 24.1; 25x31x21 640->71 43.5, 39.4; where blocks do not: 30x15x15
-        // 192->406 24.2, 23.4)
-        if (two > 32 && one <= 96) return WQ_K2_FUSED_16x16;
-    }
-    if (tb * ob >= 600) {
-        // four blocks pay for their registers on wide layers (14x32x32 128->1074 F(6,3): two blocks 101,
-        // four 97; 5x27x27 448->896 33, 30), and on others with groups of 64 where a tap reduces enough of
-        // them and their workgroups fill the CUs evenly: once or many times (two blocks, four)
-        //   F(6,3), 4 groups   one on a CU: 2x61x102 256->416 41.7, 34.5; 5x64x64 704->256 88, 72; a few
-        //                      more: 11x46x70 256->215, 36 on an XCD, 65, 82; 378 in all: 28x68x68 256->88
-        //                      99, 106; from three on a CU: 18x78x78 256->256 127, 109
-        //   F(4,3), 7 groups   one on a CU: 8x47x43 576->192 49, 45; with 4: 5x41x58 256->206 26.7, 29.2; a few
-        //                      more: 1x82x66 384->544, 36 on an XCD, 32, 45; four and a half on a CU:
-        //                      18x59x59 512->320 174, 164; 12x62x62 576->480 217, 193; less: 4x114x114
-        //                      512->293 155, 173; with 4: 28x40x46 256->485 128, 164
-        //            10 groups three on a CU: 2x119x128 768->416 173, 158; 15x38x45 640->480 155, 135
-        //   groups of 32       go either way: 28x33x33 128->163 F(6,3) 38, 45; 2x68x68 576->352 F(4,3) 61, 54
-        const long quads = tb * ob / 4;
-        if (ob >= 40 && (p->groups >= 4 || p->m == 6)) return WQ_K2_FUSED_32x32;
-        if (p->g == 64 && (p->m == 6 ? p->groups >= 4 && (four <= 32 || quads >= 768)
-                                     : (p->groups >= 7 && (four <= 32 || quads >= 1152)) ||
-                                           (p->groups >= 10 && quads >= 768)))
-            return WQ_K2_FUSED_32x32;
-        return WQ_K2_FUSED_32x16;
-    }
-    return tb >= 16 ? WQ_K2_FUSED_32x16 : WQ_K2_FUSED_16x16;
+    // a wave's reduction split in two where every block has a CU of its own and the slices are short: up to five
+    // groups each, since longer slices are longer chains of fp32 additions than the one wave's fp64 totals of four
+    // (relative error of 1x93x101 896->33: split 6.8e-7, one wave 6.3e-7)
+    // (the layers that few_groups took from the two-kernel forms keep those forms' one chain)
+    if (p->groups % 2 == 0 && p->groups >= 4 && !(p->T_pad <= 512 && p->g == 32 && p->Cin >= 128) &&
+        (p->T_pad <= 32 || (p->m == 4 && p->groups >= 6 && p->groups <= 10 && fused_xcd_load(p, 1, 1) <= 32)))
+        return WQ_K2_FUSED_KSPLIT;
+    return fused_tile(p);
 }
 
 void publish_choices(wq_plan *p) {
@@ -388,6 +398,8 @@ wq_status_t wq_plan_create(wq_plan_t **out, int N, int H, int W, int Cin, int Co
     p->wbits = 8;
     p->prepared.store(0);
     p->integer_transforms = 0;
+    p->dense_rows = full_form_layer(p);
+    p->fp32_groups = row_form_layer(p) ? 16 : 8;
     std::memset(&p->xi, 0, sizeof(p->xi));
     std::memset(&p->xf, 0, sizeof(p->xf));
     if (all) {

@@ -46,6 +46,12 @@ struct wq_plan {
     // the kernel instance of stages 2+3 (a wq_k2_variant_t) and the tap rows per workgroup of the
     // input kernel, picked from the shape when the plan is made (wq_plan_tune overrides them)
     int k2_variant, k1_rows;
+    // How the fused kernel sums, fixed by the layer and not by the variant that runs it, because a layer that
+    // quantizes its input again turns another rounding into other codes (a relative 1e-7 after one layer of a
+    // 128 x 128, 320-channel stack is 3e-2 after four): the tap rows of y in one ascending chain, as the full
+    // LDS form does, or with paired columns; and the most groups a wave adds up in fp32 alone.
+    bool dense_rows;
+    int fp32_groups;
     // 0: fp32 transforms (the path of the second quantized-stage equation alone); 1 / 2: integer
     // input and output transforms with one scale per transform matrix / per matrix row
     int integer_transforms;
