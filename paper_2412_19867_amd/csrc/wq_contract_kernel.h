@@ -508,7 +508,7 @@ hipError_t launch_cfg(const Args &a, hipStream_t s) {
     return launch_one<M, K64, CPG1, WIDE, ATSP, NT, NO, KS, D, one>(a, s);
 }
 
-// fp64 chunk totals only where a wave reduces more than the plan's fp32_groups (8 or 16) per tap
+// fp64 chunk totals only where a wave reduces more than the plan's fp32_groups per tap
 template <int M, bool K64, bool CPG1, bool ATSP>
 hipError_t launch_base(const Args &a, hipStream_t s, bool wide) {
     return wide ? launch_cfg<M, K64, CPG1, true, ATSP, 1, 1, 1, kDepth<M, 1, 1>>(a, s)

@@ -300,13 +300,20 @@ int default_k2_variant(const wq_plan *p) {
     // groups each, since longer slices are longer chains of fp32 additions than the one wave's fp64 totals of four
     // (relative error of 1x93x101 896->33: split 6.8e-7, one wave 6.3e-7)
     // (the layers that few_groups took from the two-kernel forms keep those forms' one chain)
-    if (p->groups % 2 == 0 && p->groups >= 4 && !(p->T_pad <= 512 && p->g == 32 && p->Cin >= 128) &&
-        (p->T_pad <= 32 || (p->m == 4 && p->groups >= 6 && p->groups <= 10 && fused_xcd_load(p, 1, 1) <= 32)))
+    if (p->groups % 2 == 0 && p->groups >= 4 && p->groups <= 10 && !(p->T_pad <= 512 && p->g == 32 && p->Cin >= 128) &&
+        (p->T_pad <= 32 || (p->m == 4 && p->groups >= 6 && fused_xcd_load(p, 1, 1) <= 32)))
         return WQ_K2_FUSED_KSPLIT;
     return fused_tile(p);
 }
 
-void publish_choices(wq_plan *p) {
+// Makes `variant` (WQ_K2_AUTO: the plan's own pick) the kernel of stages 2+3.  A fused kernel that the plan puts in
+// the row form's place adds up what that form does in fp32, 16 groups, so that the layer keeps its bits; one that the
+// caller asks for takes fp64 totals above 8 as on any other layer (relative error of a tap of 12 groups 5.4e-8, in
+// fp32 alone 6.9e-8; of 16, 5.4e-8 and 7.8e-8).
+void choose_variant(wq_plan *p, int variant) {
+    const bool own = variant == WQ_K2_AUTO;
+    p->k2_variant = own ? default_k2_variant(p) : variant;
+    p->fp32_groups = own && row_form_layer(p) ? 16 : 8;
     p->lay.k2_variant = p->k2_variant;
     p->lay.k1_rows = p->k1_rows;
     p->lay.k2_kernels = (wq_is_gemm_variant(p->k2_variant) || wq_is_lds_row_variant(p->k2_variant) ||
@@ -399,7 +406,6 @@ wq_status_t wq_plan_create(wq_plan_t **out, int N, int H, int W, int Cin, int Co
     p->prepared.store(0);
     p->integer_transforms = 0;
     p->dense_rows = full_form_layer(p);
-    p->fp32_groups = row_form_layer(p) ? 16 : 8;
     std::memset(&p->xi, 0, sizeof(p->xi));
     std::memset(&p->xf, 0, sizeof(p->xf));
     if (all) {
@@ -437,8 +443,7 @@ wq_status_t wq_plan_create(wq_plan_t **out, int N, int H, int W, int Cin, int Co
     L.ws_bytes = L.ws_M_off + align256(n2 * p->T_pad * p->Cout_pad * 4);
     L.debug_P_bytes = n2 * (uint64_t)T * p->groups * Cout * 4;
     p->k1_rows = default_k1_rows(p);
-    p->k2_variant = default_k2_variant(p);
-    publish_choices(p);
+    choose_variant(p, WQ_K2_AUTO);
     *out = p;
     return WQ_OK;
 }
@@ -464,8 +469,7 @@ wq_status_t wq_plan_tune(wq_plan_t *plan, int k1_rows, int k2_variant) {
     if (plan->integer_transforms && k1_rows != 0 && k1_rows != plan->n) return WQ_ERR_UNSUPPORTED;
     if (k2_variant != WQ_K2_AUTO && !variant_applicable(plan, k2_variant)) return WQ_ERR_UNSUPPORTED;
     plan->k1_rows = k1_rows ? k1_rows : (plan->integer_transforms ? plan->n : default_k1_rows(plan));
-    plan->k2_variant = k2_variant != WQ_K2_AUTO ? k2_variant : default_k2_variant(plan);
-    publish_choices(plan);
+    choose_variant(plan, k2_variant);
     return WQ_OK;
 }
 
@@ -506,8 +510,7 @@ wq_status_t wq_plan_set_integer_transforms(wq_plan_t *plan, int mode) {
     } else {
         plan->k1_rows = default_k1_rows(plan);
     }
-    plan->k2_variant = default_k2_variant(plan);
-    publish_choices(plan);
+    choose_variant(plan, WQ_K2_AUTO);
     return WQ_OK;
 }
 

@@ -46,10 +46,11 @@ struct wq_plan {
     // the kernel instance of stages 2+3 (a wq_k2_variant_t) and the tap rows per workgroup of the
     // input kernel, picked from the shape when the plan is made (wq_plan_tune overrides them)
     int k2_variant, k1_rows;
-    // How the fused kernel sums, fixed by the layer and not by the variant that runs it, because a layer that
-    // quantizes its input again turns another rounding into other codes (a relative 1e-7 after one layer of a
-    // 128 x 128, 320-channel stack is 3e-2 after four): the tap rows of y in one ascending chain, as the full
-    // LDS form does, or with paired columns; and the most groups a wave adds up in fp32 alone.
+    // How the fused kernel sums where the plan picks it in another form's place: like that form, because a layer
+    // that quantizes its input again turns another rounding into other codes (a relative 1e-7 after one layer of a
+    // 128 x 128, 320-channel stack is 3e-2 after four).  The tap rows of y in one ascending chain, as the full
+    // LDS form does, or with paired columns; and the most groups a wave adds up in fp32 alone (8, more precise than
+    // the row form's 16, wherever the caller picks the variant).
     bool dense_rows;
     int fp32_groups;
     // 0: fp32 transforms (the path of the second quantized-stage equation alone); 1 / 2: integer

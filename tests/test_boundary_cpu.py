@@ -391,3 +391,15 @@ def test_every_wave_of_the_quantized_gemm_has_a_group(wq, groups, g):
                 assert waves == 1 or waves == groups == 3
                 launched = -(-P // pixels) * -(-Cout // channels)
                 assert channels * pixels == 256 or launched >= 400
+
+
+def test_a_split_reduction_has_slices_of_at_most_five_groups(wq):
+    """A plan never picks two waves per tap row with longer slices, which would be longer chains of fp32 additions
+    than one wave's (few tiles and thousands of channels, where nothing else fills the GPU, among them)."""
+    for m in (4, 6):
+        for g in (32, 64):
+            for groups in range(2, 41, 2):
+                for (N, H, W) in ((1, 8, 8), (1, 16, 16), (1, 18, 18), (1, 30, 30), (2, 40, 44)):
+                    for Cout in (32, 96, 640, 2048, 3072, 5120):
+                        plan = wq.Plan(N, H, W, g * groups, Cout, m, g)
+                        assert plan.k2_variant_name != "fused_ksplit" or groups <= 10, (N, H, W, Cout, m, g, groups)

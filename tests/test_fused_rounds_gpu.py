@@ -36,25 +36,58 @@ def test_rounds_bands_and_passes(shape):
     assert ran >= 1
 
 
-@pytest.mark.parametrize("shape,other", [
-    ((1, 128, 128, 64, 512, 4, 32), "lds_full_32x32"), ((1, 126, 127, 192, 512, 4, 64), "lds_full_32x32"),
-    ((1, 128, 126, 288, 256, 4, 32), "lds_row_64x64"), ((1, 125, 128, 512, 256, 4, 64), "lds_row_64x64"),
-    ((2, 64, 62, 128, 96, 4, 32), "lds_tap_64x64"),
-], ids=lambda v: v if isinstance(v, str) else "%dx%dx%d_%d-%d_F%d_g%d" % v)
-def test_the_sums_of_a_layer_do_not_depend_on_the_form_that_runs_it(shape, other):
-    """Layers that a chain quantizes again: every fused tile gives the bits of the LDS form of their size."""
+ALL_TILES = ("fused_16x16", "fused_32x16", "fused_32x32")
+
+
+def forward_with(shape, variant, x, w, bias):
+    plan = wqmod.Plan(*shape).tune(0, variant)
+    blob, ws = plan.alloc_blob(), plan.alloc_workspace()
+    plan.weight_prepare(w, bias, blob)
+    y = torch.full((shape[0], shape[1], shape[2], shape[4]), float("nan"), device="cuda")
+    plan.forward(x, blob, ws, y)
+    return plan.k2_variant_name, y
+
+
+def inputs(shape):
     N, H, W, Cin, Cout, m, g = shape
     gen = torch.Generator(device="cuda").manual_seed(5)
-    x = torch.randn((N, H, W, Cin), generator=gen, device="cuda")
-    plan = wqmod.Plan(*shape)
-    blob, ws = plan.alloc_blob(), plan.alloc_workspace()
-    plan.weight_prepare(torch.randn((Cout, Cin, 3, 3), generator=gen, device="cuda"),
-                        torch.randn(Cout, generator=gen, device="cuda"), blob)
-    got = {}
-    for variant in (other, "fused_16x16", "fused_32x16", "fused_32x32"):
-        plan.tune(0, variant)
-        y = torch.full((N, H, W, Cout), float("nan"), device="cuda")
-        plan.forward(x, blob, ws, y)
-        got[variant] = y
-    for variant, y in got.items():
-        assert torch.equal(y, got[other]), variant
+    return (torch.randn((N, H, W, Cin), generator=gen, device="cuda"), torch.randn((Cout, Cin, 3, 3), generator=gen, device="cuda"),
+            torch.randn(Cout, generator=gen, device="cuda"))
+
+
+# (a fused tile the caller picks on a layer of the row form's size sums more precisely than that form above 8 groups:
+# there only the plan's own pick has its bits)
+@pytest.mark.parametrize("shape,other,forms", [
+    ((1, 128, 128, 64, 512, 4, 32), "lds_full_32x32", ALL_TILES), ((1, 126, 127, 192, 512, 4, 64), "lds_full_32x32", ALL_TILES),
+    ((1, 128, 126, 288, 256, 4, 32), "lds_row_64x64", ("auto",)), ((1, 125, 128, 512, 256, 4, 64), "lds_row_64x64", ALL_TILES),
+    ((2, 64, 62, 128, 96, 4, 32), "lds_tap_64x64", ALL_TILES),
+    # F(6,3), whose output transform cancels most: below, at and above the row form's 16 groups of fp32
+    ((1, 96, 94, 288, 768, 6, 32), "lds_row_64x64", ("auto",)), ((1, 94, 96, 512, 768, 6, 32), "lds_row_64x64", ("auto",)),
+    ((1, 96, 96, 544, 768, 6, 32), "lds_row_64x64", ("auto",) + ALL_TILES),
+], ids=lambda v: v if isinstance(v, str) else "-".join(v) if isinstance(v[0], str) else "%dx%dx%d_%d-%d_F%d_g%d" % v)
+def test_the_sums_of_a_layer_do_not_depend_on_the_form_that_runs_it(shape, other, forms):
+    """Layers that a chain quantizes again: the fused kernel gives the bits of the LDS form of their size."""
+    data = inputs(shape)
+    want = forward_with(shape, other, *data)[1]
+    for form in forms:
+        name, y = forward_with(shape, form, *data)
+        assert torch.equal(y, want), name
+
+
+@pytest.mark.parametrize("shape", [(1, 128, 126, 288, 256, 4, 32), (1, 96, 96, 384, 768, 6, 32), (1, 96, 96, 576, 768, 6, 32)],
+                         ids=lambda s: "%dx%dx%d_%d-%d_F%d_g%d" % s)
+def test_a_fused_form_the_caller_picks_sums_alike_on_layers_of_every_size(shape):
+    """The fp64 totals above 8 groups of a wave do not go away where a layer is of the row form's size: the upper
+    half of the image, which is not, has the same bits (a tile's codes and sums depend on its own patch alone)."""
+    N, H, W, Cin, Cout, m, g = shape
+    x, w, bias = inputs(shape)
+    half = (N, H // 2, W, Cin, Cout, m, g)
+    rows = (H // 2 // m) * m - m      # output rows whose patches lie inside the upper half
+    for variant in FUSED:
+        try:
+            y = forward_with(shape, variant, x, w, bias)[1]
+        except wqmod.WqError as e:
+            assert variant == "fused_ksplit" and (Cin // g) % 2, e
+            continue
+        top = forward_with(half, variant, x[:, :H // 2].contiguous(), w, bias)[1]
+        assert torch.equal(y[:, :rows], top[:, :rows]), variant

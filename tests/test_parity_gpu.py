@@ -405,6 +405,7 @@ def test_adversarially_rounded_column_scales_take_the_dense_output_transform(wq)
     # N H  W    Cin Cout m g    (few workgroups: 14, 12, 10, 8 and 6 groups a tap)
     (1, 93, 101, 896, 33, 4, 64), (27, 18, 18, 448, 32, 4, 32), (18, 31, 31, 768, 32, 4, 64), (3, 60, 82, 640, 64, 4, 64),
     (3, 31, 93, 512, 57, 4, 64), (8, 25, 27, 384, 93, 4, 64),
+    (1, 18, 18, 2048, 3072, 6, 64),   # a handful of tiles, thousands of channels and 32 groups
 ], ids=lambda c: "%dx%dx%d_%d-%d_F%d_g%d" % c)
 def test_a_split_the_plan_picks_is_as_precise_as_one_wave(wq, case):
     """Distance from the fp64 result of the same codes and scales: the plan's own choice against one wave
