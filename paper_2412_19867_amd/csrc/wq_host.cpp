@@ -245,7 +245,10 @@ int default_k2_variant(const wq_plan *p) {
     // 252 us, 36 x 40, G 13, 132, 105; nor on fewer than 384 channels, where F(4,3)'s is: 250 x 8, G 17, 132,
     // 120; but 84 x 24, G 25, 131, 152; nor up to eight groups, which a wave sums in fp32: 44 x 30, G 8, 62, 50;
     // 54 x 34, G 9, 59, 75)
-    const bool row = row_form_layer(p);
+    // (layers that cannot run the fused kernel's tiles of two and four blocks, whose A^T has no paired columns, keep
+    // the form that runs any A^T: 28x25x34 704->384 F(6,3) 112 us, with one block 132)
+    const bool row = row_form_layer(p), tiles = variant_applicable(p, WQ_K2_FUSED_32x16);
+    if (row && !tiles) return WQ_K2_LDS_ROW_64x64;
     if (row && p->m == 4 && p->Cout_pad >= 384 && p->groups >= 9) return WQ_K2_LDS_ROW_64x64;
     // With few tiles the Winograd-domain result is small next to the operands, and a tiled GEMM
     // per tap plus a separate output transform beats the fused kernel; so it does for very wide
@@ -256,7 +259,7 @@ int default_k2_variant(const wq_plan *p) {
     // against 12.3 us; 2 x 6, G 6, 12.5, 12.9; 14 x 16, G 13, 22.6, 23.3; F(6,3) 26 x 8, G 7, 27, 22.4; 14 x 6,
     // G 7, 20.7, 21.3; 16 x 34, G 4, 34.7, 27; 26 x 6, G 12, 28.7, 30.5)
     const long blocks = (long)(p->T_pad / 16) * (p->Cout_pad / 16);
-    const bool few_groups = p->m != 2 && p->T_pad >= 128 && !((p->T_pad % 64) == 32 && p->T_pad <= 160) &&
+    const bool few_groups = tiles && p->T_pad >= 128 && !((p->T_pad % 64) == 32 && p->T_pad <= 160) &&
                             (p->m == 4 ? p->groups <= 5 || (p->groups == 6 && blocks >= 60)
                                        : (p->groups <= 6 && blocks >= 90) || (p->groups <= 8 && blocks >= 180));
     const bool two_kernel = !row && ((p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128 && !few_groups))) ||
@@ -294,8 +297,8 @@ int default_k2_variant(const wq_plan *p) {
     }
     // two groups per tap and output far beyond the caches: the full LDS form, whose plain stores fill whole lines
     // (32x56x56 128->256 71.5 us, fused 74.4, 75.5, 76.1 with one, two, four blocks; 8x96x96 58.6, 55.4, 58.3, 56.7)
-    if (full_form_layer(p) && p->groups == 2 && p->T_pad >= 6144) return WQ_K2_LDS_FULL_32x32;
-    if (!variant_applicable(p, WQ_K2_FUSED_32x16)) return WQ_K2_FUSED_16x16;
+    if (full_form_layer(p) && (!tiles || (p->groups == 2 && p->T_pad >= 6144))) return WQ_K2_LDS_FULL_32x32;
+    if (!tiles) return WQ_K2_FUSED_16x16;
     // a wave's reduction split in two where every block has a CU of its own and the slices are short: up to five
     // groups each, since longer slices are longer chains of fp32 additions than the one wave's fp64 totals of four
     // (relative error of 1x93x101 896->33: split 6.8e-7, one wave 6.3e-7)

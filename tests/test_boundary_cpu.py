@@ -403,3 +403,20 @@ def test_a_split_reduction_has_slices_of_at_most_five_groups(wq):
                     for Cout in (32, 96, 640, 2048, 3072, 5120):
                         plan = wq.Plan(N, H, W, g * groups, Cout, m, g)
                         assert plan.k2_variant_name != "fused_ksplit" or groups <= 10, (N, H, W, Cout, m, g, groups)
+
+
+@pytest.mark.parametrize("shape,variant", [
+    ((2, 112, 87, 416, 623, 6, 32), "lds_row_64x64"), ((19, 62, 62, 704, 50, 4, 64), "lds_row_64x64"),
+    ((28, 25, 34, 704, 384, 6, 64), "lds_row_64x64"), ((2, 128, 128, 320, 320, 4, 64), "lds_full_32x32"),
+    ((8, 96, 96, 128, 256, 4, 64), "lds_full_32x32"), ((2, 40, 40, 160, 320, 4, 32), "lds_tap_64x64"),
+    ((2, 64, 64, 192, 320, 6, 32), "lds_tap_64x64"), ((1, 32, 32, 64, 64, 4, 32), "fused_16x16"),
+], ids=lambda v: "%dx%dx%d_%d-%d_F%d_g%d" % v if isinstance(v, tuple) else v)
+def test_layers_whose_output_matrix_has_no_paired_columns_keep_the_forms_that_run_it(wq, shape, variant):
+    """The fused kernel's tiles of two and four blocks need paired columns of A^T; with its one block per wave
+    they are no reason to leave the row, full and tap forms."""
+    AT, BT, G = (np.array(M, np.float32) for M in ct.standard_matrices(shape[5]))
+    AT.view(np.uint32)[1::2, 2::2] += np.uint32(3)     # three ulps off the pairing
+    plan = wq.Plan(*shape, AT=AT, BT=BT, G=G)
+    with pytest.raises(wq.WqError):
+        plan.tune(0, "fused_32x32")
+    assert plan.k2_variant_name == variant
