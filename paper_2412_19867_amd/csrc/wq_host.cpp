@@ -203,34 +203,109 @@ bool full_form_layer(const wq_plan *p) {
     return (long)((p->T_pad + 31) / 32) * ((p->Cout_pad + 31) / 32) >= 512;
 }
 
-// The fused kernel's tile of a workgroup: one, two or four blocks of 16 tiles x 16 channels.  More blocks
-// read fewer operand bytes per product, and leave fewer workgroups to share out.  A launch is as slow as the
-// XCD with the most of it (32 CUs): `one`, `four` = workgroups there.  (us of the forward with one, two, four
-// blocks, from 200 layers drawn over the sizes of UNet and ResNet layers)
+// The rules below read the load of the fullest XCD (32 CUs): `one`, `two`, `four` = workgroups of the fused kernel
+// there with one, two and four blocks of 16 tiles x 16 channels, and were fitted to the forward times (us) of 9000
+// layers drawn over the sizes of UNet and ResNet layers, each under every variant.  A layer is written "16-tile
+// blocks x 16-channel blocks, G groups per tap".
+
+// The fused kernel's tile of a workgroup: one, two or four blocks.  More blocks read fewer operand bytes per product,
+// and leave fewer workgroups to share out; a launch is as slow as the XCD with the most of it.
 int fused_tile(const wq_plan *p) {
     const int G = p->groups;
-    const long one = fused_xcd_load(p, 1, 1), four = fused_xcd_load(p, 2, 2);
-    // a block each while every workgroup gets a CU of its own (28 tile blocks x 6, G 7: 19.2, 23.4, 26.7), and
-    // with a group or two per tap, whose operands a bigger tile hardly re-reads less (F(4,3) 380 x 6, G 2: 41,
-    // 43, 49; 98 x 60, G 1: 45, 54, 53)
+    const long one = fused_xcd_load(p, 1, 1), two = fused_xcd_load(p, 2, 1), four = fused_xcd_load(p, 2, 2);
+    const bool odd = p->Cout % 4 != 0;   // one channel per thread in the output stage
+    // a block each while every workgroup gets a CU of its own (28 x 6, G 7: 19.2, 23.4, 26.7 with one, two, four)
     if (one <= 32) return WQ_K2_FUSED_16x16;
     if (p->m == 4) {   // two workgroups of four blocks fit a CU, 64 an XCD
-        if (G <= 2 || (G == 3 && one <= 96)) return WQ_K2_FUSED_16x16;   // 62 x 12, G 3: 18.1, 20.1, 18.5
-        if (G == 3) return WQ_K2_FUSED_32x16;                            // 234 x 26: 70, 68, 73
-        if (G == 4) return four > 45 && four <= 64 ? WQ_K2_FUSED_32x32 : WQ_K2_FUSED_32x16;   // 176 x 10: 47, 45, 42
-        // with more groups four blocks once half of the CUs have them (38 x 12, G 11: 37, 32.5, 37; 62 x 78, G 7: 137,
-        // 116, 98; 38 x 24, G 6: 27.8, 26.5, 22.6), unless the last ones are a second workgroup on few CUs (44 x 30,
-        // G 8: 62, 50, 52) or a few more than fit at once (34 x 64, G 20: 136, 116, 118; 36 x 50, G 24: 154, 122, 140)
+        // with up to three groups a bigger tile hardly re-reads less (380 x 6, G 2: 41, 43, 49; 62 x 12, G 3: 18.1, 20.1,
+        // 18.5; 676 x 10, G 3: 124.6, 131.3, 126.4)
+        if (G <= 2 || (G == 3 && (one <= 96 || four > 32))) return WQ_K2_FUSED_16x16;
+        if (G == 3) return WQ_K2_FUSED_32x16;   // four on few CUs (30 x 26: 24.2, 23.4)
+        // pairs that have a CU each (18 x 24, G 6: 23.9, 21.7, 25.5; 48 x 10, G 11: 40.6, 35.9, 41.6)
+        if (two <= 32) return WQ_K2_FUSED_32x16;
+        // single blocks where two fill every CU and pairs would be a few more than one (36 x 14, G 12: 33.5, 42.5, 39)
+        if (one <= 64) return WQ_K2_FUSED_16x16;
+        // four groups: three single blocks on a CU against a pair on some and two pairs on the others (32 x 20: 22.4, 24.2);
+        // four blocks only where they fill the GPU once (176 x 10: 47, 45, 42)
+        if (G == 4) return one <= 96 ? WQ_K2_FUSED_16x16 : four > 48 && four <= 64 ? WQ_K2_FUSED_32x32 : WQ_K2_FUSED_32x16;
+        // with more groups four blocks (38 x 12, G 11: 37, 32.5, 37; 62 x 78, G 7: 137, 116, 98; 38 x 24, G 6: 27.8, 26.5,
+        // 22.6), unless the last ones are a second workgroup on few CUs (44 x 30, G 8: 62, 50, 52) or a few more than fit at
+        // once (34 x 64, G 20: 136, 116, 118; 36 x 50, G 24: 154, 122, 140; but over groups of 64 not in a third round, unless
+        // the weights stay in the L2: 76 x 54, G 8: 143, 121, 110; 198 x 30, G 13: 384, 392, 262)
         const long over = four % 64;
-        return four <= 16 || (four > 32 && four <= 45) || (four > 64 && over >= 1 && over <= 8) ? WQ_K2_FUSED_32x16
-                                                                                                : WQ_K2_FUSED_32x32;
+        const bool in_l2 = wq_fused_xcd_mode(p->T_pad, p->Cout_pad, p->Cin, p->n, p->Cout_pad / 32) == 2;
+        if ((four > 32 && four <= 48) || (four > 64 && over >= 1 && over <= 8 && (four <= 72 || p->g == 32 || in_l2)))
+            return WQ_K2_FUSED_32x16;
+        if (G <= 6 && p->g == 32 && odd && four > 128) return WQ_K2_FUSED_32x16;   // 360 x 36, 570 channels: 208, 191, 218
+        return WQ_K2_FUSED_32x32;
     }
     // F(6,3): one workgroup of four blocks fits a CU, 32 an XCD
-    if (G == 1) return four <= 42 ? WQ_K2_FUSED_16x16 : WQ_K2_FUSED_32x16;   // 132 x 34: 69.5, 69.6, 74
-    if (four <= 16) return G <= 3 ? WQ_K2_FUSED_16x16 : WQ_K2_FUSED_32x16;   // 36 x 12, G 4: 30, 29, 33
-    if (four <= 32) return WQ_K2_FUSED_32x32;                               // 222 x 4, G 3: 41, 39, 36
-    if (four <= 42) return G <= 3 ? WQ_K2_FUSED_16x16 : G == 4 ? WQ_K2_FUSED_32x16 : WQ_K2_FUSED_32x32;
-    return G == 2 ? WQ_K2_FUSED_32x16 : WQ_K2_FUSED_32x32;                  // 94 x 24, G 2: 51, 51, 56; 58 x 28, G 5: 81, 72, 63
+    if (G == 1) return four <= 192 || odd ? WQ_K2_FUSED_16x16 : WQ_K2_FUSED_32x16;   // 50 x 22: 26, 29, 33; 214 x 34: 110, 108, 118
+    if (two <= 32) return G <= 2 || (G == 3 && four <= 16) ? WQ_K2_FUSED_16x16 : WQ_K2_FUSED_32x16;   // 20 x 20, G 5: 32, 29, 35
+    if (four <= 32) return WQ_K2_FUSED_32x32;                                                         // 222 x 4, G 3: 41, 39, 36
+    // a second round of four blocks on few CUs (66 x 18, G 4 g 32: 46.3, 43.2, 46.2; 24 x 40, G 6 g 32: 43.4, 38.3, 51.3)
+    if (four <= 48) return G <= 3 && four <= 42 ? WQ_K2_FUSED_16x16 : WQ_K2_FUSED_32x16;
+    // a third (28 x 66, G 6 g 32: 86, 80, 94), and short reductions (94 x 24, G 2: 51, 51, 56; 200 x 28, G 3 g 32: 114, 110,
+    // 116; but where channels do not fill 128-byte lines 150 x 38, 598 channels: 184, 202, 140)
+    if (G == 2 || (G <= 6 && four > 64 && four <= 72) || (G == 3 && p->g == 32 && p->Cout % 32 == 0)) return WQ_K2_FUSED_32x16;
+    return WQ_K2_FUSED_32x32;   // 58 x 28, G 5: 81, 72, 63
+}
+
+// Layers of the row form's size: the row form, one fused launch or the tap form.  All three add the groups in the
+// same order, in fp32 up to 16 groups and in fp64 totals of four beyond, so the outputs are the same bits.
+int row_layer_form(const wq_plan *p) {
+    const int G = p->groups;
+    const long four = fused_xcd_load(p, 2, 2);
+    const bool odd = p->Cout % 4 != 0;   // (scalar, scattered stores of the row form's second kernel)
+    if (!variant_applicable(p, WQ_K2_FUSED_32x16)) return WQ_K2_LDS_ROW_64x64;
+    if (p->m == 4) {
+        // from nine groups on 384 channels and more the row form: 54 x 34, G 9, 59 against 75 of the fused kernel
+        if (p->Cout_pad >= 384 && G >= 9) return WQ_K2_LDS_ROW_64x64;
+        // long reductions, whose operands the fused kernel reads over and over: 138 x 10, G 27, row 204, fused 210,
+        // tap 177; 84 x 22, G 45 g 32, 206, 263, 167
+        if (G >= 26) return WQ_K2_LDS_TAP_64x64;
+        // a second (third) workgroup of four blocks on few CUs: 42 x 22, G 18, row 74, two blocks 92, tap 65; 56 x 18, G 15,
+        // 61, 80, 60.5; 24 x 54, G 8, 42.4, 50, 45; 134 x 8, 116 channels, G 14, 88, 107, 91; groups of 32 up to twelve
+        // go the other way: 236 x 6, G 11, 76, 70, 78
+        if ((four > 32 && four <= 48) || (four > 64 && four <= 72))
+            return G >= 17 || (odd && G > 8) ? WQ_K2_LDS_TAP_64x64
+                   : p->g == 32 && G <= 12   ? WQ_K2_FUSED_32x16
+                                             : WQ_K2_LDS_ROW_64x64;
+        // almost two on every CU: 100 x 18, G 19, row 139.6, four blocks 122, tap 125; 166 x 12, G 18 g 32, 136, 112, 109;
+        // 240 x 6, G 15, 147, 162, 156
+        if (four > 48 && four <= 64 && G >= 13) {
+            if (G >= 17) return WQ_K2_LDS_TAP_64x64;
+            if (p->g == 64) return WQ_K2_LDS_ROW_64x64;
+        }
+        return fused_tile(p);   // 250 x 8, G 17: row 132, four blocks 120; 44 x 30, G 8: 62, 50
+    }
+    // F(6,3), one workgroup of four blocks on a CU.  32 on the XCD or many times that: one fused launch (100 x 56, G 8 g 32,
+    // row 425, fused 252; 32 x 32, G 12, 80, 68), but for long reductions over groups of 64 (26 x 28, G 39, 188, 203, tap
+    // 162).  A second round on few CUs: the tap form (22 x 36, G 30 g 32, row 118, fused 156, tap 95; 50 x 24, G 69 g 32, 400,
+    // 418, 295; 26 x 36, G 8, 58, 73, 60), but for eight groups that come near filling it (58 x 22, 98, 85, 92)
+    if (four > 32 && four <= 64 && !(G == 8 && (p->g == 32 || four > 42))) return WQ_K2_LDS_TAP_64x64;
+    // (wide layers of a few tiles: 4 x 232, G 24, row 118, fused 138, tap 125)
+    if (p->T_pad <= 64 && p->g == 64 && G >= 17) return WQ_K2_LDS_ROW_64x64;
+    if (G >= 26 && p->g == 64) return WQ_K2_LDS_TAP_64x64;
+    return fused_tile(p);
+}
+
+// Layers of the full LDS form's size on which it is ahead of the fused kernel, which runs the others (120 x 38, G 5:
+// 100, 84).  Both add in the same order: the same bits.
+bool full_form_ahead(const wq_plan *p) {
+    const int G = p->groups;
+    const long four = fused_xcd_load(p, 2, 2);
+    const long long y_bytes = (long long)p->N * p->H * p->W * p->Cout * 4;
+    // channels that do not fill 128-byte lines: its plain stores join in the caches, the fused kernel's streaming ones
+    // write parts of lines (528 x 28, 420 channels, G 1: 99, fused 181; 334 x 16, 236 channels, G 2: 60, 66; 56 x 70, 1100
+    // channels, G 3: 49, 69; but 420 x 8, 108 channels, G 3: 60, 54)
+    const bool wide = wq_fused_xcd_mode(p->T_pad, p->Cout_pad, p->Cin, p->n, p->Cout_pad / 32) == 0;
+    if (p->Cout % 32 && (G <= 2 || (G <= 4 && y_bytes > 100000000) || (G == 3 && wide && p->Cout % 16))) return true;
+    // output far beyond the caches (508 x 22, G 1: 74.5, 83; 392 x 16, G 2: 71.5, 74; 340 x 44, G 3: 173, 184; but 850 x 10, G 1: 80, 74)
+    if (p->g == 64 && G <= 3 && y_bytes > 100000000 && p->Cout_pad >= 224) return true;
+    // its 128 workgroups on an XCD fit at once, and the fused kernel's are a few more than fit (66 x 56, G 4: 60, 68; 56 x 72,
+    // G 2: 42, 49; 44 x 68, G 6: 66, 70; but 180 x 24, G 4: 91, 79)
+    return p->g == 64 && four > 96 && four <= 144 && (G == 4 ? p->T_pad < 3 * p->Cout_pad : wide && G != 1 && G != 3);
 }
 
 int default_k2_variant(const wq_plan *p) {
@@ -238,32 +313,27 @@ int default_k2_variant(const wq_plan *p) {
         if (p->T_pad <= 32 || ((p->T_pad % 64) == 32 && p->T_pad <= 160)) return WQ_K2_GEMM_32x128;
         return (p->g < 128 && p->m != 2) ? WQ_K2_LDS_TAP_64x64 : WQ_K2_GEMM_64x64;
     }
-    // The row form with operand tiles shared through LDS: measured ahead of the others where its
-    // workgroups (64 tiles x 64 channels x one tap row) fill the GPU once at two to three per CU
-    // and each of them walks a reduction long enough to pay for the second kernel.
-    // (not for F(6,3), whose fused kernel with four blocks is ahead: 100 tile blocks x 56, G 8 g 32, 425 against
-    // 252 us, 36 x 40, G 13, 132, 105; nor on fewer than 384 channels, where F(4,3)'s is: 250 x 8, G 17, 132,
-    // 120; but 84 x 24, G 25, 131, 152; nor up to eight groups, which a wave sums in fp32: 44 x 30, G 8, 62, 50;
-    // 54 x 34, G 9, 59, 75)
-    // (layers that cannot run the fused kernel's tiles of two and four blocks, whose A^T has no paired columns, keep
-    // the form that runs any A^T: 28x25x34 704->384 F(6,3) 112 us, with one block 132)
-    const bool row = row_form_layer(p), tiles = variant_applicable(p, WQ_K2_FUSED_32x16);
-    if (row && !tiles) return WQ_K2_LDS_ROW_64x64;
-    if (row && p->m == 4 && p->Cout_pad >= 384 && p->groups >= 9) return WQ_K2_LDS_ROW_64x64;
+    if (row_form_layer(p)) return row_layer_form(p);
+    // the fused kernel's tiles of two and four blocks (paired A^T, one K-step per group): without them a layer keeps
+    // the form that runs it for any A^T (28x25x34 704->384 F(6,3): row form 112 us, one block per wave 132)
+    const bool tiles = variant_applicable(p, WQ_K2_FUSED_32x16);
     // With few tiles the Winograd-domain result is small next to the operands, and a tiled GEMM
     // per tap plus a separate output transform beats the fused kernel; so it does for very wide
     // layers and for groups of 128 and more, where the fused kernel's register tiles re-read the
     // operands too often.
-    // (Groups of 32: up to a handful of groups the fused kernel's one launch is ahead once its blocks fill
-    // half of the CUs, later for the longer rows of F(6,3): F(4,3) 6 x 22 tile and channel blocks, G 5, 14.1
-    // against 12.3 us; 2 x 6, G 6, 12.5, 12.9; 14 x 16, G 13, 22.6, 23.3; F(6,3) 26 x 8, G 7, 27, 22.4; 14 x 6,
-    // G 7, 20.7, 21.3; 16 x 34, G 4, 34.7, 27; 26 x 6, G 12, 28.7, 30.5)
+    // (Groups of 32: up to a handful of groups the fused kernel's one launch is ahead, later for the longer rows of
+    // F(6,3): F(4,3) 8 x 20 tile and channel blocks, G 5, 15.6 against 13.2 us; 2 x 6, G 6, 12.5, 12.9; 14 x 16, G 13, 22.6,
+    // 23.3; F(6,3) 26 x 8, G 7, 27, 22.4; 24 x 14, G 7, 32.7, 28.6; 14 x 18, G 7, 26.5, 28.9; 16 x 34, G 4, 34.7, 27; 26 x 6,
+    // G 12, 28.7, 30.5; a second round of workgroups on few CUs with channels that do not fill 128-byte lines, 18 x 58, 921
+    // channels, G 6, 54, 71)
     const long blocks = (long)(p->T_pad / 16) * (p->Cout_pad / 16);
-    const bool few_groups = tiles && p->T_pad >= 128 && !((p->T_pad % 64) == 32 && p->T_pad <= 160) &&
-                            (p->m == 4 ? p->groups <= 5 || (p->groups == 6 && blocks >= 60)
-                                       : (p->groups <= 6 && blocks >= 90) || (p->groups <= 8 && blocks >= 180));
-    const bool two_kernel = !row && ((p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128 && !few_groups))) ||
-                                     p->Cin >= 1024 || p->g >= 128);
+    const long one = fused_xcd_load(p, 1, 1), four = fused_xcd_load(p, 2, 2);
+    bool few_groups = tiles && p->T_pad >= 128 && !((p->T_pad % 64) == 32 && p->T_pad <= 160);
+    if (p->m == 4) few_groups = few_groups && (p->groups <= 5 || (p->groups == 6 && blocks >= 60));
+    else few_groups = few_groups && ((p->groups <= 6 && blocks >= 90) || (p->groups <= 8 && (blocks >= 330 || (blocks >= 180 && one <= 32)))) &&
+                      !(p->Cout % 32 && four > 32 && four <= 48);
+    const bool two_kernel = (p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128 && !few_groups))) ||
+                            p->Cin >= 1024 || p->g >= 128;
     // one group of 128 or 256 per tap: nothing is re-read between groups, and the product of a tap
     // written out costs more than the fused kernel's one block per wave (22x54x54 128->96 F(2,3) 48
     // against 69 us, 10x20x20 128->70 F(4,3) 12.5 against 13.9; F(6,3)'s 64 taps go either way; a
@@ -295,9 +365,7 @@ int default_k2_variant(const wq_plan *p) {
             return WQ_K2_LDS_TAP_64x64;
         return WQ_K2_GEMM_64x64;
     }
-    // two groups per tap and output far beyond the caches: the full LDS form, whose plain stores fill whole lines
-    // (32x56x56 128->256 71.5 us, fused 74.4, 75.5, 76.1 with one, two, four blocks; 8x96x96 58.6, 55.4, 58.3, 56.7)
-    if (full_form_layer(p) && (!tiles || (p->groups == 2 && p->T_pad >= 6144))) return WQ_K2_LDS_FULL_32x32;
+    if (full_form_layer(p) && (!tiles || full_form_ahead(p))) return WQ_K2_LDS_FULL_32x32;
     if (!tiles) return WQ_K2_FUSED_16x16;
     // a wave's reduction split in two where every block has a CU of its own and the slices are short: up to five
     // groups each, since longer slices are longer chains of fp32 additions than the one wave's fp64 totals of four

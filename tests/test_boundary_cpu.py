@@ -420,3 +420,44 @@ def test_layers_whose_output_matrix_has_no_paired_columns_keep_the_forms_that_ru
     with pytest.raises(wq.WqError):
         plan.tune(0, "fused_32x32")
     assert plan.k2_variant_name == variant
+
+
+@pytest.mark.parametrize("shape,variant", [
+    # N  H    W   Cin  Cout m  g      layers of the row form's size: us of the row form, one fused launch, the tap form
+    ((23, 21, 16, 704, 936, 6, 64), "lds_tap_64x64"),     # 92, 96, 74
+    ((7, 41, 41, 544, 820, 6, 32), "lds_tap_64x64"),      # 116, 113, 88
+    ((18, 21, 29, 1664, 544, 6, 32), "lds_tap_64x64"),    # 188, 260, 144
+    ((2, 32, 32, 1280, 2560, 6, 64), "fused_32x32"),      # 137, 80, 107
+    ((2, 51, 65, 256, 1120, 6, 32), "fused_32x16"),       # 65, 44, 51
+    ((1, 18, 18, 1536, 3712, 6, 64), "lds_row_64x64"),
+    ((4, 66, 90, 2240, 320, 4, 64), "lds_tap_64x64"),     # 238, 405, 214
+    ((2, 100, 83, 736, 320, 4, 32), "lds_tap_64x64"),     # 78, 100, 74
+    ((27, 24, 22, 896, 320, 4, 64), "lds_row_64x64"),     # 63, 78, 67
+    ((16, 34, 34, 1024, 352, 4, 64), "lds_row_64x64"),    # 96, 142, 100
+    ((6, 96, 109, 288, 96, 4, 32), "fused_32x16"),        # 70, 60, 76
+    # of the full LDS form's size: us of that form, one fused launch
+    ((11, 82, 69, 128, 1012, 4, 64), "lds_full_32x32"),   # 163, 212
+    ((19, 50, 50, 256, 1116, 4, 64), "lds_full_32x32"),   # 215, 259
+    ((6, 38, 56, 384, 864, 4, 64), "lds_full_32x32"),     # 67, 72
+    ((8, 72, 66, 192, 544, 4, 64), "fused_16x16"),        # 79, 69
+    ((16, 96, 119, 64, 64, 4, 32), "fused_16x16"),        # 51, 42
+    ((2, 128, 128, 320, 320, 4, 64), "fused_32x32"),
+    # short reductions over groups of 32 on few tiles: us of the tap form, one fused launch
+    ((11, 24, 24, 224, 320, 6, 32), "lds_tap_64x64"),     # 26, 29
+    ((4, 56, 56, 128, 537, 6, 32), "lds_tap_64x64"),      # 45, 52
+    ((12, 34, 33, 192, 1056, 6, 32), "fused_32x16"),      # 76, 60
+    ((3, 31, 31, 128, 992, 4, 32), "fused_16x16"),        # 30, 19
+    # the fused kernel's tile: us with one, two, four blocks
+    ((4, 47, 47, 384, 202, 4, 32), "fused_16x16"),        # 34, 43, 39
+    ((7, 36, 36, 256, 163, 4, 64), "fused_16x16"),        # 20, 24, 24
+    ((1, 88, 114, 96, 352, 4, 32), "fused_16x16"),        # 19, 24, 27
+    ((2, 75, 75, 608, 160, 4, 32), "fused_32x16"),        # 45, 39, 50
+    ((7, 63, 82, 160, 763, 4, 32), "fused_32x16"),        # 122, 109, 137
+    ((3, 108, 66, 64, 544, 6, 64), "fused_16x16"),        # 29, 33, 34
+    ((2, 67, 67, 128, 288, 6, 64), "fused_16x16"),        # 21, 21, 25
+    ((23, 33, 45, 192, 224, 6, 32), "fused_32x16"),       # 47, 43, 55
+    ((26, 21, 20, 96, 1056, 6, 32), "fused_32x16"),       # 45, 43, 55
+], ids=lambda v: "%dx%dx%d_%d-%d_F%d_g%d" % v if isinstance(v, tuple) else v)
+def test_a_layer_takes_the_faster_of_the_forms_that_add_in_its_order(wq, shape, variant):
+    """Layers on both sides of the lines between the row, tap, full and fused forms."""
+    assert wq.Plan(*shape).k2_variant_name == variant
