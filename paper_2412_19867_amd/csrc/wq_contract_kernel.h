@@ -73,10 +73,11 @@ struct Args {
     wq_dump dump;   // debug calls: where to store the int32 group sums (P == nullptr otherwise)
     int H, W, Cin, Cout, TH, TW, T, T_pad, Cout_pad, log2g;
     int nTB, nOB, xcd_mode, band;
-    // Store y with plain instead of streaming stores: the next layer's input kernel finds 32 to 64 MB in the
-    // caches (2x128x128 320->320, chained: this kernel 42.1 -> 43.4 us, that one 20.8 -> 16.7).  Smaller outputs
-    // gain as much as they lose (32x56x56 64->64: 15.0 -> 16.4 and 16.2 -> 14.8), far larger ones lose (115 MB in
-    // half lines: 44 -> 68).
+    // Store y with plain instead of streaming stores: the next layer's input kernel finds 32 to 56 MB in the caches.
+    // Whole forward with four blocks, streaming and plain, in a chain of such layers and on other buffers each time:
+    // 24 MB (2x96x96 320->320) 40.4, 39.4 and 38.2, 39.1 us; 42 MB (2x128x128) 64.0, 61.3 and 59.6, 60.4; 55 MB
+    // (2x128x104 512->512) 97.8, 93.7 and 91.0, 91.9; 63 MB (3x128x128 320->320) 85.7, 83.2 and 78.7, 86.1; 126 MB
+    // 159, 168 and 157, 162.
     int plain_y;
     int dense_rows;   // see wq_plan
 };
@@ -542,7 +543,7 @@ hipError_t launch_m(const wq_plan *p, hipStream_t s, const int8_t *Xq, const flo
     a.nTB = a.nOB = a.xcd_mode = a.band = 0;
     {   // see finish
         const long long bytes = (long long)p->N * p->H * p->W * p->Cout * 4;
-        a.plain_y = M == 4 && p->k2_variant == WQ_K2_FUSED_32x32 && bytes >= (32LL << 20) && bytes <= (64LL << 20);
+        a.plain_y = M == 4 && p->k2_variant == WQ_K2_FUSED_32x32 && bytes >= (32LL << 20) && bytes <= (56LL << 20);
     }
     const bool k64 = p->kstep == 64, cpg1 = p->g == p->kstep;
     const int variant = p->k2_variant;   // a fused one, checked for this plan when it was chosen

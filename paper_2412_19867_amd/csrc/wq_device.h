@@ -49,7 +49,8 @@ __device__ __forceinline__ int mad24(int m, int v, int c) {
 
 // Store of an output value: streaming (non-temporal), the layer does not read y again.  (Plain
 // stores make the next layer's input kernel faster when it follows at once, and this layer's
-// output stage slower by as much: measured equal on a chained stack, 4-8 % slower elsewhere.)
+// output stage slower: a gain only where y is large and still fits the caches, where the fused kernel's
+// four-block form takes them.)
 template <typename T>
 __device__ __forceinline__ void store_y(T v, T *p) {
     __builtin_nontemporal_store(v, p);
