@@ -72,7 +72,7 @@ struct Args {
     float *y;
     wq_dump dump;   // debug calls: where to store the int32 group sums (P == nullptr otherwise)
     int H, W, Cin, Cout, TH, TW, T, T_pad, Cout_pad, log2g;
-    int nTB, nOB, xcd_mode, band;
+    wq_fused_blocks blocks;
     // Store y with plain instead of streaming stores: the next layer's input kernel finds 32 to 56 MB in the caches.
     // Whole forward with four blocks, streaming and plain, in a chain of such layers and on other buffers each time:
     // 24 MB (2x96x96 320->320) 40.4, 39.4 and 38.2, 39.1 us; 42 MB (2x128x128) 64.0, 61.3 and 59.6, 60.4; 55 MB
@@ -112,22 +112,8 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
 
     // ---- which block (uniform) ----
     int tb, ob;
-    {
-        const int id = blockIdx.x, xcd = id & 7, s = id >> 3;
-        if (a.xcd_mode != 2) {
-            // in bands of the other operand's blocks: all of the XCD's own blocks pass a band while it is in the L2
-            const int others = a.xcd_mode == 0 ? a.nTB : a.nOB, own = ((a.xcd_mode == 0 ? a.nOB : a.nTB) + 7) >> 3;
-            const int first = s / (own * a.band) * a.band, r = s - first * own, width = min(a.band, others - first);
-            const int mine8 = (r / width) * 8 + xcd, other = first + r % width;
-            ob = a.xcd_mode == 0 ? mine8 : other;
-            tb = a.xcd_mode == 0 ? other : mine8;
-        } else {   // 4 parts of the tiles x 2 halves of the channels
-            const int hob = (a.nOB + 1) >> 1;
-            tb = (s / hob) * 4 + (xcd >> 1);
-            ob = (xcd & 1) * hob + s % hob;
-        }
-        if (tb >= a.nTB || ob >= a.nOB) return;
-    }
+    wq_fused_block(a.blocks, blockIdx.x, tb, ob);
+    if (tb >= a.blocks.nTB || ob >= a.blocks.nOB) return;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = w % n, ks = w / n;   // tap row, K slice (uniform)
@@ -478,17 +464,8 @@ template <int M, bool K64, bool CPG1, bool WIDE, bool ATSP, int NT, int NO, int 
 hipError_t launch_one(const Args &a, hipStream_t s) {
     // the debug entry point runs the same template with the stores of the int32 sums compiled in
     Args b = a;
-    b.nTB = a.T_pad / (16 * NT);
-    b.nOB = a.Cout_pad / (16 * NO);
-    b.xcd_mode = wq_fused_xcd_mode(a.T_pad, a.Cout_pad, a.Cin, M + 2, b.nOB);
-    {   // all blocks where they fit an XCD's 4 MB L2 (all taps of them), otherwise bands of 1 MB
-        const long bytes = (long)(M + 2) * (M + 2) * a.Cin * 16 * (b.xcd_mode == 0 ? NT : NO);
-        const int others = b.xcd_mode == 0 ? b.nTB : b.nOB;
-        b.band = others * bytes <= (4L << 20) ? others : max(1, (int)((1L << 20) / bytes));
-    }
-    const int split = b.xcd_mode == 0 ? b.nOB : b.nTB, other = b.xcd_mode == 0 ? b.nTB : b.nOB;
-    const unsigned grid = b.xcd_mode == 2 ? (unsigned)(((b.nTB + 3) / 4) * ((b.nOB + 1) / 2) * 8)
-                                          : (unsigned)(((split + 7) / 8) * 8 * other);
+    b.blocks = wq_fused_launch_blocks(a.T_pad, a.Cout_pad, a.Cin, M + 2, NT, NO);
+    const unsigned grid = wq_fused_grid(b.blocks);
     if (a.dump.P)
         hipLaunchKernelGGL((k_contract_output<M, K64, CPG1, WIDE, ATSP, true, NT, NO, KS, D, ONE>), dim3(grid),
                            dim3(64 * (M + 2) * KS), 0, s, b);
@@ -540,7 +517,7 @@ hipError_t launch_m(const wq_plan *p, hipStream_t s, const int8_t *Xq, const flo
     a.T = p->T; a.T_pad = p->T_pad; a.Cout_pad = p->Cout_pad;
     a.log2g = 0;
     while ((1 << a.log2g) < p->g) ++a.log2g;
-    a.nTB = a.nOB = a.xcd_mode = a.band = 0;
+    a.blocks = {};
     {   // see finish
         const long long bytes = (long long)p->N * p->H * p->W * p->Cout * 4;
         a.plain_y = M == 4 && p->k2_variant == WQ_K2_FUSED_32x32 && bytes >= (32LL << 20) && bytes <= (56LL << 20);

@@ -8,6 +8,7 @@
 #include <atomic>
 
 #include "wq.h"
+#include "wq_fused_blocks.h"
 
 // Transform matrices as handed to kernels by value (kernarg segment -> SGPRs).
 struct wq_xf {
@@ -108,16 +109,6 @@ inline bool wq_is_lds_row_variant(int v) { return v >= WQ_K2_LDS_ROW_64x64 && v 
 inline bool wq_is_lds_tap_variant(int v) { return v == WQ_K2_LDS_TAP_64x64 || v == WQ_K2_LDS_TAP_128x128; }
 inline bool wq_is_lds_variant(int v) {
     return wq_is_lds_full_variant(v) || wq_is_lds_row_variant(v) || wq_is_lds_tap_variant(v);
-}
-
-// How the fused kernel's workgroups are shared out to the eight XCDs: 0 = every 8th block of output
-// channels each, 1 = every 8th block of tiles (whichever operand is larger), 2 = every 4th block of tiles
-// and one half of the channels: where all taps' weights would fill an XCD's 4 MB L2 on their own, half of
-// them stays resident next to the streaming activations.  nOB: blocks of output channels.
-inline int wq_fused_xcd_mode(int T_pad, int Cout_pad, int Cin, int n, int nOB) {
-    const long wbytes = (long)Cout_pad * Cin, xbytes = (long)T_pad * Cin, wall = wbytes * n * n;
-    if (wbytes >= xbytes) return 0;
-    return wall > (5L << 19) && wall <= (8L << 20) && nOB >= 2 ? 2 : 1;
 }
 
 // Which part of the int32 group sums a debug call stores: taps [tap0, tap0+ntaps) x tiles
