@@ -20,10 +20,10 @@
 // finishes Y[a][b] = sum_i A^T[a][i] (sum_ks R_{i,ks}[b]), adds bias and stores
 // NHWC with the ragged right/bottom edge masked.
 //
-// What bounds it: a 1 KiB operand load costs the CU's load path 17 cycles, whatever its width a load costs 8
-// at least, and a SIMD issues a block's 12 dequantization instructions and its MFMA in 46 (the two do not
-// overlap).  With NT x NO blocks of operands per wave the load path takes 17 (NT + NO) / (NT NO) cycles of a
-// CU per block, 34 with one and 17 with four, against 11.5 of its four SIMDs.
+// What bounds it: a 1 KiB operand load costs the CU's load path 17 cycles, one of a word per lane 8, and a SIMD
+// issues a block's 12 dequantization instructions and its MFMA in 46 (the two do not overlap).  With NT x NO
+// blocks of operands per wave the load path takes 17 (NT + NO) / (NT NO) cycles of a CU per block, 34 with one
+// and 17 with four, against 11.5 of its four SIMDs.
 //
 // A wave waits for nothing but its own loads, so what counts is that the compiler can count them:
 // the request of the K-step D ahead is unconditional, a walk is whole rounds of n K-steps, and the request
@@ -35,19 +35,21 @@
 // Scales of groups of one K-step: a round's scales of n groups come in one load per tensor straight into LDS
 // that is the wave's own (no barrier: the wave's count of loads in flight says when they are there), a round
 // ahead, and reach the lanes as broadcast LDS reads, which cost neither the load path nor the vector ALU
-// anything.  (One word per lane, load and K-step, spread by DPP, took two of five loads, and a DPP
-// instruction among others keeps the SIMD from issuing for two waves at once: 2.4 -> 4.4 cycles for the
-// instructions around it.)  Kernel, before and after, with one, two and four blocks: 2x128x128 320->320 F(4,3)
-// 52.2, 44.8, 51.6 -> 49.9, 42.6, 41.5 us; 32x56x56 64->64 F(6,3) 18.2, 16.4, 16.9 -> 17.5, 15.7, 14.6;
-// 1x32x32 64->64 F(4,3) 5.5 -> 4.8.  Longer groups keep the DPP form.
+// anything.  (One word per lane, load and K-step, spread by DPP, took two of five loads, and one DPP
+// instruction in twelve keeps the SIMD from issuing for two waves at once: 2.9 -> 4.4 cycles an instruction.)
+// This kernel alone under a trace, with that form and now, one, two and four blocks: 2x128x128 320->320 F(4,3)
+// 54.4, 48.2, 51.2 -> 53.7, 46.5, 44.5 us (46 with plain stores of y, in a chain of such layers); 32x56x56 64->64
+// F(6,3) 18.3, 16.3, 16.6 -> 18.0, 16.7, 14.9; 1x32x32 64->64 F(4,3), one block, 5.3 -> 5.2.  Longer groups keep the
+// DPP form.
 //
 // Workgroups are numbered so that the eight XCDs (which receive consecutive
 // workgroup ids round-robin and have private L2s) each own a slice of the
 // larger operand: with xcd_mode 0 an XCD owns every 8th block of output
 // channels (weights stay in its L2), with xcd_mode 1 every 8th block of tiles,
 // with xcd_mode 2 every 4th block of tiles and one half of the channels.  Where the other operand does not fit
-// that L2 it passes in bands of 1 MB (all of the XCD's own blocks meet a band before the next comes): 26x46 tile
-// and channel blocks of 960 channels 73 -> 56 us, 80 x 62 blocks of 448 140 -> 98.
+// that L2 it passes in bands of 1 MB (all of the XCD's own blocks meet a band before the next comes).  Whole forward
+// without and with, one, two and four blocks: 5x64x64 448->992 F(4,3) 217, 140, 131 -> 143, 125, 102 us; 5x96x96 448->992
+// F(6,3) 388, 244, 232 -> 267, 212, 180; 2x96x96 512->640 152, 114, 100 -> 107, 99, 88.
 #pragma once
 
 #include <type_traits>
@@ -388,8 +390,8 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
 
     // ---- output transform across tap rows, 16 tiles and BP columns at a time ----
     // A thread forms V neighbouring channels of one column of a tile.  Four with two channel blocks (a store
-    // instruction covers 8 lines of 128 bytes: 2x128x128 320->320 42.1 us, with one channel per thread 54), one
-    // with a single block (4 half lines; four channels per thread, 16 half lines: 8x60x60 64->992 F(6,3) 45, 44).
+    // instruction covers 8 lines of 128 bytes: 2x128x128 320->320 44.6 us, with one channel per thread 48.7; 32x56x56
+    // 64->64 F(6,3) 15.0, 15.9), one with a single block (4 half lines, against 16 half lines).
     auto finish = [&](auto vec, auto plain, int nt, int p) {
         constexpr int V = decltype(vec)::value, Q = 16 * NO / V, PC = 16 * Q;   // PC threads form a column
         constexpr int TH = 64 * NW, COLS = TH >= PC ? TH / PC : 1;              // columns at a time

@@ -301,7 +301,8 @@ bool full_form_ahead(const wq_plan *p) {
     // channels, G 3: 49, 69; but 420 x 8, 108 channels, G 3: 60, 54)
     const bool wide = wq_fused_xcd_mode(p->T_pad, p->Cout_pad, p->Cin, p->n, p->Cout_pad / 32) == 0;
     if (p->Cout % 32 && (G <= 2 || (G <= 4 && y_bytes > 100000000) || (G == 3 && wide && p->Cout % 16))) return true;
-    // output far beyond the caches (508 x 22, G 1: 74.5, 83; 392 x 16, G 2: 71.5, 74; 340 x 44, G 3: 173, 184; but 850 x 10, G 1: 80, 74)
+    // output far beyond the caches (508 x 22, G 1: 74.5, 83; 392 x 16, G 2: 71.5, 74; 340 x 44, G 3: 173, 184; but 850 x
+    // 10, G 1: 80, 74)
     if (p->g == 64 && G <= 3 && y_bytes > 100000000 && p->Cout_pad >= 224) return true;
     // its 128 workgroups on an XCD fit at once, and the fused kernel's are a few more than fit (66 x 56, G 4: 60, 68; 56 x 72,
     // G 2: 42, 49; 44 x 68, G 6: 66, 70; but 180 x 24, G 4: 91, 79)
@@ -330,8 +331,8 @@ int default_k2_variant(const wq_plan *p) {
     const long one = fused_xcd_load(p, 1, 1), four = fused_xcd_load(p, 2, 2);
     bool few_groups = tiles && p->T_pad >= 128 && !((p->T_pad % 64) == 32 && p->T_pad <= 160);
     if (p->m == 4) few_groups = few_groups && (p->groups <= 5 || (p->groups == 6 && blocks >= 60));
-    else few_groups = few_groups && ((p->groups <= 6 && blocks >= 90) || (p->groups <= 8 && (blocks >= 330 || (blocks >= 180 && one <= 32)))) &&
-                      !(p->Cout % 32 && four > 32 && four <= 48);
+    else few_groups = few_groups && !(p->Cout % 32 && four > 32 && four <= 48) &&
+                      ((p->groups <= 6 && blocks >= 90) || (p->groups <= 8 && blocks >= (one <= 32 ? 180 : 330)));
     const bool two_kernel = (p->T_pad <= 512 && (p->Cin >= 512 || (p->g == 32 && p->Cin >= 128 && !few_groups))) ||
                             p->Cin >= 1024 || p->g >= 128;
     // one group of 128 or 256 per tap: nothing is re-read between groups, and the product of a tap

@@ -108,3 +108,19 @@ def test_a_fused_form_the_caller_picks_sums_alike_on_layers_of_every_size(shape)
             continue
         top = forward_with(half, variant, x[:, :H // 2].contiguous(), w, bias)[1]
         assert torch.equal(y[:, :rows], top[:, :rows]), variant
+
+
+@pytest.mark.parametrize("variant", FUSED)
+def test_an_output_that_starts_at_any_float(variant):
+    """The output stage stores four channels at a time; y need not start at a multiple of 16 bytes."""
+    shape = (2, 13, 11, 128, 40, 4, 64)
+    x, w, bias = inputs(shape)
+    want = forward_with(shape, variant, x, w, bias)[1]
+    plan = wqmod.Plan(*shape).tune(0, variant)
+    blob, ws = plan.alloc_blob(), plan.alloc_workspace()
+    plan.weight_prepare(w, bias, blob)
+    for at in (1, 2, 3):
+        store = torch.full((want.numel() + 8,), float("nan"), device="cuda")
+        plan.forward(x, blob, ws, store[at:at + want.numel()].view(want.shape))
+        assert torch.equal(store[at:at + want.numel()].view(want.shape), want)
+        assert torch.isnan(store[:at]).all() and torch.isnan(store[at + want.numel():]).all()
