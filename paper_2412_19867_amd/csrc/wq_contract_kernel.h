@@ -64,6 +64,10 @@ namespace {   // every including file instantiates its own tile size; nothing he
 template <int M, int NT, int NO, bool K64 = true>
 constexpr int kDepth = NT * NO == 4 || (M == 6 && NT * NO == 2 && K64) ? 2 : (M == 4 ? 3 : 4);
 
+// the instances that Args::plain_y is for
+template <int M, int NT, int NO>
+constexpr bool kPlainY = M == 4 && NT == 2 && NO == 2;
+
 struct Args {
     wq_xf xf;
     const int8_t *Xq;
@@ -443,23 +447,36 @@ __global__ __launch_bounds__(64 * (M + 2) * KS) void k_contract_output(const Arg
     // four channels per thread where every pixel's channels start at a multiple of 16 bytes, otherwise one:
     // scalar stores of a lane's four channels would be scattered
     const bool vec4 = (a.Cout & 3) == 0;
+    constexpr int P = M / BP;
+    // One copy of this stage's code for all passes.  With a copy each the kernels had 29 to 35 KB in place of 13 to 21,
+    // which a program of several layers fetches into the instruction cache (64 KB for two CUs) on every call: a
+    // step of the ResNet-18 layers, F(6,3), batch 32, 111.2 -> 106.8 us, the kernel of its 56x56 layer 19.7 -> 15.2 there
+    // and 15.1 either way when that layer repeats.
+#pragma unroll 1
+    for (int pass = 0; pass < NT * P; ++pass) {
+        __syncthreads();   // the scales, or the tiles before, have been read
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int p = 0; p < M / BP; ++p) {
-            __syncthreads();   // the scales, or the tiles before, have been read
+            for (int p = 0; p < P; ++p)
+                if (pass == nt * P + p) {
 #pragma unroll
-            for (int bp = 0; bp < BP; ++bp)
+                    for (int bp = 0; bp < BP; ++bp)
 #pragma unroll
-                for (int no = 0; no < NO; ++no)
-                    *reinterpret_cast<float4 *>(&Rs[(w * BP + bp) * RSW + l16 * RS + 16 * no + 4 * q]) = R[p * BP + bp][no][nt];
-            __syncthreads();
-            constexpr std::integral_constant<int, NO == 2 ? 4 : 1> many;
-            constexpr std::integral_constant<int, 1> one;
-            if (!vec4) finish(one, std::false_type{}, nt, p);
-            else if (a.plain_y) finish(many, std::true_type{}, nt, p);   // (a branch at the store would be merged)
-            else finish(many, std::false_type{}, nt, p);
+                        for (int no = 0; no < NO; ++no)
+                            *reinterpret_cast<float4 *>(&Rs[(w * BP + bp) * RSW + l16 * RS + 16 * no + 4 * q]) = R[p * BP + bp][no][nt];
+                }
+        __syncthreads();
+        constexpr std::integral_constant<int, 1> one;
+        if constexpr (NO == 2) {
+            constexpr std::integral_constant<int, 4> many;
+            if (!vec4) finish(one, std::false_type{}, pass / P, pass % P);
+            else if (kPlainY<M, NT, NO> && a.plain_y) finish(many, std::true_type{}, pass / P, pass % P);   // (a branch at the store would be merged)
+            else finish(many, std::false_type{}, pass / P, pass % P);
+        } else {
+            finish(one, std::false_type{}, pass / P, pass % P);
         }
+    }
 }
 
 template <int M, bool K64, bool CPG1, bool WIDE, bool ATSP, int NT, int NO, int KS, int D, bool ONE>
